@@ -296,7 +296,7 @@ int sv_adjoint_grad(sv_handle h, sv_handle lam, const sv_op *ops, int n_ops,
                     const double *params, int n_params, int n_terms, const uint64_t *z_masks,
                     const double *coeffs, double *host_loss, double *host_grad);
 
-/* Batches of independent circuits (one persistent launch).
+/* Batches of independent circuits (one graph launch).
  *
  * sv_batch_create compiles n_circuits circuits: circuit i acts on its own
  * register of widths[i] qubits (4..30 for SV_C64, 3..30 for SV_C128), starts
@@ -305,8 +305,9 @@ int sv_adjoint_grad(sv_handle h, sv_handle lam, const sv_op *ops, int n_ops,
  * result of circuit i is <psi_i| Z^{z_mask} |psi_i> in FP64.  Circuits whose
  * state fits in one workgroup's LDS never touch HBM; wider ones keep their
  * state in device memory.  The whole batch is captured once as a HIP graph
- * holding one persistent kernel whose workgroups take circuits from a device
- * queue, longest first.  flags: SV_BATCH_KEEP_STATES also stores every final
+ * holding one persistent kernel, whose workgroups take the LDS-resident
+ * circuits from a device queue, longest first, and one kernel per pass index
+ * over the tiles of all wider circuits.  flags: SV_BATCH_KEEP_STATES also stores every final
  * state (for sv_batch_state).  All work is ordered on hip_stream.
  * sv_batch_run launches the graph (asynchronous); sv_batch_results waits and
  * copies the n_circuits results to host memory; sv_batch_output returns

@@ -1,15 +1,21 @@
-// Batched circuits: one persistent launch runs thousands of independent
-// circuits of different widths.
+// Batched circuits: one graph launch runs thousands of independent circuits
+// of different widths.
 //
-// Workgroups pop circuit indices from a device queue (an atomic counter) in
-// the host's longest-first order until the queue is empty, so every
-// workgroup exits once all circuits are taken.  A circuit whose state fits
-// in one LDS tile (up to 2^13 complex64 / 2^12 complex128 amplitudes) starts
-// from |0...0> directly in LDS, runs all its gates there and reduces its
-// Z-string expectation without touching HBM.  A wider circuit keeps its
-// state in HBM and runs the host's tile passes over it; the first pass
-// synthesises |0...0> instead of loading it, and the last pass accumulates
-// the expectation while it stores the final tiles.
+// A circuit whose state fits in one LDS tile (up to 2^13 complex64 / 2^12
+// complex128 amplitudes) starts from |0...0> directly in LDS, runs all its
+// gates there and reduces its Z-string expectation without touching HBM: a
+// persistent kernel's workgroups pop such circuits from a device queue (an
+// atomic counter) in the host's longest-first order until it is empty.
+// Wider circuits keep their states in HBM and advance together, one launch
+// per pass index over the tiles of all of them; the first pass synthesises
+// |0...0> instead of loading it, and the last writes one expectation partial
+// per tile, which a final kernel adds up in tile order.
+//
+// With a wide circuit walked by one workgroup the batch took as long as its
+// widest circuit alone, whatever the other compute units did: 1024 circuits
+// of 10 to 18 qubits took 11.9 ms on the device, with one launch per pass
+// 5.4 ms; 4096 circuits of 10 to 20 qubits 106 and 85 ms; one 20-qubit
+// circuit alone 43 and 0.32 ms.
 #include "sv_internal.hpp"
 #include "tile_sweep.hpp"
 
@@ -19,27 +25,6 @@
 namespace sv {
 
 constexpr int kBatchThreads = 512;
-
-template <typename T>
-struct BV;
-template <>
-struct BV<float> {
-    using type = float4;
-    static constexpr int amps = 2, bits = 1;
-};
-template <>
-struct BV<double> {
-    using type = double2;
-    static constexpr int amps = 1, bits = 0;
-};
-
-__device__ __forceinline__ uint64_t btile_addr(const TileSpec &sp, uint64_t base, uint32_t l) {
-    uint64_t g = base | (l & ((1u << sp.L) - 1u));
-    const uint32_t hi = l >> sp.L;
-    for (int i = 0; i < sp.K; ++i)
-        if ((hi >> i) & 1u) g |= 1ull << sp.high[i];
-    return g;
-}
 
 __device__ __forceinline__ double bwave_sum(double x) {
 #pragma unroll
@@ -134,8 +119,30 @@ __device__ void batch_tile(cpx<T> *state, cpx<T> *lds, const TileSpec &sp, int m
     }
 }
 
+// Sum over the workgroup in a fixed order, in thread 0.
+__device__ __forceinline__ double batch_sum(double x, double *s_red) {
+    x = bwave_sum(x);
+    if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = x;
+    __syncthreads();
+    double t = 0.0;
+    if (threadIdx.x == 0)
+        for (int w = 0; w < kBatchThreads / 64; ++w) t += s_red[w];
+    __syncthreads();
+    return t;
+}
+
+// The program's arrays are kernel arguments of their own, const and without
+// aliases: the records are then read with scalar loads, as in the gate tile
+// pass.  Read through the argument struct they came by vector loads and a
+// readfirstlane per word.
+#define SV_BATCH_PROGRAM                                                                           \
+    const BatchCircuit *__restrict__ circuits, const BatchPass *__restrict__ passes,               \
+        const TileSweep *__restrict__ sweeps, const char *__restrict__ recs
+
+// LDS-resident circuits: one pass over one tile each.
 template <typename T, int W, bool TWOQ>
-__global__ __launch_bounds__(kBatchThreads) void k_batch(BatchArgs a) {
+__global__ __launch_bounds__(kBatchThreads) void k_batch(BatchArgs a, SV_BATCH_PROGRAM,
+                                                         const int32_t *__restrict__ order) {
     extern __shared__ char lds_raw[];
     cpx<T> *lds = reinterpret_cast<cpx<T> *>(lds_raw);
     __shared__ int s_idx;
@@ -143,57 +150,99 @@ __global__ __launch_bounds__(kBatchThreads) void k_batch(BatchArgs a) {
     for (;;) {
         if (threadIdx.x == 0) s_idx = (int)atomicAdd(a.counter, 1u);
         __syncthreads();
-        const int qi = s_idx;
-        __syncthreads();
-        if (qi >= a.n_circuits) break; // uniform: every wave leaves together
-        const int ci = a.order[qi];
-        const BatchCircuit &c = a.circuits[ci]; // read through memory (uniform)
+        // uniform, and known to be: the record walk stays on the scalar unit
+        const int qi = __builtin_amdgcn_readfirstlane(s_idx);
+        if (qi >= a.n_small) break; // uniform: every wave leaves together
+        const int ci = order[qi];
+        const BatchCircuit &c = circuits[ci];
+        const BatchPass &p = passes[c.pass_off];
         cpx<T> *state = reinterpret_cast<cpx<T> *>(reinterpret_cast<char *>(a.states) + c.state_off);
         double zacc = 0.0;
-        for (int pi = 0; pi < c.n_passes; ++pi) {
-            const BatchPass &p = a.passes[c.pass_off + pi];
-            const int m = p.sp.L + p.sp.K;
-            const uint64_t n_tiles = 1ull << (c.w - m);
-            const bool last = pi == c.n_passes - 1;
-            for (uint64_t tile = 0; tile < n_tiles; ++tile) {
-                uint64_t base = tile << p.sp.L;
-                for (int i = 0; i < p.sp.K; ++i) base = insert_zero(base, p.sp.high[i]);
-                batch_tile<T, W, TWOQ>(state, lds, p.sp, m, base, a.sweeps + p.sweep_off, p.n_sweeps,
-                                       a.recs + p.gate_off, pi == 0, last, !last || c.keep, a.zmask, zacc);
-            }
-            // the next pass reads what this pass wrote: make the stores visible
-            __threadfence();
-            __syncthreads();
-        }
-        zacc = bwave_sum(zacc);
-        if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = zacc;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double t = 0.0;
-            for (int w = 0; w < kBatchThreads / 64; ++w) t += s_red[w];
-            a.out[ci] = t;
-        }
+        batch_tile<T, W, TWOQ>(state, lds, p.sp, c.w, 0, sweeps + p.sweep_off, p.n_sweeps, recs + p.gate_off,
+                               true, true, c.keep, a.zmask, zacc);
+        zacc = batch_sum(zacc, s_red);
+        if (threadIdx.x == 0) a.out[ci] = zacc;
+        // Also keeps this store and the next pop apart: as neighbouring
+        // blocks of thread 0 they were merged into a loop of their own, in
+        // which the other threads went round again before the pop.
         __syncthreads();
     }
 }
 
-__global__ void k_batch_reset(unsigned int *counter) { *counter = 0u; }
-
+// Pass 'level' of every wide circuit that has one.
 template <typename T, int W, bool TWOQ>
-static void launch_batch_t(const BatchArgs &args, int grid, size_t lds, hipStream_t s) {
-    (void)hipFuncSetAttribute((const void *)k_batch<T, W, TWOQ>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)lds);
-    k_batch<T, W, TWOQ><<<grid, kBatchThreads, lds, s>>>(args);
+__global__ __launch_bounds__(kBatchThreads) void k_batch_wide(BatchArgs a, SV_BATCH_PROGRAM,
+                                                              const int32_t *__restrict__ wide,
+                                                              const BatchGroup *__restrict__ all_groups,
+                                                              BatchLevel lv, int level) {
+    extern __shared__ char lds_raw[];
+    cpx<T> *lds = reinterpret_cast<cpx<T> *>(lds_raw);
+    __shared__ double s_red[kBatchThreads / 64];
+    const BatchGroup *groups = all_groups + lv.group_off;
+    for (int64_t item = blockIdx.x; item < lv.items; item += gridDim.x) {
+        int g = 0;
+        while (g + 1 < lv.n_groups && item >= groups[g + 1].first) ++g;
+        const int64_t local = item - groups[g].first;
+        const int tl = groups[g].tiles_log;
+        const int ci = wide[groups[g].list_off + (int)(local >> tl)];
+        const uint64_t tile = (uint64_t)local & ((1ull << tl) - 1ull);
+        const BatchCircuit &c = circuits[ci];
+        const BatchPass &p = passes[c.pass_off + level];
+        cpx<T> *state = reinterpret_cast<cpx<T> *>(reinterpret_cast<char *>(a.states) + c.state_off);
+        uint64_t base = tile << p.sp.L;
+        for (int i = 0; i < p.sp.K; ++i) base = insert_zero(base, p.sp.high[i]);
+        const bool last = level == c.n_passes - 1;
+        double zacc = 0.0;
+        batch_tile<T, W, TWOQ>(state, lds, p.sp, c.w - tl, base, sweeps + p.sweep_off, p.n_sweeps,
+                               recs + p.gate_off, level == 0, last, !last || c.keep, a.zmask, zacc);
+        if (last) {
+            zacc = batch_sum(zacc, s_red);
+            if (threadIdx.x == 0) a.parts[c.part_off + (int64_t)tile] = zacc;
+        }
+    }
 }
 
-hipError_t launch_batch(const BatchArgs &args, int dtype, int sweep_w, int tile_m, int grid, bool two_qubit,
-                        hipStream_t s) {
-    const int m = tile_m;
-    const size_t lds = (size_t)(1u << m) * (dtype == SV_C64 ? 8 : 16);
-    k_batch_reset<<<1, 1, 0, s>>>(args.counter);
+// Expectation of a wide circuit: its tiles' partials, in a fixed order.
+__global__ __launch_bounds__(64) void k_batch_sum(BatchArgs a, int tile_m) {
+    const int ci = a.wide[blockIdx.x];
+    const BatchCircuit &c = a.circuits[ci];
+    const int64_t n = 1ll << (c.w - tile_m);
+    double x = 0.0;
+    for (int64_t i = threadIdx.x; i < n; i += 64) x += a.parts[c.part_off + i];
+    x = bwave_sum(x);
+    if (threadIdx.x == 0) a.out[ci] = x;
+}
+
+__global__ void k_batch_reset(unsigned int *counter) { *counter = 0u; }
+
+// A launch's threads must number fewer than 2^32.
+constexpr int64_t kMaxWideGrid = 1 << 22;
+
+template <typename T, int W, bool TWOQ>
+static void launch_batch_t(const BatchArgs &args, const BatchLevel *levels, int n_levels, int tile_m, int grid,
+                           size_t lds, hipStream_t s) {
+    if (args.n_small) {
+        (void)hipFuncSetAttribute((const void *)k_batch<T, W, TWOQ>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  (int)lds);
+        k_batch_reset<<<1, 1, 0, s>>>(args.counter);
+        k_batch<T, W, TWOQ><<<grid, kBatchThreads, lds, s>>>(args, args.circuits, args.passes, args.sweeps, args.recs,
+                                                            args.order);
+    }
+    if (!args.n_wide) return;
+    (void)hipFuncSetAttribute((const void *)k_batch_wide<T, W, TWOQ>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)lds);
+    for (int l = 0; l < n_levels; ++l)
+        k_batch_wide<T, W, TWOQ><<<(unsigned)std::min(levels[l].items, kMaxWideGrid), kBatchThreads, lds, s>>>(
+            args, args.circuits, args.passes, args.sweeps, args.recs, args.wide, args.groups, levels[l], l);
+    k_batch_sum<<<args.n_wide, 64, 0, s>>>(args, tile_m);
+}
+
+hipError_t launch_batch(const BatchArgs &args, const BatchLevel *levels, int n_levels, int dtype, int sweep_w,
+                        int tile_m, int grid, bool two_qubit, hipStream_t s) {
+    const size_t lds = (size_t)(1u << tile_m) * (dtype == SV_C64 ? 8 : 16);
 #define SV_BATCH_CASE(TT, WW, Q)                                                                   \
     if ((dtype == SV_C64) == std::is_same<TT, float>::value && sweep_w == WW && two_qubit == Q) {  \
-        launch_batch_t<TT, WW, Q>(args, grid, lds, s);                                             \
+        launch_batch_t<TT, WW, Q>(args, levels, n_levels, tile_m, grid, lds, s);                   \
         return hipGetLastError();                                                                  \
     }
     SV_BATCH_CASE(float, 4, false)

@@ -1936,9 +1936,43 @@ struct BatchProgram {
     std::vector<TileSweep> sweeps;
     std::vector<char> recs; // packed records of all passes
     bool two_qubit = false;
-    std::vector<int32_t> order;
-    size_t state_bytes = 0;
+    std::vector<int32_t> order;       // LDS-resident circuits, longest first
+    std::vector<int32_t> wide;        // circuits of every level's groups
+    std::vector<BatchGroup> groups;
+    std::vector<BatchLevel> levels;   // one per pass index of the wide circuits
+    int n_wide = 0;
+    size_t state_bytes = 0, n_parts = 0;
 };
+
+// Work items of the wide circuits' passes: per pass index the circuits that
+// have it, by width, and the groups of equal width.  The first list holds
+// every wide circuit (each has at least one pass).
+static void batch_levels(BatchProgram &bp, int mmax) {
+    std::vector<int32_t> wide;
+    for (size_t i = 0; i < bp.circuits.size(); ++i)
+        if (bp.circuits[i].w > mmax) wide.push_back((int32_t)i);
+    bp.n_wide = (int)wide.size();
+    std::stable_sort(wide.begin(), wide.end(),
+                     [&](int a, int b) { return bp.circuits[a].w > bp.circuits[b].w; });
+    for (int level = 0;; ++level) {
+        BatchLevel lv{};
+        lv.group_off = (int32_t)bp.groups.size();
+        int w = -1;
+        for (int32_t ci : wide) {
+            const BatchCircuit &c = bp.circuits[ci];
+            if (c.n_passes <= level) continue;
+            if (c.w != w) {
+                bp.groups.push_back({lv.items, c.w - mmax, (int32_t)bp.wide.size()});
+                ++lv.n_groups;
+                w = c.w;
+            }
+            bp.wide.push_back(ci);
+            lv.items += 1ll << (c.w - mmax);
+        }
+        if (!lv.items) break;
+        bp.levels.push_back(lv);
+    }
+}
 
 // Fusion width of a batch program: fw = 0 keeps the gates; fw = 1 or 2
 // multiplies, greedily in circuit order, gates into blocks of at most fw
@@ -2026,6 +2060,10 @@ static BatchProgram compile_batch(const std::vector<int> &widths,
             c.state_off = (int64_t)bp.state_bytes;
             bp.state_bytes += align256(((size_t)1 << w) * el);
         }
+        if (w > mmax) {
+            c.part_off = (int64_t)bp.n_parts;
+            bp.n_parts += (size_t)1 << (w - mmax);
+        }
         for (const Pass &p : passes) {
             uint64_t needed = 0;
             std::vector<const Gate *> ptrs;
@@ -2063,8 +2101,9 @@ static BatchProgram compile_batch(const std::vector<int> &widths,
         bp.circuits.push_back(c);
         cost[i] = std::ldexp((double)(circ[i].size() + 1) * (double)passes.size(), w);
     }
-    bp.order.resize(widths.size());
-    for (size_t i = 0; i < widths.size(); ++i) bp.order[i] = (int32_t)i;
+    for (size_t i = 0; i < widths.size(); ++i)
+        if (widths[i] <= mmax) bp.order.push_back((int32_t)i);
+    batch_levels(bp, mmax);
     std::stable_sort(bp.order.begin(), bp.order.end(), [&](int a, int b) { return cost[a] > cost[b]; });
     return bp;
 }
@@ -2128,30 +2167,39 @@ static int batch_prepare(sv_batch *b, int tile_m, int sweep_w, int grid, int fus
     const size_t o_s = align256(o_p + bp.passes.size() * sizeof(BatchPass));
     const size_t o_g = align256(o_s + bp.sweeps.size() * sizeof(TileSweep));
     const size_t o_o = align256(o_g + bp.recs.size());
-    const size_t total = align256(o_o + bp.order.size() * sizeof(int32_t));
+    const size_t o_w = align256(o_o + bp.order.size() * sizeof(int32_t));
+    const size_t o_r = align256(o_w + bp.wide.size() * sizeof(int32_t));
+    const size_t o_e = align256(o_r + bp.groups.size() * sizeof(BatchGroup)); // partials, written on the device
+    const size_t total = align256(o_e + bp.n_parts * sizeof(double));
     size_t free_b = 0, total_b = 0;
     SV_HIP(hipMemGetInfo(&free_b, &total_b));
     if (total + bp.state_bytes + (64u << 20) > free_b)
         return fail(SV_ENOMEM, "batch program and states exceed free device memory");
     SV_HIP(hipMalloc((void **)&b->d_prog, total));
     if (bp.state_bytes) SV_HIP(hipMalloc(&b->d_states, bp.state_bytes));
-    std::vector<char> host(total, 0);
+    std::vector<char> host(o_e, 0);
     std::memcpy(host.data() + o_c, bp.circuits.data(), bp.circuits.size() * sizeof(BatchCircuit));
     std::memcpy(host.data() + o_p, bp.passes.data(), bp.passes.size() * sizeof(BatchPass));
     std::memcpy(host.data() + o_s, bp.sweeps.data(), bp.sweeps.size() * sizeof(TileSweep));
     std::memcpy(host.data() + o_g, bp.recs.data(), bp.recs.size());
     std::memcpy(host.data() + o_o, bp.order.data(), bp.order.size() * sizeof(int32_t));
-    SV_HIP(hipMemcpy(b->d_prog, host.data(), total, hipMemcpyHostToDevice));
+    std::memcpy(host.data() + o_w, bp.wide.data(), bp.wide.size() * sizeof(int32_t));
+    std::memcpy(host.data() + o_r, bp.groups.data(), bp.groups.size() * sizeof(BatchGroup));
+    SV_HIP(hipMemcpy(b->d_prog, host.data(), o_e, hipMemcpyHostToDevice));
     BatchArgs &a = b->args;
     a.circuits = reinterpret_cast<const BatchCircuit *>(b->d_prog + o_c);
     a.passes = reinterpret_cast<const BatchPass *>(b->d_prog + o_p);
     a.sweeps = reinterpret_cast<const TileSweep *>(b->d_prog + o_s);
     a.recs = b->d_prog + o_g;
     a.order = reinterpret_cast<const int32_t *>(b->d_prog + o_o);
+    a.wide = reinterpret_cast<const int32_t *>(b->d_prog + o_w);
+    a.groups = reinterpret_cast<const BatchGroup *>(b->d_prog + o_r);
+    a.parts = reinterpret_cast<double *>(b->d_prog + o_e);
     a.counter = b->d_counter;
     a.states = b->d_states;
     a.out = b->d_out;
-    a.n_circuits = b->n;
+    a.n_small = (int)bp.order.size();
+    a.n_wide = bp.n_wide;
     a.zmask = b->zmask;
     b->state_off.resize(b->n);
     b->n_passes.resize(b->n);
@@ -2165,7 +2213,8 @@ static int batch_prepare(sv_batch *b, int tile_m, int sweep_w, int grid, int fus
     b->fuse_w = fuse_w;
     b->two_qubit = bp.two_qubit;
     // one eager launch (sets kernel attributes, checks the launch), then capture
-    SV_HIP(launch_batch(a, b->dtype, sweep_w, tile_m, grid, b->two_qubit, b->stream));
+    SV_HIP(launch_batch(a, bp.levels.data(), (int)bp.levels.size(), b->dtype, sweep_w, tile_m, grid, b->two_qubit,
+                        b->stream));
     SV_HIP(hipStreamSynchronize(b->stream));
     // capture on a private stream (the caller's may be the null stream, which
     // cannot be captured); the graph is launched on the caller's stream
@@ -2176,7 +2225,8 @@ static int batch_prepare(sv_batch *b, int tile_m, int sweep_w, int grid, int fus
         (void)hipStreamDestroy(cap);
         return hip_fail(e0, "hipStreamBeginCapture");
     }
-    hipError_t e = launch_batch(a, b->dtype, sweep_w, tile_m, grid, b->two_qubit, cap);
+    hipError_t e = launch_batch(a, bp.levels.data(), (int)bp.levels.size(), b->dtype, sweep_w, tile_m, grid,
+                                b->two_qubit, cap);
     hipGraph_t g = nullptr;
     hipError_t e2 = hipStreamEndCapture(cap, &g);
     (void)hipStreamDestroy(cap);

@@ -288,6 +288,7 @@ struct BatchCircuit {
     int32_t pass_off;
     int32_t keep;      // store the final state
     int64_t state_off; // byte offset of the state in the batch's state buffer
+    int64_t part_off;  // wide circuits: first of the tiles' expectation partials
 };
 struct BatchPass {
     TileSpec sp;
@@ -296,20 +297,37 @@ struct BatchPass {
     int32_t gate_off;      // byte offset of the pass's records in the stream
     int32_t pad;
 };
+// Circuits wider than an LDS tile advance together, one launch per pass
+// index: a launch's work items are the tiles of every circuit that has the
+// pass, listed by width (widths of one group have 2^tiles_log tiles each).
+struct BatchGroup {
+    int64_t first;      // first work item of the group
+    int32_t tiles_log;
+    int32_t list_off;   // its first circuit in BatchArgs::wide
+};
 struct BatchArgs {
     const BatchCircuit *circuits;
     const BatchPass *passes;
     const TileSweep *sweeps;
     const char *recs;
-    const int32_t *order;
+    const int32_t *order;  // LDS-resident circuits, longest first
+    const int32_t *wide;   // circuits of every group of every level
+    const BatchGroup *groups;
     unsigned int *counter;
     void *states;
+    double *parts;         // expectation partials of the wide circuits' tiles
     double *out;
-    int n_circuits;
+    int n_small;           // circuits in order
+    int n_wide;            // circuits wider than a tile (the first ones of 'wide')
     uint64_t zmask;
 };
-hipError_t launch_batch(const BatchArgs &args, int dtype, int sweep_w, int tile_m, int grid, bool two_qubit,
-                        hipStream_t s);
+// One pass index of the wide circuits.
+struct BatchLevel {
+    int32_t n_groups, group_off;
+    int64_t items;
+};
+hipError_t launch_batch(const BatchArgs &args, const BatchLevel *levels, int n_levels, int dtype, int sweep_w,
+                        int tile_m, int grid, bool two_qubit, hipStream_t s);
 
 // ----------------------------------------------------------- measurement
 constexpr int kMaxMeasureQubits = 6;
