@@ -16,6 +16,16 @@
 // of 10 to 18 qubits took 11.9 ms on the device, with one launch per pass
 // 5.4 ms; 4096 circuits of 10 to 20 qubits 106 and 85 ms; one 20-qubit
 // circuit alone 43 and 0.32 ms.
+//
+// A wide circuit starts on one amplitude and each pass spreads it over the
+// qubits of its tiles.  The host knows from the gates which qubits the
+// passes before this one have moved (BatchPass::live), so tiles that still
+// hold only zeros are not listed: the first pass, which holds most of a
+// ladder's gates, runs one tile of each circuit instead of 2 to 32 (0.36
+// instead of 2.47 ms on the 1024 circuits, whose run takes 3.6 ms).  Listed and left at once by
+// their workgroups they saved nothing: the tiles that remained were every
+// 2nd to 32nd workgroup, which the dispatcher had dealt to the same XCD and
+// compute units.
 #include "sv_internal.hpp"
 #include "tile_sweep.hpp"
 
@@ -45,11 +55,13 @@ __device__ __forceinline__ double zterm(cpx<T> a, uint64_t x, uint64_t zmask) {
 // first pass, else the state; the sink accumulates the Z-string terms on
 // the last pass and stores the state unless that pass is the last and the
 // states are not kept.  A thread owns at most one group per sweep
-// (2^(m-W) <= kBatchThreads).
+// (2^(m-W) <= kBatchThreads).  'dead' holds the qubits no earlier pass has
+// moved: amplitudes with such a bit set are zero and are not read.
 template <typename T, int W, bool TWOQ>
 __device__ void batch_tile(cpx<T> *state, cpx<T> *lds, const TileSpec &sp, int m, uint64_t base,
                            const TileSweep *__restrict__ sweeps, int n_sweeps, const char *__restrict__ recs,
-                           bool synth, bool last_pass, bool store, uint64_t zmask, double &zacc) {
+                           bool synth, bool last_pass, bool store, uint64_t dead, uint64_t zmask,
+                           double &zacc) {
     constexpr int D = 1 << W;
     const uint32_t n_groups = (1u << m) >> W;
     for (int si = 0; si < n_sweeps; ++si) {
@@ -86,7 +98,10 @@ __device__ void batch_tile(cpx<T> *state, cpx<T> *lds, const TileSpec &sp, int m
                 for (int j = 0; j < D; ++j) v[j] = cpx<T>{(row | goff_of(j)) == 0 ? T(1) : T(0), T(0)};
             } else if (first) {
 #pragma unroll
-                for (int j = 0; j < D; ++j) v[j] = state[row | goff_of(j)];
+                for (int j = 0; j < D; ++j) {
+                    const uint64_t x = row | goff_of(j);
+                    v[j] = x & dead ? cpx<T>{T(0), T(0)} : state[x];
+                }
             } else {
 #pragma unroll
                 for (int j = 0; j < D; ++j) v[j] = lds[pg ^ poff_of(j)];
@@ -159,7 +174,7 @@ __global__ __launch_bounds__(kBatchThreads) void k_batch(BatchArgs a, SV_BATCH_P
         cpx<T> *state = reinterpret_cast<cpx<T> *>(reinterpret_cast<char *>(a.states) + c.state_off);
         double zacc = 0.0;
         batch_tile<T, W, TWOQ>(state, lds, p.sp, c.w, 0, sweeps + p.sweep_off, p.n_sweeps, recs + p.gate_off,
-                               true, true, c.keep, a.zmask, zacc);
+                               true, true, c.keep, 0, a.zmask, zacc);
         zacc = batch_sum(zacc, s_red);
         if (threadIdx.x == 0) a.out[ci] = zacc;
         // Also keeps this store and the next pop apart: as neighbouring
@@ -185,16 +200,28 @@ __global__ __launch_bounds__(kBatchThreads) void k_batch_wide(BatchArgs a, SV_BA
         const int64_t local = item - groups[g].first;
         const int tl = groups[g].tiles_log;
         const int ci = wide[groups[g].list_off + (int)(local >> tl)];
-        const uint64_t tile = (uint64_t)local & ((1ull << tl) - 1ull);
         const BatchCircuit &c = circuits[ci];
         const BatchPass &p = passes[c.pass_off + level];
+        // bit i of the tile's number in the list is the i-th bit of p.tiles
+        uint32_t tile = 0, rest = (uint32_t)local & ((1u << tl) - 1u);
+        for (uint32_t b = p.tiles; b; b &= b - 1u, rest >>= 1)
+            if (rest & 1u) tile |= b & (0u - b);
         cpx<T> *state = reinterpret_cast<cpx<T> *>(reinterpret_cast<char *>(a.states) + c.state_off);
-        uint64_t base = tile << p.sp.L;
+        uint64_t base = (uint64_t)tile << p.sp.L;
         for (int i = 0; i < p.sp.K; ++i) base = insert_zero(base, p.sp.high[i]);
         const bool last = level == c.n_passes - 1;
+        const int m = p.sp.L + p.sp.K;
+        const uint64_t dead = ~p.live;
+        if (base & dead) { // a tile of zeros: no pass reads it before one has written it
+            if (last && c.keep)
+                for (uint32_t l = threadIdx.x; l < (1u << m); l += kBatchThreads)
+                    state[base | tile_offset(p.sp, l)] = cpx<T>{T(0), T(0)};
+            if (last && threadIdx.x == 0) a.parts[c.part_off + (int64_t)tile] = 0.0;
+            continue;
+        }
         double zacc = 0.0;
-        batch_tile<T, W, TWOQ>(state, lds, p.sp, c.w - tl, base, sweeps + p.sweep_off, p.n_sweeps,
-                               recs + p.gate_off, level == 0, last, !last || c.keep, a.zmask, zacc);
+        batch_tile<T, W, TWOQ>(state, lds, p.sp, m, base, sweeps + p.sweep_off, p.n_sweeps,
+                               recs + p.gate_off, level == 0, last, !last || c.keep, dead, a.zmask, zacc);
         if (last) {
             zacc = batch_sum(zacc, s_red);
             if (threadIdx.x == 0) a.parts[c.part_off + (int64_t)tile] = zacc;

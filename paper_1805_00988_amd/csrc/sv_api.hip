@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <array>
+#include <cfloat>
 #include <cmath>
 #include <cstdio>
 #include <complex>
@@ -29,6 +30,11 @@ struct sv_state {
     size_t arena_cap = 0;
     hipEvent_t stage_done = nullptr;  // last copy out of h_arena
     bool stage_pending = false;
+    // qubits that a gate other than a diagonal one has acted on since the
+    // register was last set to a basis state.  It only picks the tile pass
+    // that tests its tiles for zeros: the buffer is the caller's to write,
+    // so what a tile holds is always read from it.
+    uint64_t moved = 0;
     // per-launch timing (sv_timing): event pairs around each kernel launch
     struct Rec {
         int kid;
@@ -223,6 +229,8 @@ static int stage_wait(sv_state *h) {
 static bool is_one(const double *z) { return z[0] == 1.0 && z[1] == 0.0; }
 static bool is_zero(const double *z) { return z[0] == 0.0 && z[1] == 0.0; }
 
+static bool is_diag1(const Gate &g) { return g.k == 1 && is_zero(g.U + 2) && is_zero(g.U + 4); }
+
 static int vbits_of(int dtype) { return dtype == SV_C64 ? 1 : 0; }
 
 // Tile pass holding one gate (used for two-qubit gates on qubit 0 of a
@@ -232,6 +240,7 @@ static int tile_single(sv_state *h, const Gate &g);
 static double gate_flops_per_amp(const Gate &g);
 
 static int apply_one(sv_state *h, const Gate &g) {
+    if (!is_diag1(g)) h->moved |= g.tmask();
     if (g.k == 1) {
         const double *U = g.U;
         if (is_zero(U + 2) && is_zero(U + 4)) {
@@ -308,6 +317,8 @@ struct PassCode {
     bool two_qubit = false;     // holds SK_2Q records
     bool lane_phases = false;   // holds SK_LPH records
     uint32_t direct = 0;        // kDirectFirst / kDirectLast (launch_tile)
+    uint64_t moves = 0;         // targets of its gates that are not diagonal
+    bool finite = true;         // every matrix entry is, in the state's precision
     std::vector<TileSweep> sweeps;
     std::vector<TileGate> gates; // records in sweep order (host form)
     std::vector<std::vector<char>> tables; // SK_PTAB payloads (descriptors and tables)
@@ -354,8 +365,6 @@ static void pack_records(PassCode &pc, bool f32) {
     }
     pc.recs.resize(pc.recs.size() + kRecordTail, 0);
 }
-
-static bool is_diag1(const Gate &g) { return g.k == 1 && is_zero(g.U + 2) && is_zero(g.U + 4); }
 
 static bool is_x(const Gate &g) {
     const double x[8] = {0, 0, 1, 0, 1, 0, 0, 0};
@@ -885,6 +894,10 @@ static PassCode compile_pass(const TileSpec &sp, const std::vector<const Gate *>
         close();
         while (first < gs.size() && done[first]) ++first;
     }
+    for (const Gate *g : gs) {
+        if (!is_diag1(*g)) pc.moves |= g->tmask();
+        for (int i = 0; i < 2 << (2 * g->k); ++i) pc.finite = pc.finite && std::fabs(g->U[i]) <= (f32 ? FLT_MAX : DBL_MAX);
+    }
     pack_records(pc, f32);
     // the first and last sweeps read / write the state directly (measured
     // faster than staging the tile through LDS for every register layout,
@@ -904,8 +917,11 @@ static int launch_pass(sv_state *h, const PassCode &pc, size_t off) {
     const TileSweep *sw = reinterpret_cast<const TileSweep *>(h->d_arena + off);
     const char *gt = h->d_arena + off + align256(pc.sweeps.size() * sizeof(TileSweep));
     Timed tm(h, K_TILE, 2.0 * state_bytes(h), pc.flops_per_amp * (double)(1ull << h->n));
+    const uint64_t all = h->n < 64 ? (1ull << h->n) - 1ull : ~0ull;
+    const bool zeros = pc.finite && (all & ~tile_qubits(pc.sp) & ~h->moved) != 0;
     SV_HIP(launch_tile(h->amps, h->n, h->dtype, pc.sp, sw, (int)pc.sweeps.size(), gt, pc.two_qubit, pc.lane_phases,
-                       pc.direct, h->stream));
+                       pc.direct | (zeros ? kSkipZero : 0u), h->stream));
+    h->moved |= pc.moves;
     return SV_OK;
 }
 
@@ -1851,6 +1867,7 @@ static void stage_fused(sv_state *h, FusedPass &fp, size_t off) {
 static int launch_fused(sv_state *h, const FusedPass &fp, size_t off) {
     if (fp.plain) return launch_pass(h, fp.code, off);
     Timed tm(h, K_FUSED, 2.0 * state_bytes(h), fp.flops_per_amp * (double)(1ull << h->n));
+    h->moved |= tile_qubits(fp.sp);
     SV_HIP(launch_dense_pass(h->amps, h->n, h->dtype, fp.sp, fp.k,
                              reinterpret_cast<const DenseBlock *>(h->d_arena + off), (int)fp.blocks.size(),
                              h->d_arena, fp.engine, fp.direct, h->stream));
@@ -1945,29 +1962,43 @@ struct BatchProgram {
 };
 
 // Work items of the wide circuits' passes: per pass index the circuits that
-// have it, by width, and the groups of equal width.  The first list holds
-// every wide circuit (each has at least one pass).
+// have it, by the number of tiles to run, and the groups of equal number.
+// The first list holds every wide circuit (each has at least one pass).
 static void batch_levels(BatchProgram &bp, int mmax) {
     std::vector<int32_t> wide;
     for (size_t i = 0; i < bp.circuits.size(); ++i)
         if (bp.circuits[i].w > mmax) wide.push_back((int32_t)i);
     bp.n_wide = (int)wide.size();
-    std::stable_sort(wide.begin(), wide.end(),
-                     [&](int a, int b) { return bp.circuits[a].w > bp.circuits[b].w; });
     for (int level = 0;; ++level) {
-        BatchLevel lv{};
-        lv.group_off = (int32_t)bp.groups.size();
-        int w = -1;
+        // the tiles to run: those on qubits an earlier pass has moved, and on
+        // the last pass all (their partials, and states that are kept)
+        std::vector<std::pair<int, int32_t>> by_tiles;
         for (int32_t ci : wide) {
             const BatchCircuit &c = bp.circuits[ci];
             if (c.n_passes <= level) continue;
-            if (c.w != w) {
-                bp.groups.push_back({lv.items, c.w - mmax, (int32_t)bp.wide.size()});
-                ++lv.n_groups;
-                w = c.w;
+            BatchPass &p = bp.passes[(size_t)c.pass_off + level];
+            const uint64_t S = tile_qubits(p.sp);
+            p.tiles = 0;
+            for (int q = 0, bit = 0; q < c.w; ++q) {
+                if ((S >> q) & 1ull) continue;
+                if (level == c.n_passes - 1 || ((p.live >> q) & 1ull)) p.tiles |= 1u << bit;
+                ++bit;
             }
-            bp.wide.push_back(ci);
-            lv.items += 1ll << (c.w - mmax);
+            by_tiles.push_back({__builtin_popcount(p.tiles), ci});
+        }
+        std::stable_sort(by_tiles.begin(), by_tiles.end(),
+                         [](const auto &a, const auto &b) { return a.first > b.first; });
+        BatchLevel lv{};
+        lv.group_off = (int32_t)bp.groups.size();
+        int tl = -1;
+        for (const auto &e : by_tiles) {
+            if (e.first != tl) {
+                tl = e.first;
+                bp.groups.push_back({lv.items, tl, (int32_t)bp.wide.size()});
+                ++lv.n_groups;
+            }
+            bp.wide.push_back(e.second);
+            lv.items += 1ll << tl;
         }
         if (!lv.items) break;
         bp.levels.push_back(lv);
@@ -2064,6 +2095,8 @@ static BatchProgram compile_batch(const std::vector<int> &widths,
             c.part_off = (int64_t)bp.n_parts;
             bp.n_parts += (size_t)1 << (w - mmax);
         }
+        uint64_t live = 0;
+        bool finite = true;
         for (const Pass &p : passes) {
             uint64_t needed = 0;
             std::vector<const Gate *> ptrs;
@@ -2093,11 +2126,17 @@ static BatchProgram compile_batch(const std::vector<int> &widths,
             q.n_sweeps = (int)pc.sweeps.size();
             q.sweep_off = (int)bp.sweeps.size();
             q.gate_off = (int)bp.recs.size();
+            q.live = live;
+            live |= pc.moves;
+            finite = finite && pc.finite;
             bp.passes.push_back(q);
             bp.sweeps.insert(bp.sweeps.end(), pc.sweeps.begin(), pc.sweeps.end());
             bp.recs.insert(bp.recs.end(), pc.recs.begin(), pc.recs.end());
             bp.two_qubit = bp.two_qubit || pc.two_qubit;
         }
+        // a matrix entry beyond the precision's range makes zeros NaN: then
+        // every tile runs
+        for (size_t k = 0; k < passes.size() && !finite; ++k) bp.passes[(size_t)c.pass_off + k].live = ~0ull;
         bp.circuits.push_back(c);
         cost[i] = std::ldexp((double)(circ[i].size() + 1) * (double)passes.size(), w);
     }
@@ -2332,6 +2371,7 @@ int sv_set_basis(sv_handle h, uint64_t x) {
     if (h->n < 64 && (x >> h->n) != 0) return fail(SV_EINVAL, "basis index >= 2^n");
     Timed tm(h, K_INIT, state_bytes(h));
     SV_HIP(launch_init_basis(h->amps, h->n, h->dtype, x, h->stream));
+    h->moved = 0;
     return SV_OK;
 }
 
@@ -2746,6 +2786,7 @@ int sv_fused_tune(sv_handle h, const sv_op *ops, int n_ops, const double *params
     size_t free_b = 0, total_b = 0;
     SV_HIP(hipMemGetInfo(&free_b, &total_b));
     if (bytes + (64u << 20) > free_b) return fail(SV_ENOMEM, "no room for a copy of the state");
+    const uint64_t moved = h->moved;
     void *saved = nullptr;
     SV_HIP(hipMalloc(&saved, bytes));
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -2768,6 +2809,7 @@ int sv_fused_tune(sv_handle h, const sv_op *ops, int n_ops, const double *params
             e = hipMemcpyAsync(h->amps, saved, bytes, hipMemcpyDeviceToDevice, h->stream);
             if (e == hipSuccess) e = hipEventRecord(e0, h->stream);
             if (e != hipSuccess) { rc = hip_fail(e, "sv_fused_tune"); break; }
+            h->moved = moved;
             if ((rc = run_one(cand[c].first, cand[c].second))) break;
             float ms = 0.0f;
             e = hipEventRecord(e1, h->stream);
@@ -2782,6 +2824,7 @@ int sv_fused_tune(sv_handle h, const sv_op *ops, int n_ops, const double *params
             bp = cand[c].second;
         }
     }
+    h->moved = moved;
     if (!rc) {
         e = hipMemcpyAsync(h->amps, saved, bytes, hipMemcpyDeviceToDevice, h->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(h->stream);

@@ -216,7 +216,8 @@ hipError_t launch_scale(void *amps, int n, int dtype, uint64_t set_mask, const d
 // back instead of staging the tile through LDS (worth it when the sweep's
 // register positions leave the lowest tile bits to the lanes, so that a
 // wave's accesses stay contiguous).
-constexpr uint32_t kDirectFirst = 1, kDirectLast = 2;
+// kSkipZero: test the tile for zeros after the first sweep's loads.
+constexpr uint32_t kDirectFirst = 1, kDirectLast = 2, kSkipZero = 4;
 hipError_t launch_tile(void *amps, int n, int dtype, const TileSpec &spec, const TileSweep *dev_sweeps,
                        int n_sweeps, const char *dev_recs, bool two_qubit, bool lane_phases, uint32_t direct,
                        hipStream_t s);
@@ -295,11 +296,15 @@ struct BatchPass {
     int32_t n_sweeps;
     int32_t sweep_off;
     int32_t gate_off;      // byte offset of the pass's records in the stream
-    int32_t pad;
+    uint32_t tiles;        // bits of the tile index that the listed tiles take
+    // qubits that gates of earlier passes have moved off |0>; an amplitude
+    // with any other bit set is zero, whatever the state buffer holds there
+    uint64_t live;
 };
 // Circuits wider than an LDS tile advance together, one launch per pass
 // index: a launch's work items are the tiles of every circuit that has the
-// pass, listed by width (widths of one group have 2^tiles_log tiles each).
+// pass, listed by the number of tiles: those of one group list 2^tiles_log
+// tiles each (the tiles that are not all zero; on its last pass all).
 struct BatchGroup {
     int64_t first;      // first work item of the group
     int32_t tiles_log;
