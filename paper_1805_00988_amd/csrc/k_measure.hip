@@ -41,20 +41,38 @@ __device__ __forceinline__ uint32_t outcome_bits(uint64_t x, const MeasurePos &m
 // ------------------------------------------------------------- marginals
 // Every thread keeps its own 2^k FP64 bins in LDS (bin b of thread t at
 // b * kMeasThreads + t: consecutive lanes, consecutive banks), the
-// workgroup then sums each bin over its threads in order.
+// workgroup then sums each bin over its threads in order.  Bound by the read
+// of the state: kMeasUnroll nontemporal loads in flight per thread, and the
+// outcome of a vector is a part of the thread's own bits, set once, and a
+// part that the workgroup shares, on the scalar unit.  27 qubits complex128,
+// 4 qubits measured: 354 us, 400 with one load per round.
+constexpr int kMeasUnroll = 8;
+constexpr int kMeasThreadBits = 8;
+static_assert(kMeasThreads == 1 << kMeasThreadBits, "index bits");
 template <typename T>
 __global__ __launch_bounds__(kMeasThreads) void k_marginals(const typename Amp16<T>::type *__restrict__ v,
                                                             uint64_t n_vec, MeasurePos mp, double *partials) {
     extern __shared__ double bins[];
+    constexpr int vb = Amp16<T>::bits;
     const int nb = 1 << mp.k;
     for (int b = 0; b < nb; ++b) bins[b * kMeasThreads + threadIdx.x] = 0.0;
-    const uint64_t stride = (uint64_t)gridDim.x * kMeasThreads;
-    for (uint64_t e = (uint64_t)blockIdx.x * kMeasThreads + threadIdx.x; e < n_vec; e += stride) {
-        const typename Amp16<T>::type w = v[e];
+    uint32_t own[1 << vb];
 #pragma unroll
-        for (int i = 0; i < (sizeof(T) == 4 ? 2 : 1); ++i) {
-            const uint64_t x = (e << Amp16<T>::bits) + i;
-            bins[outcome_bits(x, mp) * kMeasThreads + threadIdx.x] += pr(amp_of<T>(w, i));
+    for (int i = 0; i < (1 << vb); ++i) own[i] = outcome_bits(((uint64_t)threadIdx.x << vb) + i, mp);
+    constexpr uint64_t per = (uint64_t)kMeasUnroll * kMeasThreads;
+    for (uint64_t base = (uint64_t)blockIdx.x * per; base < n_vec; base += (uint64_t)gridDim.x * per) {
+        typename Amp16<T>::type w[kMeasUnroll];
+#pragma unroll
+        for (int u = 0; u < kMeasUnroll; ++u) {
+            const uint64_t e = base + (uint64_t)u * kMeasThreads + threadIdx.x;
+            w[u] = e < n_vec ? ld_nt(&v[e]) : typename Amp16<T>::type{};
+        }
+#pragma unroll
+        for (int u = 0; u < kMeasUnroll; ++u) {
+            const uint32_t shared = outcome_bits((base + (uint64_t)u * kMeasThreads) << vb, mp);
+#pragma unroll
+            for (int i = 0; i < (1 << vb); ++i)
+                bins[(shared | own[i]) * kMeasThreads + threadIdx.x] += pr(amp_of<T>(w[u], i));
         }
     }
     __syncthreads();
@@ -92,36 +110,67 @@ __global__ __launch_bounds__(kMeasThreads) void k_masked_prob(const typename Amp
 }
 
 // --------------------------------------------------------------- collapse
+// psi_x * scale on the outcome, zero elsewhere.  Only vectors that hold an
+// amplitude of the outcome are read: the write of the state bounds this (4
+// of 27 qubits complex128: 400 us, 778 reading all of it).
+constexpr int kCollapseUnroll = 4;
 template <typename T>
 __global__ __launch_bounds__(kMeasThreads) void k_collapse(typename Amp16<T>::type *__restrict__ v, uint64_t n_vec,
                                                            uint64_t mask, uint64_t want, T scale) {
-    const uint64_t stride = (uint64_t)gridDim.x * kMeasThreads;
-    for (uint64_t e = (uint64_t)blockIdx.x * kMeasThreads + threadIdx.x; e < n_vec; e += stride) {
-        typename Amp16<T>::type w = v[e];
-        const uint64_t x = e << Amp16<T>::bits;
-        const T s0 = ((x & mask) == want) ? scale : T(0);
-        if constexpr (sizeof(T) == 4) {
-            const T s1 = (((x + 1) & mask) == want) ? scale : T(0);
-            w = float4{w.x * s0, w.y * s0, w.z * s1, w.w * s1};
-        } else {
-            w = double2{w.x * s0, w.y * s0};
+    constexpr int vb = Amp16<T>::bits;
+    constexpr uint64_t vmask = (1ull << vb) - 1ull; // index bits within a vector
+    constexpr uint64_t per = (uint64_t)kCollapseUnroll * kMeasThreads;
+    for (uint64_t base = (uint64_t)blockIdx.x * per; base < n_vec; base += (uint64_t)gridDim.x * per) {
+        typename Amp16<T>::type w[kCollapseUnroll];
+#pragma unroll
+        for (int u = 0; u < kCollapseUnroll; ++u) {
+            const uint64_t e = base + (uint64_t)u * kMeasThreads + threadIdx.x;
+            const bool some = e < n_vec && (((e << vb) ^ want) & mask & ~vmask) == 0;
+            w[u] = some ? ld_nt(&v[e]) : typename Amp16<T>::type{};
         }
-        v[e] = w;
+#pragma unroll
+        for (int u = 0; u < kCollapseUnroll; ++u) {
+            const uint64_t e = base + (uint64_t)u * kMeasThreads + threadIdx.x;
+            if (e >= n_vec) continue;
+            const uint64_t x = e << vb;
+            const bool in0 = (x & mask) == want;
+            if constexpr (vb == 1) {
+                const bool in1 = ((x + 1) & mask) == want;
+                w[u] = float4{in0 ? w[u].x * scale : 0.f, in0 ? w[u].y * scale : 0.f, in1 ? w[u].z * scale : 0.f,
+                              in1 ? w[u].w * scale : 0.f};
+            } else {
+                w[u] = double2{in0 ? w[u].x * scale : 0.0, in0 ? w[u].y * scale : 0.0};
+            }
+            v[e] = w[u];
+        }
     }
 }
 
 // --------------------------------------------------------------- sampling
 // Sum of each contiguous block of 2^block_log amplitudes (one workgroup per
-// block, grid-stride over blocks).
+// block).  27 qubits complex128: 310 us, 405 with one load in flight per
+// thread.
 template <typename T>
-__global__ __launch_bounds__(kMeasThreads) void k_block_sums(const cpx<T> *__restrict__ v, int block_log,
-                                                             uint64_t n_blocks, double *sums) {
+__global__ __launch_bounds__(kMeasThreads) void k_block_sums(const typename Amp16<T>::type *__restrict__ v,
+                                                             int block_log, uint64_t n_blocks, double *sums) {
     __shared__ double sh[kMeasThreads / 64];
-    const uint64_t bsize = 1ull << block_log;
+    constexpr int vb = Amp16<T>::bits;
+    const uint64_t n_vec = (1ull << block_log) >> vb;
     for (uint64_t b = blockIdx.x; b < n_blocks; b += gridDim.x) {
-        const cpx<T> *p = v + b * bsize;
+        const typename Amp16<T>::type *p = v + b * n_vec;
         double acc = 0.0;
-        for (uint64_t i = threadIdx.x; i < bsize; i += kMeasThreads) acc += pr(p[i]);
+        for (uint64_t i0 = 0; i0 < n_vec; i0 += (uint64_t)kMeasUnroll * kMeasThreads) {
+            typename Amp16<T>::type w[kMeasUnroll];
+#pragma unroll
+            for (int u = 0; u < kMeasUnroll; ++u) {
+                const uint64_t i = i0 + (uint64_t)u * kMeasThreads + threadIdx.x;
+                w[u] = i < n_vec ? ld_nt(&p[i]) : typename Amp16<T>::type{};
+            }
+#pragma unroll
+            for (int u = 0; u < kMeasUnroll; ++u)
+#pragma unroll
+                for (int k = 0; k < (1 << vb); ++k) acc += pr(amp_of<T>(w[u], k));
+        }
         acc = meas_wave_sum(acc);
         if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
         __syncthreads();
@@ -134,21 +183,107 @@ __global__ __launch_bounds__(kMeasThreads) void k_block_sums(const cpx<T> *__res
     }
 }
 
-// One wave per sample: scan the sample's block 64 amplitudes at a time
+// Cumulative sums of the blocks in two steps: a thread adds one run of
+// kRunBlocks blocks (a line of sums), then one workgroup forms pre[r], the
+// mass before run r, and pre[n_runs], the total.  There a thread adds its
+// runs in order, one thread the threads' sums in order, and each thread
+// writes its prefixes from the same operands, so that they never decrease
+// and a run without mass has pre[r] == pre[r + 1]: no target falls into it.
+// On the host, with the copy of 2^16 sums and a second round trip for the
+// targets, this took 420 us; in one workgroup, whose threads read a run of 64
+// sums each, 111; here 25.
+constexpr int kRunBlocks = 16, kPrefixThreads = 1024, kPrefixRuns = 4;
+__global__ __launch_bounds__(64) void k_run_sums(const double *__restrict__ sums, int per, int n_runs,
+                                                 double *__restrict__ runs) {
+    const int r = blockIdx.x * 64 + threadIdx.x;
+    if (r >= n_runs) return;
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < kRunBlocks; ++k)
+        if (k < per) s += sums[r * per + k];
+    runs[r] = s;
+}
+
+__global__ __launch_bounds__(kPrefixThreads) void k_run_prefix(const double *__restrict__ runs, int n_runs,
+                                                               double *__restrict__ pre) {
+    __shared__ double run[kPrefixThreads + 1];
+    const int t = threadIdx.x;
+    double x[kPrefixRuns], s = 0.0;
+#pragma unroll
+    for (int k = 0; k < kPrefixRuns; ++k) {
+        x[k] = t * kPrefixRuns + k < n_runs ? runs[t * kPrefixRuns + k] : 0.0;
+        s += x[k];
+    }
+    run[t + 1] = s;
+    __syncthreads();
+    if (t == 0) {
+        double c = 0.0;
+        run[0] = 0.0;
+#pragma unroll 32
+        for (int i = 1; i <= kPrefixThreads; ++i) {
+            c += run[i];
+            run[i] = c;
+        }
+        pre[n_runs] = c;
+    }
+    __syncthreads();
+    const double from = run[t];
+    double part = 0.0;
+#pragma unroll
+    for (int k = 0; k < kPrefixRuns; ++k) {
+        if (t * kPrefixRuns + k < n_runs) pre[t * kPrefixRuns + k] = from + part;
+        part += x[k];
+    }
+}
+
+// One wave per sample.  Its target is u times the total; its run of blocks
+// is the first whose cumulative end exceeds the target (64 ends per step of
+// the search), or the last one with mass if rounding leaves none, its block
+// is found in the run likewise, and it then scans the block 64 amplitudes at
+// a time
 // (FP64 inclusive prefix across the wave plus the running sum) and take the
 // first amplitude whose cumulative sum exceeds the sample's target; if
 // rounding leaves none, the block's last amplitude with p > 0.
 template <typename T>
 __global__ __launch_bounds__(kMeasThreads) void k_sample_scan(const cpx<T> *__restrict__ v, int block_log,
-                                                              int n_samples, const int64_t *__restrict__ blk,
-                                                              const double *__restrict__ target,
+                                                              int n_samples, int per, int n_runs,
+                                                              const double *__restrict__ sums,
+                                                              const double *__restrict__ pre,
+                                                              const double *__restrict__ uniforms,
                                                               uint64_t *__restrict__ out) {
     const int lane = threadIdx.x & 63;
     const int s = (int)((blockIdx.x * kMeasThreads + threadIdx.x) >> 6);
     if (s >= n_samples) return; // whole waves leave together
     const uint64_t bsize = 1ull << block_log;
-    const uint64_t base = (uint64_t)blk[s] << block_log;
-    const double t = target[s];
+    const double total = pre[n_runs];
+    if (!(total > 0.0)) return; // reported by the host
+    const double goal = uniforms[s] * total;
+    const bool beyond = !(total > goal);
+    int r = 0;
+    for (int len = n_runs; len > 1;) {
+        const int step = len > 64 ? len >> 6 : 1;
+        const bool in = (lane + 1) * step <= len;
+        const double end = in ? pre[r + (lane + 1) * step] : 0.0;
+        const uint64_t hit = __ballot(in && (beyond ? end >= total : end > goal));
+        r += (hit ? __builtin_ctzll(hit) : 0) * step;
+        len = step;
+    }
+    const double mass = lane < per ? sums[r * per + lane] : 0.0;
+    const double from = pre[r];
+    double part = 0.0, before = 0.0;
+    int blk = -1, last_mass = 0;
+    for (int k = 0; k < per && blk < 0; ++k) {
+        const double x = __shfl(mass, k, 64);
+        if (x > 0.0) {
+            last_mass = k;
+            before = part;
+        }
+        part += x;
+        if (from + part > goal) blk = k;
+    }
+    if (blk < 0) blk = last_mass;
+    const uint64_t base = (uint64_t)(r * per + blk) << block_log;
+    const double t = goal - (from + before);
     double run = 0.0;
     int64_t last = -1;
     int64_t found = -1;
@@ -219,7 +354,8 @@ hipError_t launch_collapse(void *amps, int n, int dtype, uint64_t mask, uint64_t
     const int vb = dtype == SV_C64 ? 1 : 0;
     if (n < vb) return hipErrorInvalidValue;
     const uint64_t n_vec = (1ull << n) >> vb;
-    const unsigned grid = stream_grid(n_vec);
+    const uint64_t per = (uint64_t)kCollapseUnroll * kMeasThreads;
+    const unsigned grid = (unsigned)std::min<uint64_t>((n_vec + per - 1) / per, 1u << 20);
     if (dtype == SV_C64)
         k_collapse<float><<<grid, kMeasThreads, 0, s>>>((float4 *)amps, n_vec, mask, want, (float)scale);
     else
@@ -230,26 +366,40 @@ hipError_t launch_collapse(void *amps, int n, int dtype, uint64_t mask, uint64_t
 int sample_block_log(int n) { return std::max(std::min(n, 8), n - 16); }
 
 hipError_t launch_block_sums(const void *amps, int n, int dtype, int block_log, double *sums, hipStream_t s) {
-    if (block_log > n) return hipErrorInvalidValue;
+    if (block_log > n || block_log < (dtype == SV_C64 ? 1 : 0)) return hipErrorInvalidValue;
     const uint64_t nbk = 1ull << (n - block_log);
-    const unsigned grid = (unsigned)std::min<uint64_t>(nbk, 4096);
+    const unsigned grid = (unsigned)std::min<uint64_t>(nbk, 1u << 16);
     if (dtype == SV_C64)
-        k_block_sums<float><<<grid, kMeasThreads, 0, s>>>((const cpx<float> *)amps, block_log, nbk, sums);
+        k_block_sums<float><<<grid, kMeasThreads, 0, s>>>((const float4 *)amps, block_log, nbk, sums);
     else
-        k_block_sums<double><<<grid, kMeasThreads, 0, s>>>((const cpx<double> *)amps, block_log, nbk, sums);
+        k_block_sums<double><<<grid, kMeasThreads, 0, s>>>((const double2 *)amps, block_log, nbk, sums);
     return hipGetLastError();
 }
 
-hipError_t launch_sample_scan(const void *amps, int dtype, int block_log, int n_samples, const int64_t *blk,
-                              const double *target, uint64_t *out, hipStream_t s) {
+static int sample_per(int n_blocks) { return std::min(n_blocks, kRunBlocks); }
+int sample_runs(int n_blocks) { return n_blocks / sample_per(n_blocks); }
+
+hipError_t launch_run_prefix(const double *sums, int n_blocks, double *runs, double *pre, hipStream_t s) {
+    if (n_blocks < 1 || (n_blocks & (n_blocks - 1))) return hipErrorInvalidValue;
+    const int n_runs = sample_runs(n_blocks);
+    if (n_runs > kPrefixThreads * kPrefixRuns) return hipErrorInvalidValue;
+    k_run_sums<<<(n_runs + 63) / 64, 64, 0, s>>>(sums, sample_per(n_blocks), n_runs, runs);
+    k_run_prefix<<<1, kPrefixThreads, 0, s>>>(runs, n_runs, pre);
+    return hipGetLastError();
+}
+
+hipError_t launch_sample_scan(const void *amps, int dtype, int block_log, int n_samples, int n_blocks,
+                              const double *sums, const double *pre, const double *uniforms, uint64_t *out,
+                              hipStream_t s) {
     if (n_samples <= 0) return hipSuccess;
     const unsigned grid = (unsigned)(((uint64_t)n_samples * 64 + kMeasThreads - 1) / kMeasThreads);
+    const int per = sample_per(n_blocks), n_runs = sample_runs(n_blocks);
     if (dtype == SV_C64)
-        k_sample_scan<float><<<grid, kMeasThreads, 0, s>>>((const cpx<float> *)amps, block_log, n_samples, blk,
-                                                           target, out);
+        k_sample_scan<float><<<grid, kMeasThreads, 0, s>>>((const cpx<float> *)amps, block_log, n_samples, per, n_runs,
+                                                           sums, pre, uniforms, out);
     else
-        k_sample_scan<double><<<grid, kMeasThreads, 0, s>>>((const cpx<double> *)amps, block_log, n_samples, blk,
-                                                            target, out);
+        k_sample_scan<double><<<grid, kMeasThreads, 0, s>>>((const cpx<double> *)amps, block_log, n_samples, per,
+                                                            n_runs, sums, pre, uniforms, out);
     return hipGetLastError();
 }
 

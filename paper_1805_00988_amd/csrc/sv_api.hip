@@ -2649,45 +2649,31 @@ int sv_sample(sv_handle h, int n_samples, const double *uniforms, uint64_t *host
         if (!(uniforms[i] >= 0.0 && uniforms[i] < 1.0)) return fail(SV_EINVAL, "uniforms must be in [0, 1)");
     const int bl = sample_block_log(h->n);
     const size_t B = (size_t)1 << (h->n - bl), S = (size_t)n_samples;
-    int rc = ensure_scratch(h, B + 3 * S);
+    // block sums, the sums of runs of blocks and their cumulative sums (the
+    // last one, the total, right before the outcomes: one copy brings both
+    // back), uniforms
+    const size_t R = (size_t)sample_runs((int)B);
+    int rc = ensure_scratch(h, B + 2 * R + 1 + 2 * S);
     if (rc) return rc;
-    double *d_sums = h->d_scratch;
-    int64_t *d_blk = reinterpret_cast<int64_t *>(h->d_scratch + B);
-    double *d_tgt = h->d_scratch + B + S;
-    uint64_t *d_out = reinterpret_cast<uint64_t *>(h->d_scratch + B + 2 * S);
+    double *d_sums = h->d_scratch, *d_runs = d_sums + B, *d_pre = d_runs + R, *d_u = d_pre + R + 1 + S;
+    uint64_t *d_out = reinterpret_cast<uint64_t *>(d_pre + R + 1);
+    SV_HIP(hipMemcpyAsync(d_u, uniforms, S * sizeof(double), hipMemcpyHostToDevice, h->stream));
     {
         Timed tm(h, K_MEASURE, state_bytes(h), 2.0 * (double)(1ull << h->n));
         SV_HIP(launch_block_sums(h->amps, h->n, h->dtype, bl, d_sums, h->stream));
     }
-    std::vector<double> sums(B), pre(B + 1);
-    SV_HIP(hipMemcpyAsync(sums.data(), d_sums, B * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-    SV_HIP(hipStreamSynchronize(h->stream));
-    pre[0] = 0.0;
-    for (size_t b = 0; b < B; ++b) pre[b + 1] = pre[b] + sums[b];
-    const double total = pre[B];
-    if (!(total > 0.0)) return fail(SV_EINVAL, "the state has norm 0");
-    // block of each sample: the first block whose cumulative end exceeds the
-    // target (the last block with mass if rounding leaves none)
-    size_t last_nz = 0;
-    for (size_t b = 0; b < B; ++b)
-        if (sums[b] > 0.0) last_nz = b;
-    std::vector<int64_t> blk(S);
-    std::vector<double> tgt(S);
-    for (size_t i = 0; i < S; ++i) {
-        const double t = uniforms[i] * total;
-        size_t b = (size_t)(std::upper_bound(pre.begin() + 1, pre.end(), t) - (pre.begin() + 1));
-        if (b >= B) b = last_nz;
-        blk[i] = (int64_t)b;
-        tgt[i] = t - pre[b];
-    }
-    SV_HIP(hipMemcpyAsync(d_blk, blk.data(), S * sizeof(int64_t), hipMemcpyHostToDevice, h->stream));
-    SV_HIP(hipMemcpyAsync(d_tgt, tgt.data(), S * sizeof(double), hipMemcpyHostToDevice, h->stream));
+    SV_HIP(launch_run_prefix(d_sums, (int)B, d_runs, d_pre, h->stream));
     {
         Timed tm(h, K_MEASURE, 0.0, 0.0);
-        SV_HIP(launch_sample_scan(h->amps, h->dtype, bl, n_samples, d_blk, d_tgt, d_out, h->stream));
+        SV_HIP(launch_sample_scan(h->amps, h->dtype, bl, n_samples, (int)B, d_sums, d_pre, d_u, d_out, h->stream));
     }
-    SV_HIP(hipMemcpyAsync(host_out, d_out, S * sizeof(uint64_t), hipMemcpyDeviceToHost, h->stream));
+    std::vector<uint64_t> back(S + 1);
+    SV_HIP(hipMemcpyAsync(back.data(), d_pre + R, (S + 1) * sizeof(uint64_t), hipMemcpyDeviceToHost, h->stream));
     SV_HIP(hipStreamSynchronize(h->stream));
+    double total;
+    std::memcpy(&total, &back[0], sizeof(total));
+    if (!(total > 0.0)) return fail(SV_EINVAL, "the state has norm 0");
+    std::memcpy(host_out, back.data() + 1, S * sizeof(uint64_t));
     return SV_OK;
 }
 

@@ -353,8 +353,13 @@ hipError_t launch_collapse(void *amps, int n, int dtype, uint64_t mask, uint64_t
 // sampling: blocks of 2^sample_block_log(n) amplitudes
 int sample_block_log(int n);
 hipError_t launch_block_sums(const void *amps, int n, int dtype, int block_log, double *sums, hipStream_t s);
-hipError_t launch_sample_scan(const void *amps, int dtype, int block_log, int n_samples, const int64_t *blk,
-                              const double *target, uint64_t *out, hipStream_t s);
+// the blocks (a power of two of them) in runs: pre[0 .. sample_runs] gets the
+// runs' cumulative sums; 'runs' holds sample_runs doubles
+int sample_runs(int n_blocks);
+hipError_t launch_run_prefix(const double *sums, int n_blocks, double *runs, double *pre, hipStream_t s);
+hipError_t launch_sample_scan(const void *amps, int dtype, int block_log, int n_samples, int n_blocks,
+                              const double *sums, const double *pre, const double *uniforms, uint64_t *out,
+                              hipStream_t s);
 
 int adjoint_blocks();
 hipError_t launch_adjoint_init(const void *psi, void *lam, int n, int dtype, int n_terms,
