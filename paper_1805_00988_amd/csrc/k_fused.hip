@@ -182,8 +182,8 @@ struct Bf16Cfg<5> {
 
 // One block applied to the tile by this wave's wave-tiles.  f points to the
 // block's operand fragments.
-template <int K, bool SG, bool DG>
-__device__ __forceinline__ void block_bf16(cpx<float> *lds, cpx<float> *state, uint64_t base, const bf16x8 *f,
+template <int K, bool SG, bool DG, bool ZS>
+__device__ __forceinline__ uint32_t block_bf16(cpx<float> *lds, cpx<float> *state, uint64_t base, const bf16x8 *f,
                                            const BlockTabs &t, uint32_t n_wt, int wave, int nwaves) {
     using C = Bf16Cfg<K>;
     constexpr int ROWS = C::rows, KS = C::ksteps;
@@ -202,6 +202,7 @@ __device__ __forceinline__ void block_bf16(cpx<float> *lds, cpx<float> *state, u
     // results of row r at 4kk + q (16x16) or 4kk + 8(q/4) + q%4 (32x32)
     const uint32_t l_lane = t.goff[r] ^ t.qoff[4 * kk];
     const uint64_t g_lane = base | t.gg[r] | t.gq[4 * kk];
+    uint32_t bits = 0;
     for (uint32_t wt = wave; wt < n_wt; wt += nwaves) {
         const uint32_t lw = t.goff[ROWS + wt] ^ l_lane; // goff_hi[wt]
         const uint64_t gw = t.gg[ROWS + wt] | g_lane;
@@ -212,6 +213,9 @@ __device__ __forceinline__ void block_bf16(cpx<float> *lds, cpx<float> *state, u
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 x[i] = blk_load<float, SG>(lds, state, lw ^ t.qoff[8 * s + i], gw | t.gq[8 * s + i]);
+            if constexpr (ZS)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) bits |= magnitude_bits(x[i].re) | magnitude_bits(x[i].im);
             bf16x8 h, l;
             split4(x, h, l);
             if constexpr (ROWS == 32) {
@@ -236,6 +240,7 @@ __device__ __forceinline__ void block_bf16(cpx<float> *lds, cpx<float> *state, u
             blk_store<float, DG>(lds, state, lw ^ t.qoff[c], gw | t.gq[c], cpx<float>{yr[q], yi[q]});
         }
     }
+    return bits;
 }
 
 // complex64, FP32 (v_mfma_f32_16x16x4_f32 for K = 4, 32x32x2 for K = 5).
@@ -253,8 +258,8 @@ struct F32Cfg<5> {
     static constexpr int rows = 32, kps = 2, threads = 256;
 };
 
-template <int K, bool SG, bool DG>
-__device__ __forceinline__ void block_f32(cpx<float> *lds, cpx<float> *state, uint64_t base, const float *f,
+template <int K, bool SG, bool DG, bool ZS>
+__device__ __forceinline__ uint32_t block_f32(cpx<float> *lds, cpx<float> *state, uint64_t base, const float *f,
                                           const BlockTabs &t, uint32_t n_wt, int wave, int nwaves) {
     using C = F32Cfg<K>;
     constexpr int D = 1 << K, ROWS = C::rows, KPS = C::kps;
@@ -272,6 +277,7 @@ __device__ __forceinline__ void block_f32(cpx<float> *lds, cpx<float> *state, ui
     // 4kk + 8(q/4) + q%4 (32x32) of row r
     const uint32_t la = t.goff[r] ^ t.qoff[kk], lo = t.goff[r] ^ t.qoff[4 * kk];
     const uint64_t ga = base | t.gg[r] | t.gq[kk], go = base | t.gg[r] | t.gq[4 * kk];
+    uint32_t bits = 0;
     for (uint32_t wt = wave; wt < n_wt; wt += nwaves) {
         const uint32_t lh = t.goff[ROWS + wt];
         const uint64_t gh = t.gg[ROWS + wt];
@@ -279,6 +285,7 @@ __device__ __forceinline__ void block_f32(cpx<float> *lds, cpx<float> *state, ui
 #pragma unroll
         for (int s = 0; s < HALF; ++s) {
             const cpx<float> x = blk_load<float, SG>(lds, state, lh ^ la ^ t.qoff[KPS * s], gh | ga | t.gq[KPS * s]);
+            if constexpr (ZS) bits |= magnitude_bits(x.re) | magnitude_bits(x.im);
             if constexpr (ROWS == 32) {
                 yr = __builtin_amdgcn_mfma_f32_32x32x2f32(bw[0][s], x.re, yr, 0, 0, 0);
                 yi = __builtin_amdgcn_mfma_f32_32x32x2f32(bw[1][s], x.re, yi, 0, 0, 0);
@@ -297,6 +304,7 @@ __device__ __forceinline__ void block_f32(cpx<float> *lds, cpx<float> *state, ui
             blk_store<float, DG>(lds, state, lh ^ lo ^ t.qoff[c], gh | go | t.gq[c], cpx<float>{yr[q], yi[q]});
         }
     }
+    return bits;
 }
 
 // complex128 on the FP64 matrix cores (v_mfma_f64_16x16x4f64; result
@@ -304,8 +312,8 @@ __device__ __forceinline__ void block_f32(cpx<float> *lds, cpx<float> *state, ui
 // device): wave-tiles of 16 groups, D/16 output tiles of 16 amplitudes per
 // part, K-steps as in the FP32 kernel.  Fragments stay in registers for
 // K = 4 and are read per K-step for K = 5.
-template <int K, bool SG, bool DG>
-__device__ __forceinline__ void block_f64(cpx<double> *lds, cpx<double> *state, uint64_t base,
+template <int K, bool SG, bool DG, bool ZS>
+__device__ __forceinline__ uint32_t block_f64(cpx<double> *lds, cpx<double> *state, uint64_t base,
                                           const double *frag, const BlockTabs &t, uint32_t n_wt, int wave,
                                           int nwaves) {
     constexpr int D = 1 << K;
@@ -323,6 +331,7 @@ __device__ __forceinline__ void block_f64(cpx<double> *lds, cpx<double> *state, 
     // reads: index kk + 4s of row r; results: kk + 4q + 16nt of row r
     const uint32_t l_lane = t.goff[r] ^ t.qoff[kk];
     const uint64_t g_lane = base | t.gg[r] | t.gq[kk];
+    uint32_t bits = 0;
     for (uint32_t wt = wave; wt < n_wt; wt += nwaves) {
         const uint32_t lw = t.goff[16 + wt] ^ l_lane; // goff_hi[wt]
         const uint64_t gw = t.gg[16 + wt] | g_lane;
@@ -334,6 +343,7 @@ __device__ __forceinline__ void block_f64(cpx<double> *lds, cpx<double> *state, 
 #pragma unroll
         for (int s = 0; s < HALF; ++s) {
             const cpx<double> x = blk_load<double, SG>(lds, state, lw ^ t.qoff[4 * s], gw | t.gq[4 * s]);
+            if constexpr (ZS) bits |= magnitude_bits(x.re) | magnitude_bits(x.im);
 #pragma unroll
             for (int p = 0; p < 2; ++p)
 #pragma unroll
@@ -354,6 +364,7 @@ __device__ __forceinline__ void block_f64(cpx<double> *lds, cpx<double> *state, 
                                       cpx<double>{acc[0][nt][q], acc[1][nt][q]});
             }
     }
+    return bits;
 }
 
 // Register-staged passes (any tile size; the only path for K = 5): each
@@ -366,26 +377,35 @@ struct EngCfg {
     static constexpr int threads = ENG == kPrecMfma64 ? 256 : (K == 5 ? 256 : 512);
 };
 
-template <int ENG, int K, bool SG, bool DG>
-__device__ __forceinline__ void apply_block_t(cpx<typename EngCfg<ENG, K>::T> *lds,
-                                              cpx<typename EngCfg<ENG, K>::T> *state, uint64_t base,
-                                              const char *op, const BlockTabs &t, uint32_t n_wt, int wave,
-                                              int nwaves) {
+// The return value of a block that reads the state with ZS: magnitude bits
+// of the lane's operands.
+template <int ENG, int K, bool SG, bool DG, bool ZS = false>
+__device__ __forceinline__ uint32_t apply_block_t(cpx<typename EngCfg<ENG, K>::T> *lds,
+                                                  cpx<typename EngCfg<ENG, K>::T> *state, uint64_t base,
+                                                  const char *op, const BlockTabs &t, uint32_t n_wt, int wave,
+                                                  int nwaves) {
     if constexpr (ENG == SV_PREC_SPLIT_BF16)
-        block_bf16<K, SG, DG>(lds, state, base, reinterpret_cast<const bf16x8 *>(op), t, n_wt, wave, nwaves);
+        return block_bf16<K, SG, DG, ZS>(lds, state, base, reinterpret_cast<const bf16x8 *>(op), t, n_wt, wave,
+                                         nwaves);
     else if constexpr (ENG == SV_PREC_FP32)
-        block_f32<K, SG, DG>(lds, state, base, reinterpret_cast<const float *>(op), t, n_wt, wave, nwaves);
+        return block_f32<K, SG, DG, ZS>(lds, state, base, reinterpret_cast<const float *>(op), t, n_wt, wave, nwaves);
     else
-        block_f64<K, SG, DG>(lds, state, base, reinterpret_cast<const double *>(op), t, n_wt, wave, nwaves);
+        return block_f64<K, SG, DG, ZS>(lds, state, base, reinterpret_cast<const double *>(op), t, n_wt, wave,
+                                        nwaves);
 }
 
-template <int ENG, int K>
+// ZSKIP (kSkipZero): a tile whose operands the first block found to be all
+// zero is left as it is; the first block's results, in LDS, are dropped.
+// While a register spreads from a basis state most tiles are zeros: depth 40
+// at 28 qubits in split-BF16 blocks, 37.4 -> 33.4 ms.
+template <int ENG, int K, bool ZSKIP>
 __global__ __launch_bounds__((EngCfg<ENG, K>::threads)) void k_dense_mfma(
     typename Amp16<typename EngCfg<ENG, K>::T>::type *v, TileSpec sp, int m, const DenseBlock *__restrict__ blocks,
     int n_blocks, const char *__restrict__ base_ptr, uint64_t n_tiles, uint32_t direct) {
     using Cf = EngCfg<ENG, K>;
     using T = typename Cf::T;
     extern __shared__ char lds_raw[];
+    __shared__ uint32_t seen[ZSKIP ? Cf::threads / 64 : 1];
     cpx<T> *lds = reinterpret_cast<cpx<T> *>(lds_raw);
     cpx<T> *state = reinterpret_cast<cpx<T> *>(v);
     const uint32_t tsize = 1u << m;
@@ -398,7 +418,8 @@ __global__ __launch_bounds__((EngCfg<ENG, K>::threads)) void k_dense_mfma(
             tile_load<T, Cf::threads, 8>(v, lds, sp, base, tsize);
             __syncthreads();
         }
-        for (int b = 0; b < n_blocks; ++b) {
+        bool zero = false;
+        for (int b = 0; b < n_blocks && !zero; ++b) {
             const DenseBlock &B = blocks[b];
             const uint32_t *tab = reinterpret_cast<const uint32_t *>(base_ptr + B.tab_off);
             const uint64_t *gtab = reinterpret_cast<const uint64_t *>(base_ptr + B.gtab_off);
@@ -406,8 +427,18 @@ __global__ __launch_bounds__((EngCfg<ENG, K>::threads)) void k_dense_mfma(
             const char *op = base_ptr + B.op_off + variant_offset(B, base);
             const bool sg = b == 0 && dfirst, dg = b == n_blocks - 1 && dlast;
             if (sg && dg) apply_block_t<ENG, K, true, true>(lds, state, base, op, t, n_wt, wave, nwaves);
-            else if (sg) apply_block_t<ENG, K, true, false>(lds, state, base, op, t, n_wt, wave, nwaves);
-            else if (dg) apply_block_t<ENG, K, false, true>(lds, state, base, op, t, n_wt, wave, nwaves);
+            else if (sg) {
+                const uint32_t bits = apply_block_t<ENG, K, true, false, ZSKIP>(lds, state, base, op, t, n_wt, wave,
+                                                                               nwaves);
+                if constexpr (ZSKIP) {
+                    const uint32_t any = wave_zero(bits) ? 0u : 1u;
+                    if ((threadIdx.x & 63u) == 0u) seen[wave] = any;
+                    __syncthreads();
+                    uint32_t tile_any = 0;
+                    for (int w = 0; w < nwaves; ++w) tile_any |= seen[w];
+                    zero = __builtin_amdgcn_readfirstlane(tile_any) == 0u;
+                }
+            } else if (dg) apply_block_t<ENG, K, false, true>(lds, state, base, op, t, n_wt, wave, nwaves);
             else apply_block_t<ENG, K, false, false>(lds, state, base, op, t, n_wt, wave, nwaves);
             // the next block (or the next tile's first LDS writes) follows
             // every wave's reads of this one
@@ -439,11 +470,15 @@ hipError_t launch_dense_pass(void *amps, int n, int dtype, const TileSpec &sp, i
 #define SV_MFMA_CASE(ENG, KK)                                                                      \
     if (prec == ENG && k == KK) {                                                                  \
         using VT = typename Amp16<typename EngCfg<ENG, KK>::T>::type;                              \
-        (void)hipFuncSetAttribute((const void *)k_dense_mfma<ENG, KK>,                             \
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);           \
-        k_dense_mfma<ENG, KK><<<grid, EngCfg<ENG, KK>::threads, lds, s>>>((VT *)amps, sp, m, dev_blocks, \
-                                                                         n_blocks, dev_base, n_tiles, \
-                                                                         direct);                      \
+        auto launch = [&](auto kernel) {                                                           \
+            (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, \
+                                      (int)lds);                                                   \
+            kernel<<<grid, EngCfg<ENG, KK>::threads, lds, s>>>((VT *)amps, sp, m, dev_blocks, n_blocks, \
+                                                               dev_base, n_tiles, direct);         \
+        };                                                                                         \
+        const uint32_t z = kSkipZero | kDirectFirst | kDirectLast;                                 \
+        if ((direct & z) == z) launch(k_dense_mfma<ENG, KK, true>);                                \
+        else launch(k_dense_mfma<ENG, KK, false>);                                                 \
         return hipGetLastError();                                                                  \
     }
         SV_MFMA_CASE(SV_PREC_SPLIT_BF16, 4)

@@ -65,19 +65,6 @@ constexpr int kMinNtRunBits = 3; // 2^3 16-byte vectors = 128 bytes
 // storing everything, 22.5 ms).  The test covers whole waves, not lanes:
 // lines written in part would be read back by the memory.  'skip' is off
 // when a matrix entry is not finite in the state's precision (0 * inf).
-__device__ __forceinline__ uint32_t magnitude_bits(float x) { return __float_as_uint(x) & 0x7fffffffu; }
-__device__ __forceinline__ uint32_t magnitude_bits(double x) {
-    const uint64_t b = __double_as_longlong(x);
-    return ((uint32_t)(b >> 32) & 0x7fffffffu) | (uint32_t)b;
-}
-__device__ __forceinline__ uint32_t magnitude_bits(const float4 &v) {
-    return magnitude_bits(v.x) | magnitude_bits(v.y) | magnitude_bits(v.z) | magnitude_bits(v.w);
-}
-__device__ __forceinline__ uint32_t magnitude_bits(const double2 &v) {
-    return magnitude_bits(v.x) | magnitude_bits(v.y);
-}
-__device__ __forceinline__ bool wave_zero(uint32_t bits) { return __builtin_amdgcn_ballot_w64(bits != 0u) == 0ull; }
-
 static bool finite_as(int dtype, const double *U, int n) {
     for (int i = 0; i < n; ++i)
         if (!(std::fabs(U[i]) <= (dtype == SV_C64 ? (double)FLT_MAX : DBL_MAX))) return false;

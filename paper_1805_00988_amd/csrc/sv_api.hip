@@ -330,6 +330,12 @@ static uint64_t tile_qubits(const TileSpec &sp) {
     return S;
 }
 
+// Some qubit outside the tile is as the basis state left it: most of the
+// pass's tiles are likely to hold zeros.
+static bool untouched_outside(const sv_state *h, const TileSpec &sp) {
+    return (((1ull << h->n) - 1ull) & ~tile_qubits(sp) & ~h->moved) != 0;
+}
+
 // A tile pass compiled for the device: tile layout, register sweeps and the
 // sweeps' gate records (stored consecutively in sweep order).
 struct PassCode {
@@ -939,8 +945,7 @@ static int launch_pass(sv_state *h, const PassCode &pc, size_t off) {
     const TileSweep *sw = reinterpret_cast<const TileSweep *>(h->d_arena + off);
     const char *gt = h->d_arena + off + align256(pc.sweeps.size() * sizeof(TileSweep));
     Timed tm(h, K_TILE, 2.0 * state_bytes(h), pc.flops_per_amp * (double)(1ull << h->n));
-    const uint64_t all = h->n < 64 ? (1ull << h->n) - 1ull : ~0ull;
-    const bool zeros = pc.finite && (all & ~tile_qubits(pc.sp) & ~h->moved) != 0;
+    const bool zeros = pc.finite && untouched_outside(h, pc.sp);
     SV_HIP(launch_tile(h->amps, h->n, h->dtype, pc.sp, sw, (int)pc.sweeps.size(), gt, pc.two_qubit, pc.lane_phases,
                        pc.direct | (zeros ? kSkipZero : 0u), h->stream));
     h->moved |= pc.moves;
@@ -1570,6 +1575,8 @@ struct FusedPass {
     int k = 0;
     int engine = SV_PREC_NATIVE;
     uint32_t direct = 0; // kDirectFirst / kDirectLast (matrix cores)
+    uint64_t moves = 0;  // qubits of its blocks
+    bool finite = true;  // every matrix entry is, in FP32
     std::vector<DenseBlock> blocks;
     // per block, its padded matrix for each variant of its outside qubits
     std::vector<std::vector<std::vector<std::complex<double>>>> mats;
@@ -1661,6 +1668,7 @@ static FusedPass build_fused_pass(const sv_state *h, const TileSpec &sp, const s
     if (is_mfma(fp.engine)) fp.direct = kDirectFirst | kDirectLast;
     for (int bi : idx) {
         const Block &B = bs[bi];
+        for (int j = 0; j < B.k; ++j) fp.moves |= 1ull << B.q[j];
         DenseBlock db{};
         db.bp.k = fp.k;
         uint32_t used = 0;
@@ -1682,6 +1690,8 @@ static FusedPass build_fused_pass(const sv_state *h, const TileSpec &sp, const s
         std::vector<std::vector<std::complex<double>>> vs;
         for (const auto &M : B.var.empty() ? std::vector<std::vector<std::complex<double>>>{B.M} : B.var)
             vs.push_back(B.k == fp.k ? M : pad_matrix(M, B.k, fp.k));
+        for (const auto &M : vs)
+            for (const auto &z : M) fp.finite = fp.finite && std::abs(z.real()) <= FLT_MAX && std::abs(z.imag()) <= FLT_MAX;
         fp.mats.push_back(std::move(vs));
         fp.flops_per_amp += 8.0 * (double)(1 << B.k);
     }
@@ -1926,10 +1936,11 @@ static void stage_fused(sv_state *h, FusedPass &fp, size_t off) {
 static int launch_fused(sv_state *h, const FusedPass &fp, size_t off) {
     if (fp.plain) return launch_pass(h, fp.code, off);
     Timed tm(h, K_FUSED, 2.0 * state_bytes(h), fp.flops_per_amp * (double)(1ull << h->n));
-    h->moved |= tile_qubits(fp.sp);
+    const uint32_t zeros = fp.finite && untouched_outside(h, fp.sp) ? kSkipZero : 0u;
     SV_HIP(launch_dense_pass(h->amps, h->n, h->dtype, fp.sp, fp.k,
                              reinterpret_cast<const DenseBlock *>(h->d_arena + off), (int)fp.blocks.size(),
-                             h->d_arena, fp.engine, fp.direct, h->stream));
+                             h->d_arena, fp.engine, fp.direct | zeros, h->stream));
+    h->moved |= fp.moves;
     return SV_OK;
 }
 

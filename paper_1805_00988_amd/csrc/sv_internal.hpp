@@ -70,6 +70,21 @@ __device__ __forceinline__ void st_nt(double2 *p, double2 v) {
     __builtin_nontemporal_store(w, reinterpret_cast<f64x2_nt *>(p));
 }
 
+// ------------------------------------------------------------ zero tests
+// Bits that are all clear where a value is zero (of either sign).
+__device__ __forceinline__ uint32_t magnitude_bits(float x) { return __float_as_uint(x) & 0x7fffffffu; }
+__device__ __forceinline__ uint32_t magnitude_bits(double x) {
+    const uint64_t b = __double_as_longlong(x);
+    return ((uint32_t)(b >> 32) & 0x7fffffffu) | (uint32_t)b;
+}
+__device__ __forceinline__ uint32_t magnitude_bits(const float4 &v) {
+    return magnitude_bits(v.x) | magnitude_bits(v.y) | magnitude_bits(v.z) | magnitude_bits(v.w);
+}
+__device__ __forceinline__ uint32_t magnitude_bits(const double2 &v) {
+    return magnitude_bits(v.x) | magnitude_bits(v.y);
+}
+__device__ __forceinline__ bool wave_zero(uint32_t bits) { return __builtin_amdgcn_ballot_w64(bits != 0u) == 0ull; }
+
 // ------------------------------------------------------ index enumeration
 // Positions (ascending) at which a zero bit is inserted into an enumeration
 // index, and the bits OR-ed in afterwards.  This maps a dense counter onto
