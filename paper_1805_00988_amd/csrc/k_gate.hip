@@ -543,7 +543,36 @@ __device__ void tile_pass_direct(cpx<T> *__restrict__ state, cpx<T> *lds, const 
             PhaseAcc<T, W> acc;
             acc.init();
             run_records<T, W, TWOQ, LPH>(v, acc, gb, recs + S.rec_off, ng, base);
-            if (last) {
+            if (S.perm) {
+                // the results go to other groups' places, once every group
+                // of this sweep has been read (after a first sweep's loads
+                // from the state nothing reads the LDS tile)
+                if (first == last) __syncthreads();
+                const uint32_t to = permuted_group(S, recs, g, base);
+                if (last) {
+                    const uint64_t rt = tile_offset(sp, to);
+                    uint64_t tbit[W];
+#pragma unroll
+                    for (int b = 0; b < W; ++b) tbit[b] = tile_offset(sp, S.reg_col[b]);
+#pragma unroll
+                    for (int j = 0; j < D; ++j) {
+                        uint64_t o = rt;
+#pragma unroll
+                        for (int b = 0; b < W; ++b)
+                            if ((j >> b) & 1) o ^= tbit[b];
+                        state[base | o] = v[j];
+                    }
+                } else {
+#pragma unroll
+                    for (int j = 0; j < D; ++j) {
+                        uint32_t o = to;
+#pragma unroll
+                        for (int b = 0; b < W; ++b)
+                            if ((j >> b) & 1) o ^= S.reg_col[b];
+                        lds[o] = v[j];
+                    }
+                }
+            } else if (last) {
 #pragma unroll
                 for (int j = 0; j < D; ++j) row[goff_of(j)] = v[j];
             } else {

@@ -336,6 +336,13 @@ static bool untouched_outside(const sv_state *h, const TileSpec &sp) {
     return (((1ull << h->n) - 1ull) & ~tile_qubits(sp) & ~h->moved) != 0;
 }
 
+// X on local bit t where the tile holds the index bits 'cout' and, if c >= 0,
+// the amplitude has local bit c set (not both kinds of control).
+struct PermGate {
+    int t, c;
+    uint64_t cout;
+};
+
 // A tile pass compiled for the device: tile layout, register sweeps and the
 // sweeps' gate records (stored consecutively in sweep order).
 struct PassCode {
@@ -348,6 +355,7 @@ struct PassCode {
     uint64_t moves = 0;         // targets of its gates that are not diagonal
     bool finite = true;         // every matrix entry is, in the state's precision
     std::vector<TileSweep> sweeps;
+    std::vector<std::vector<PermGate>> perms; // per sweep: the X gates its stores apply
     std::vector<TileGate> gates; // records in sweep order (host form)
     std::vector<std::vector<char>> tables; // SK_PTAB payloads (descriptors and tables)
     std::vector<char> recs;      // the same, packed for the device (pack_records)
@@ -389,6 +397,49 @@ static void pack_records(PassCode &pc, bool f32) {
             r.size = (int32_t)sz;
             const char *src = reinterpret_cast<const char *>(&r);
             pc.recs.insert(pc.recs.end(), src, src + sz);
+        }
+    }
+    // the sweeps' permutations: images of the group-index bits, the register
+    // bits and 0, and the conditional constants
+    for (size_t si = 0; si < pc.sweeps.size(); ++si) {
+        TileSweep &S = pc.sweeps[si];
+        S.perm = si < pc.perms.size() && !pc.perms[si].empty();
+        if (!S.perm) continue;
+        const int W = std::min(pc.m, kSweepW), ab = f32 ? 8 : 16;
+        uint32_t regs = 0;
+        int n_reg = 0;
+        for (int b = 0; b < W && (b == 0 || S.qpos[b] > S.qpos[b - 1]); ++b, ++n_reg) regs |= 1u << S.qpos[b];
+        std::vector<uint32_t> col(pc.m); // images of the tile index's bits
+        for (int b = 0; b < pc.m; ++b) col[b] = 1u << b;
+        uint32_t cst = 0;
+        std::vector<PermCond> conds;
+        for (const PermGate &p : pc.perms[si]) {
+            const uint32_t tb = 1u << p.t;
+            if (p.c >= 0) {
+                for (uint32_t &x : col)
+                    if ((x >> p.c) & 1u) x ^= tb;
+                if ((cst >> p.c) & 1u) cst ^= tb;
+                for (PermCond &q : conds)
+                    if ((q.vec >> p.c) & 1u) q.vec ^= tb;
+            } else if (p.cout == 0) {
+                cst ^= tb;
+            } else {
+                conds.push_back({p.cout, tb, 0u});
+            }
+        }
+        const bool last = si + 1 == pc.sweeps.size();
+        auto out = [&](uint32_t l) { return last ? l : lds_swizzle(l, ab); };
+        for (int b = 0, i = 0, r = 0; b < pc.m; ++b) {
+            if ((regs >> b) & 1u) S.reg_col[r++] = out(col[b]);
+            else S.lane_col[i++] = out(col[b]);
+        }
+        S.cst = out(cst);
+        S.n_cond = (int32_t)conds.size();
+        S.cond_off = (int32_t)pc.recs.size();
+        for (PermCond &q : conds) {
+            q.vec = out(q.vec);
+            const char *src = reinterpret_cast<const char *>(&q);
+            pc.recs.insert(pc.recs.end(), src, src + sizeof(q));
         }
     }
     pc.recs.resize(pc.recs.size() + kRecordTail, 0);
@@ -638,16 +689,19 @@ static TileGate encode_probe(const TileSpec &sp, const std::vector<int> &qset, c
 constexpr int kMinPhaseRun = 4;
 
 static PassCode compile_pass(const TileSpec &sp, const std::vector<const Gate *> &gs, int sweep_w, bool f32,
-                             const std::vector<const Probe *> *probes = nullptr, bool lph_f32 = false) {
+                             const std::vector<const Probe *> *probes = nullptr, bool lph_f32 = false,
+                             bool store_perms = false) {
     PassCode pc;
     pc.sp = sp;
     pc.m = sp.L + sp.K;
     const int W = std::min(pc.m, sweep_w);
+    // stores can permute where every thread of whole waves holds one group
+    const bool perms = store_perms && W == sweep_w && pc.m - W >= 6 && pc.m - W <= kPermLane;
     std::vector<int> qset;
     std::vector<size_t> cur;
     auto probe_of = [&](size_t i) -> const Probe * { return probes ? (*probes)[i] : nullptr; };
-    auto close = [&]() {
-        if (cur.empty()) return;
+    auto close = [&](bool empty_too) {
+        if (cur.empty() && !empty_too) return;
         // free register positions come from the top of the tile, leaving the
         // low tile bits to the lanes (contiguous accesses)
         for (int b = pc.m - 1; (int)qset.size() < W && b >= 0; --b)
@@ -882,10 +936,29 @@ static PassCode compile_pass(const TileSpec &sp, const std::vector<const Gate *>
     // gate on other qubits across it, since that gate and its inverse cancel
     // around the probe's Pauli).  Fewer sweeps mean fewer exchanges of the
     // tile through LDS.
+    //
+    // X gates and controlled X gates (one control in the tile or any outside
+    // it) that nothing later in the sweep touches are not applied to
+    // registers: the sweep's stores permute (TileSweep::perm).  One whose
+    // target the sweep does not hold in registers waits for its end too, its
+    // qubits closed to later gates that do not commute with it ('target',
+    // 'control' below), and one that commutes to the sweep's start joins the
+    // stores of the sweep before.
     std::vector<char> done(gs.size(), 0);
     size_t first = 0;
+    size_t left = gs.size(); // gates in no sweep yet
+    std::vector<PermGate> perm(gs.size(), PermGate{-1, -1, 0}); // t < 0: none
+    for (size_t i = 0; i < gs.size() && perms; ++i) {
+        if (!is_x(*gs[i])) continue;
+        TileGate tmp{};
+        const uint32_t cin = encode_controls(sp, gs[i]->ctrl, &tmp);
+        if (__builtin_popcount(cin) > 1 || (cin && tmp.cout)) continue;
+        perm[i] = {local_bit(sp, gs[i]->t[0]), cin ? __builtin_ctz(cin) : -1, tmp.cout};
+    }
     while (first < gs.size()) {
         uint64_t blocked = 0; // qubits of the gates left behind by this sweep
+        uint64_t target = 0, control = 0; // qubits of the gates waiting for its end
+        std::vector<PermGate> at_end;
         for (size_t i = first; i < gs.size(); ++i) {
             if (done[i]) continue;
             const Gate *g = gs[i];
@@ -894,9 +967,12 @@ static PassCode compile_pass(const TileSpec &sp, const std::vector<const Gate *>
                 blocked |= qm;
                 continue;
             }
-            if (is_diag1(*g) && !probe_of(i)) {
+            const bool diag = is_diag1(*g) && !probe_of(i);
+            const bool held = (qm & target) || (!diag && (g->tmask() & control)); // does not commute with a waiting gate
+            if (diag && !held) {
                 cur.push_back(i);
                 done[i] = 1;
+                --left;
                 continue;
             }
             std::vector<int> need;
@@ -904,13 +980,23 @@ static PassCode compile_pass(const TileSpec &sp, const std::vector<const Gate *>
                 const int lb = local_bit(sp, g->t[j]);
                 if (std::find(qset.begin(), qset.end(), lb) == qset.end()) need.push_back(lb);
             }
-            if ((int)(qset.size() + need.size()) > W) {
+            const bool fits = !held && (int)(qset.size() + need.size()) <= W;
+            if (!fits && perm[i].t >= 0) {
+                at_end.push_back(perm[i]);
+                target |= g->tmask();
+                control |= g->ctrl;
+                done[i] = 1;
+                --left;
+                continue;
+            }
+            if (!fits) {
                 blocked |= qm;
                 continue;
             }
             qset.insert(qset.end(), need.begin(), need.end());
             cur.push_back(i);
             done[i] = 1;
+            --left;
         }
         // the first open gate fits an empty register set whenever W >= k;
         // should it not, it still gets a sweep of its own (the loop ends)
@@ -918,8 +1004,52 @@ static PassCode compile_pass(const TileSpec &sp, const std::vector<const Gate *>
             for (int j = 0; j < gs[first]->k; ++j) qset.push_back(local_bit(sp, gs[first]->t[j]));
             cur.push_back(first);
             done[first] = 1;
+            --left;
         }
-        close();
+        if (perms) {
+            // gates that commute past all kept gates after them (not in the
+            // pass's last sweep: its stores go to the state, in the order the
+            // lanes were given for them), then past all kept gates before
+            // them
+            for (int back = 1; back >= 0; --back) {
+                uint64_t any = 0, moved = 0; // qubits of the kept gates; those moved by them
+                std::vector<size_t> kept;
+                std::vector<PermGate> out;
+                for (size_t k = 0; k < cur.size(); ++k) {
+                    const size_t i = cur[back ? cur.size() - 1 - k : k];
+                    const Gate &g = *gs[i];
+                    if ((back ? left > 0 : !pc.sweeps.empty()) && perm[i].t >= 0 && !(g.tmask() & any) &&
+                        !(g.ctrl & moved)) {
+                        out.push_back(perm[i]);
+                        continue;
+                    }
+                    any |= g.qmask();
+                    if (!is_diag1(g)) moved |= g.tmask();
+                    kept.push_back(i);
+                }
+                if (back) {
+                    std::reverse(kept.begin(), kept.end());
+                    at_end.insert(at_end.begin(), out.rbegin(), out.rend());
+                } else if (!out.empty()) {
+                    auto &before = pc.perms.back();
+                    before.insert(before.end(), out.begin(), out.end());
+                }
+                cur = kept;
+            }
+            qset.clear();
+            for (size_t i : cur)
+                if (!is_diag1(*gs[i]) || probe_of(i))
+                    for (int j = 0; j < gs[i]->k; ++j) {
+                        const int lb = local_bit(sp, gs[i]->t[j]);
+                        if (std::find(qset.begin(), qset.end(), lb) == qset.end()) qset.push_back(lb);
+                    }
+        }
+        if (cur.empty() && !pc.sweeps.empty()) {
+            pc.perms.back().insert(pc.perms.back().end(), at_end.begin(), at_end.end());
+        } else {
+            close(!at_end.empty());
+            pc.perms.push_back(std::move(at_end));
+        }
         while (first < gs.size() && done[first]) ++first;
     }
     for (const Gate *g : gs) {
@@ -1258,7 +1388,7 @@ static int run_gates(sv_state *h, const std::vector<Gate> &gs, int mode) {
             for (int gi : p.gates) local.push_back(retarget_phase(gs[gi], tile_qubits(sp)));
             std::vector<const Gate *> ptrs;
             for (const Gate &g : local) ptrs.push_back(&g);
-            r.code = compile_pass(sp, ptrs, sweep_width(h->dtype), h->dtype == SV_C64, nullptr, true);
+            r.code = compile_pass(sp, ptrs, sweep_width(h->dtype), h->dtype == SV_C64, nullptr, true, true);
         }
         ready.push_back(std::move(r));
         int rc;
@@ -1832,7 +1962,7 @@ static int compile_fused_gates(const sv_state *h, const std::vector<Gate> &gs, i
             fp.plain = true;
             fp.sp = sp;
             fp.m = mtile;
-            fp.code = compile_pass(sp, ptrs, sweep_width(h->dtype), h->dtype == SV_C64, nullptr, true);
+            fp.code = compile_pass(sp, ptrs, sweep_width(h->dtype), h->dtype == SV_C64, nullptr, true, true);
             fp.cost = plain_pass_cost(h, fp.code);
             if (fp.cost < best.cost) {
                 best = std::move(fp);
@@ -1965,20 +2095,15 @@ static int run_fused_passes(sv_state *h, std::vector<FusedPass> &fps, ArenaRoom 
     return SV_OK;
 }
 
-// Fuse and run a gate list: all passes in one upload on small states, each
-// launched as soon as it is compiled on larger ones (as in run_gates).
+// Fuse and run a gate list.  Each pass is launched as soon as it is compiled
+// (about a millisecond of host time, on any size of state).
 static int run_fused_gates(sv_state *h, const std::vector<Gate> &gs, int k_max, int prec, int *n_blocks) {
-    const bool each = lookahead_level(h) > 0;
     ArenaRoom room;
-    std::vector<FusedPass> ready;
-    const int rc = compile_fused_gates(h, gs, k_max, prec, n_blocks, [&](FusedPass fp) -> int {
-        ready.push_back(std::move(fp));
-        if (!each) return SV_OK;
-        const int e = run_fused_passes(h, ready, room);
-        ready.clear();
-        return e;
+    std::vector<FusedPass> ready(1);
+    return compile_fused_gates(h, gs, k_max, prec, n_blocks, [&](FusedPass fp) -> int {
+        ready[0] = std::move(fp);
+        return run_fused_passes(h, ready, room);
     });
-    return rc ? rc : run_fused_passes(h, ready, room);
 }
 
 static int parse_ops(const sv_state *h, int n, const sv_op *ops, int n_ops, const double *params,

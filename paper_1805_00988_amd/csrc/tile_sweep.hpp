@@ -620,48 +620,16 @@ __device__ __forceinline__ void register_offsets(const TileSweep &S, uint32_t (&
     }
 }
 
-// Apply the sweeps of one pass to the tile in LDS.  'base' is the global
-// index of the tile's local amplitude 0 (for controls outside the tile).
-// Caller synchronises before (tile loaded); every sweep ends with a barrier.
-// The LDS swizzle is linear over XOR and a group's bits are disjoint from
-// the register bits, so amplitude j of the group sits at
-// lds_phys(gb) ^ lds_phys(register bits of j).
-template <typename T, int W, bool TWOQ>
-__device__ void tile_run_sweeps(cpx<T> *lds, int m, uint64_t base, const TileSweep *__restrict__ sweeps,
-                                int n_sweeps, const char *__restrict__ recs) {
-    constexpr int D = 1 << W;
-    const uint32_t n_groups = (1u << m) >> W;
-    for (int si = 0; si < n_sweeps; ++si) {
-        const TileSweep &S = sweeps[si];
-        const int ng = S.n_gates;
-        const char *r0 = recs + S.rec_off;
-        uint32_t PF[D];
-        register_offsets<T, W>(S, PF);
-        for (uint32_t g = threadIdx.x; g < n_groups; g += blockDim.x) {
-            const uint32_t gb = group_bits<W>(S, g);
-            const uint32_t pg = lds_phys<T>(gb);
-            cpx<T> v[D];
-            uint32_t addr[D];
+// Image of group g (register index 0) under the sweep's permutation.
+__device__ __forceinline__ uint32_t permuted_group(const TileSweep &S, const char *__restrict__ recs, uint32_t g,
+                                                   uint64_t base) {
+    const PermCond *pc = reinterpret_cast<const PermCond *>(recs + S.cond_off);
+    uint32_t c = S.cst;
+    for (int i = 0; i < S.n_cond; ++i) c ^= (base & pc[i].cond) == pc[i].cond ? pc[i].vec : 0u;
+    uint32_t r = __builtin_amdgcn_readfirstlane(c);
 #pragma unroll
-            for (int j = 0; j < D; ++j) {
-                addr[j] = pg ^ PF[j];
-                v[j] = lds[addr[j]];
-            }
-            PhaseAcc<T, W> acc;
-            acc.init();
-            const char *rp = r0;
-            for (int gi = 0; gi < ng; ++gi) {
-                const TileGate &G = *reinterpret_cast<const TileGate *>(rp);
-                // advance before the gate: its inline assembly would make the
-                // compiler read the size again after it
-                rp += G.size;
-                sweep_gate_t<T, W, TWOQ>(v, acc, gb, G, base);
-            }
-#pragma unroll
-            for (int j = 0; j < D; ++j) lds[addr[j]] = v[j];
-        }
-        __syncthreads();
-    }
+    for (int i = 0; i < kPermLane; ++i) r ^= (0u - ((g >> i) & 1u)) & S.lane_col[i];
+    return r;
 }
 
 } // namespace sv
