@@ -317,7 +317,26 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint_tile(typename AV<T>::ty
                     sweep_gate_h<T, W + 1, TWOQ, false>(vw, acc_unused, gb, h, G, base);
                 }
             }
-            if (last) {
+            const uint32_t to = S.perm ? permuted_group(S, recs, g, base) : 0u;
+            if (last && S.perm) {
+                // other groups' places, once every group has been read
+                if (first) __syncthreads();
+                const uint64_t rt = tile_offset(sp, to);
+                uint64_t tbit[W];
+#pragma unroll
+                for (int b = 0; b < W; ++b) tbit[b] = tile_offset(sp, S.reg_col[b]);
+                if (act) {
+#pragma unroll
+                    for (int j = 0; j < D; ++j) {
+                        uint64_t o = rt;
+#pragma unroll
+                        for (int b = 0; b < W; ++b)
+                            if ((j >> b) & 1) o ^= tbit[b];
+                        ps[base | o] = v[j];
+                        ls[base | o] = w[j];
+                    }
+                }
+            } else if (last) {
                 if (act) {
 #pragma unroll
                     for (int j = 0; j < D; ++j) {
@@ -330,7 +349,17 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint_tile(typename AV<T>::ty
                 uint32_t PF[D], PN[D];
                 register_offsets<T, W>(S, PF);
                 register_offsets<T, W>(N, PN);
-                const uint32_t pg = lds_phys<T>(gb);
+                uint32_t pg = lds_phys<T>(gb);
+                if (S.perm) {
+                    pg = to;
+#pragma unroll
+                    for (int j = 0; j < D; ++j) {
+                        PF[j] = 0;
+#pragma unroll
+                        for (int b = 0; b < W; ++b)
+                            if ((j >> b) & 1) PF[j] ^= S.reg_col[b];
+                    }
+                }
                 const uint32_t pn = lds_phys<T>(group_bits<W>(N, act ? g : 0u));
                 // each barrier orders one vector's writes before its reads,
                 // and its reads before the next writes to the tile

@@ -64,6 +64,7 @@ __device__ void batch_tile(cpx<T> *state, cpx<T> *lds, const TileSpec &sp, int m
                            double &zacc) {
     constexpr int D = 1 << W;
     const uint32_t n_groups = (1u << m) >> W;
+    const uint32_t wave_first = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
     for (int si = 0; si < n_sweeps; ++si) {
         const TileSweep &S = sweeps[si];
         const bool first = si == 0, last = si == n_sweeps - 1;
@@ -116,7 +117,42 @@ __device__ void batch_tile(cpx<T> *state, cpx<T> *lds, const TileSpec &sp, int m
                 rp += G.size;
                 sweep_gate_t<T, W, TWOQ>(v, acc, gb, G, base);
             }
-            if (last) {
+            if (S.perm) {
+                // other groups' places, once every group of this sweep has
+                // been read
+                if (first == last) __syncthreads();
+                const uint32_t to = permuted_group(S, recs, g, base);
+                if (last) {
+                    const uint64_t rt = tile_offset(sp, to);
+                    uint64_t tbit[W];
+#pragma unroll
+                    for (int b = 0; b < W; ++b) tbit[b] = tile_offset(sp, S.reg_col[b]);
+                    auto at = [&](int j) {
+                        uint64_t o = rt;
+#pragma unroll
+                        for (int b = 0; b < W; ++b)
+                            if ((j >> b) & 1) o ^= tbit[b];
+                        return base | o;
+                    };
+                    if (last_pass) {
+#pragma unroll
+                        for (int j = 0; j < D; ++j) zacc += zterm(v[j], at(j), zmask);
+                    }
+                    if (store) {
+#pragma unroll
+                        for (int j = 0; j < D; ++j) state[at(j)] = v[j];
+                    }
+                } else {
+#pragma unroll
+                    for (int j = 0; j < D; ++j) {
+                        uint32_t o = to;
+#pragma unroll
+                        for (int b = 0; b < W; ++b)
+                            if ((j >> b) & 1) o ^= S.reg_col[b];
+                        lds[o] = v[j];
+                    }
+                }
+            } else if (last) {
                 if (last_pass) {
 #pragma unroll
                     for (int j = 0; j < D; ++j) zacc += zterm(v[j], row | goff_of(j), zmask);
@@ -130,6 +166,8 @@ __device__ void batch_tile(cpx<T> *state, cpx<T> *lds, const TileSpec &sp, int m
                 for (int j = 0; j < D; ++j) lds[pg ^ poff_of(j)] = v[j];
             }
         }
+        // waves without groups take part in the barrier above
+        if (S.perm && first == last && wave_first >= n_groups) __syncthreads();
         __syncthreads();
     }
 }

@@ -446,8 +446,9 @@ static void pack_records(PassCode &pc, bool f32) {
 }
 
 static bool is_x(const Gate &g) {
+    // by value: the adjoint's conjugates hold negative zeros
     const double x[8] = {0, 0, 1, 0, 1, 0, 0, 0};
-    return g.k == 1 && std::memcmp(g.U, x, sizeof(x)) == 0;
+    return g.k == 1 && std::equal(x, x + 8, g.U);
 }
 
 // Controls of a gate: bits outside the tile go to the record (tested once
@@ -2322,7 +2323,7 @@ static BatchProgram compile_batch(const std::vector<int> &widths,
             } else {
                 tile_layout(w, m, lmin, needed, &sp);
             }
-            PassCode pc = compile_pass(sp, ptrs, sweep_w, dtype == SV_C64);
+            PassCode pc = compile_pass(sp, ptrs, sweep_w, dtype == SV_C64, nullptr, false, true);
             if (pc.sweeps.empty()) {
                 // a circuit without gates still needs one sweep: the batch
                 // kernel synthesises |0...0> and reduces in a sweep's registers
@@ -3125,7 +3126,7 @@ int sv_adjoint_grad(sv_handle h, sv_handle lam, const sv_op *ops, int n_ops, con
         nslot[pi] = ns;
         TileSpec sp{};
         tile_layout(h->n, mmax, lmin, needed, &sp);
-        code[pi] = compile_pass(sp, ptrs, sweep_width(h->dtype), h->dtype == SV_C64, &prs);
+        code[pi] = compile_pass(sp, ptrs, sweep_width(h->dtype), h->dtype == SV_C64, &prs, false, true);
         offs[pi] = total;
         total += align256(code[pi].bytes());
     }

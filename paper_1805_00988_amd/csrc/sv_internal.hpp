@@ -195,7 +195,8 @@ constexpr int kSweepW = 4; // tile qubits held in registers per sweep (fewer for
 // depth 20 at 28 qubits complex128 has 79 sweeps instead of 95 (61.2 -> 55.4
 // ms), at 29 qubits complex64 62 instead of 74 (61.6 -> 57.8 ms), a
 // 12-qubit register 25 instead of 42.
-constexpr int kPermLane = 10; // most group-index bits of a sweep
+constexpr int kPermLane = 9; // most group-index bits of a sweep whose stores permute: one group per
+                             // thread of at most 512 threads
 struct TileSweep {
     int32_t n_gates;       // records of this sweep, stored consecutively
     int32_t qpos[kSweepW]; // ascending local positions held in registers
