@@ -242,11 +242,10 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint_tile(typename AV<T>::ty
                                                       int slot0, int n_slots, double *partials,
                                                       uint64_t n_tiles) {
     constexpr int D = 1 << W;
-    extern __shared__ char lds_raw[];
-    const uint32_t tsize = 1u << m;
     // one LDS tile, used by psi and then by lam at each exchange (half the
     // LDS of a tile per vector: more workgroups per CU)
-    cpx<T> *lt = reinterpret_cast<cpx<T> *>(lds_raw);
+    extern __shared__ char lds[];
+    const uint32_t tsize = 1u << m;
     // one row of slot sums per wave, written only by that wave's lane 0 (no
     // atomics): the workgroup's sums are then formed in a fixed order and the
     // gradient is the same bit for bit on every run
@@ -280,23 +279,13 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint_tile(typename AV<T>::ty
             const TileSweep &S = sweeps[si];
             const int ng = S.n_gates;
             const bool first = si == 0, last = si == n_sweeps - 1;
-            const uint32_t gb = group_bits<W>(S, act ? g : 0u);
-            const uint64_t row = base | tile_offset(sp, gb);
-            uint64_t gbit[W];
-#pragma unroll
-            for (int b = 0; b < W; ++b) gbit[b] = tile_offset(sp, 1u << S.qpos[b]);
-            auto goff_of = [&](int j) {
-                uint64_t o = 0;
-#pragma unroll
-                for (int b = 0; b < W; ++b)
-                    if ((j >> b) & 1) o |= gbit[b];
-                return o;
-            };
             if (first) {
+                const uint64_t row = base | group_columns(S.at_lane, g);
 #pragma unroll
                 for (int j = 0; j < D; ++j) {
-                    v[j] = act ? ps[row | goff_of(j)] : cpx<T>{T(0), T(0)};
-                    w[j] = act ? ls[row | goff_of(j)] : cpx<T>{T(0), T(0)};
+                    const uint64_t x = row | register_columns<W>(S.at_reg, j);
+                    v[j] = act ? ps[x] : cpx<T>{T(0), T(0)};
+                    w[j] = act ? ls[x] : cpx<T>{T(0), T(0)};
                 }
             }
             const char *rp = recs + S.rec_off;
@@ -305,7 +294,7 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint_tile(typename AV<T>::ty
                 rp += G.size;
                 if (is_probe(G.kind)) {
                     if ((base & G.cout) != G.cout) continue; // uniform
-                    const double mine = act ? probe_gate<T, W>(v, w, gb, G) : 0.0;
+                    const double mine = act ? probe_gate<T, W>(v, w, g, G) : 0.0;
                     const double c = wave_sum_d(mine);
                     if ((threadIdx.x & 63) == 0) slot_acc[threadIdx.x >> 6][G.b1] += c;
                 } else {
@@ -314,74 +303,34 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint_tile(typename AV<T>::ty
                     // mask repeats for lam's half
                     GateHot h = *reinterpret_cast<const GateHot *>(&G);
                     h.amask |= h.amask << D;
-                    sweep_gate_h<T, W + 1, TWOQ, false>(vw, acc_unused, gb, h, G, base);
+                    sweep_gate_h<T, W + 1, TWOQ, false>(vw, acc_unused, g, h, G, base);
                 }
             }
-            const uint32_t to = S.perm ? permuted_group(S, recs, g, base) : 0u;
-            if (last && S.perm) {
-                // other groups' places, once every group has been read
-                if (first) __syncthreads();
-                const uint64_t rt = tile_offset(sp, to);
-                uint64_t tbit[W];
-#pragma unroll
-                for (int b = 0; b < W; ++b) tbit[b] = tile_offset(sp, S.reg_col[b]);
+            if (last) {
+                // other groups' places only once every group has been read
+                if (first && S.perm) __syncthreads();
+                const uint64_t to = to_constant(S, recs, base) ^ group_columns(S.to_lane, g);
                 if (act) {
 #pragma unroll
                     for (int j = 0; j < D; ++j) {
-                        uint64_t o = rt;
-#pragma unroll
-                        for (int b = 0; b < W; ++b)
-                            if ((j >> b) & 1) o ^= tbit[b];
-                        ps[base | o] = v[j];
-                        ls[base | o] = w[j];
-                    }
-                }
-            } else if (last) {
-                if (act) {
-#pragma unroll
-                    for (int j = 0; j < D; ++j) {
-                        ps[row | goff_of(j)] = v[j];
-                        ls[row | goff_of(j)] = w[j];
+                        const uint64_t x = base | (to ^ register_columns<W>(S.to_reg, j));
+                        ps[x] = v[j];
+                        ls[x] = w[j];
                     }
                 }
             } else {
                 const TileSweep &N = sweeps[si + 1];
-                uint32_t PF[D], PN[D];
-                register_offsets<T, W>(S, PF);
-                register_offsets<T, W>(N, PN);
-                uint32_t pg = lds_phys<T>(gb);
-                if (S.perm) {
-                    pg = to;
-#pragma unroll
-                    for (int j = 0; j < D; ++j) {
-                        PF[j] = 0;
-#pragma unroll
-                        for (int b = 0; b < W; ++b)
-                            if ((j >> b) & 1) PF[j] ^= S.reg_col[b];
-                    }
-                }
-                const uint32_t pn = lds_phys<T>(group_bits<W>(N, act ? g : 0u));
+                const uint32_t pg = out_constant(S, recs, base) ^ group_columns(S.out_lane, g);
+                const uint32_t pn = group_columns(N.in_lane, g);
                 // each barrier orders one vector's writes before its reads,
                 // and its reads before the next writes to the tile
-                if (act) {
-#pragma unroll
-                    for (int j = 0; j < D; ++j) lt[pg ^ PF[j]] = v[j];
-                }
+                if (act) lds_store_group<T, W>(lds, pg, S.out_reg, v);
                 __syncthreads();
-                if (act) {
-#pragma unroll
-                    for (int j = 0; j < D; ++j) v[j] = lt[pn ^ PN[j]];
-                }
+                if (act) lds_load_group<T, W>(lds, pn, N.in_reg, v);
                 __syncthreads();
-                if (act) {
-#pragma unroll
-                    for (int j = 0; j < D; ++j) lt[pg ^ PF[j]] = w[j];
-                }
+                if (act) lds_store_group<T, W>(lds, pg, S.out_reg, w);
                 __syncthreads();
-                if (act) {
-#pragma unroll
-                    for (int j = 0; j < D; ++j) w[j] = lt[pn ^ PN[j]];
-                }
+                if (act) lds_load_group<T, W>(lds, pn, N.in_reg, w);
                 __syncthreads();
             }
         }

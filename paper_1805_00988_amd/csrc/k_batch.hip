@@ -58,7 +58,7 @@ __device__ __forceinline__ double zterm(cpx<T> a, uint64_t x, uint64_t zmask) {
 // (2^(m-W) <= kBatchThreads).  'dead' holds the qubits no earlier pass has
 // moved: amplitudes with such a bit set are zero and are not read.
 template <typename T, int W, bool TWOQ>
-__device__ void batch_tile(cpx<T> *state, cpx<T> *lds, const TileSpec &sp, int m, uint64_t base,
+__device__ void batch_tile(cpx<T> *state, char *lds, int m, uint64_t base,
                            const TileSweep *__restrict__ sweeps, int n_sweeps, const char *__restrict__ recs,
                            bool synth, bool last_pass, bool store, uint64_t dead, uint64_t zmask,
                            double &zacc) {
@@ -68,102 +68,38 @@ __device__ void batch_tile(cpx<T> *state, cpx<T> *lds, const TileSpec &sp, int m
     for (int si = 0; si < n_sweeps; ++si) {
         const TileSweep &S = sweeps[si];
         const bool first = si == 0, last = si == n_sweeps - 1;
-        uint32_t pb[W];
-        uint64_t gbit[W];
-#pragma unroll
-        for (int b = 0; b < W; ++b) {
-            pb[b] = lds_phys<T>(1u << S.qpos[b]);
-            gbit[b] = tile_offset(sp, 1u << S.qpos[b]);
-        }
-        auto goff_of = [&](int j) {
-            uint64_t o = 0;
-#pragma unroll
-            for (int b = 0; b < W; ++b)
-                if ((j >> b) & 1) o |= gbit[b];
-            return o;
-        };
-        auto poff_of = [&](int j) {
-            uint32_t o = 0;
-#pragma unroll
-            for (int b = 0; b < W; ++b)
-                if ((j >> b) & 1) o ^= pb[b];
-            return o;
-        };
         for (uint32_t g = threadIdx.x; g < n_groups; g += blockDim.x) {
-            const uint32_t gb = group_bits<W>(S, g);
-            const uint32_t pg = lds_phys<T>(gb);
-            const uint64_t row = base | tile_offset(sp, gb);
             cpx<T> v[D];
-            if (first && synth) {
-#pragma unroll
-                for (int j = 0; j < D; ++j) v[j] = cpx<T>{(row | goff_of(j)) == 0 ? T(1) : T(0), T(0)};
-            } else if (first) {
+            if (first) {
+                const uint64_t row = base | group_columns(S.at_lane, g);
 #pragma unroll
                 for (int j = 0; j < D; ++j) {
-                    const uint64_t x = row | goff_of(j);
-                    v[j] = x & dead ? cpx<T>{T(0), T(0)} : state[x];
+                    const uint64_t x = row | register_columns<W>(S.at_reg, j);
+                    if (synth) v[j] = cpx<T>{x == 0 ? T(1) : T(0), T(0)};
+                    else v[j] = x & dead ? cpx<T>{T(0), T(0)} : state[x];
                 }
             } else {
-#pragma unroll
-                for (int j = 0; j < D; ++j) v[j] = lds[pg ^ poff_of(j)];
+                lds_load_group<T, W>(lds, group_columns(S.in_lane, g), S.in_reg, v);
             }
             PhaseAcc<T, W> acc;
             acc.init();
-            const char *rp = recs + S.rec_off;
-            for (int gi = 0; gi < S.n_gates; ++gi) {
-                const TileGate &G = *reinterpret_cast<const TileGate *>(rp);
-                // advance before the gate: its inline assembly would make the
-                // compiler read the size again after it
-                rp += G.size;
-                sweep_gate_t<T, W, TWOQ>(v, acc, gb, G, base);
-            }
-            if (S.perm) {
-                // other groups' places, once every group of this sweep has
-                // been read
-                if (first == last) __syncthreads();
-                const uint32_t to = permuted_group(S, recs, g, base);
-                if (last) {
-                    const uint64_t rt = tile_offset(sp, to);
-                    uint64_t tbit[W];
-#pragma unroll
-                    for (int b = 0; b < W; ++b) tbit[b] = tile_offset(sp, S.reg_col[b]);
-                    auto at = [&](int j) {
-                        uint64_t o = rt;
-#pragma unroll
-                        for (int b = 0; b < W; ++b)
-                            if ((j >> b) & 1) o ^= tbit[b];
-                        return base | o;
-                    };
-                    if (last_pass) {
-#pragma unroll
-                        for (int j = 0; j < D; ++j) zacc += zterm(v[j], at(j), zmask);
-                    }
-                    if (store) {
-#pragma unroll
-                        for (int j = 0; j < D; ++j) state[at(j)] = v[j];
-                    }
-                } else {
-#pragma unroll
-                    for (int j = 0; j < D; ++j) {
-                        uint32_t o = to;
-#pragma unroll
-                        for (int b = 0; b < W; ++b)
-                            if ((j >> b) & 1) o ^= S.reg_col[b];
-                        lds[o] = v[j];
-                    }
-                }
-            } else if (last) {
+            run_records<T, W, TWOQ>(v, acc, g, recs + S.rec_off, S.n_gates, base);
+            // results that go to other groups' places wait until every group
+            // of this sweep has been read
+            if (S.perm && first == last) __syncthreads();
+            if (last) {
+                const uint64_t to = to_constant(S, recs, base) ^ group_columns(S.to_lane, g);
                 if (last_pass) {
 #pragma unroll
-                    for (int j = 0; j < D; ++j) zacc += zterm(v[j], row | goff_of(j), zmask);
+                    for (int j = 0; j < D; ++j)
+                        zacc += zterm(v[j], base | (to ^ register_columns<W>(S.to_reg, j)), zmask);
                 }
                 if (store) {
 #pragma unroll
-                    for (int j = 0; j < D; ++j) state[row | goff_of(j)] = v[j];
+                    for (int j = 0; j < D; ++j) state[base | (to ^ register_columns<W>(S.to_reg, j))] = v[j];
                 }
             } else {
-#pragma unroll
-                for (int j = 0; j < D; ++j) lds[pg ^ poff_of(j)] = v[j];
+                lds_store_group<T, W>(lds, out_constant(S, recs, base) ^ group_columns(S.out_lane, g), S.out_reg, v);
             }
         }
         // waves without groups take part in the barrier above
@@ -196,8 +132,7 @@ __device__ __forceinline__ double batch_sum(double x, double *s_red) {
 template <typename T, int W, bool TWOQ>
 __global__ __launch_bounds__(kBatchThreads) void k_batch(BatchArgs a, SV_BATCH_PROGRAM,
                                                          const int32_t *__restrict__ order) {
-    extern __shared__ char lds_raw[];
-    cpx<T> *lds = reinterpret_cast<cpx<T> *>(lds_raw);
+    extern __shared__ char lds[];
     __shared__ int s_idx;
     __shared__ double s_red[kBatchThreads / 64];
     for (;;) {
@@ -211,7 +146,7 @@ __global__ __launch_bounds__(kBatchThreads) void k_batch(BatchArgs a, SV_BATCH_P
         const BatchPass &p = passes[c.pass_off];
         cpx<T> *state = reinterpret_cast<cpx<T> *>(reinterpret_cast<char *>(a.states) + c.state_off);
         double zacc = 0.0;
-        batch_tile<T, W, TWOQ>(state, lds, p.sp, c.w, 0, sweeps + p.sweep_off, p.n_sweeps, recs + p.gate_off,
+        batch_tile<T, W, TWOQ>(state, lds, c.w, 0, sweeps + p.sweep_off, p.n_sweeps, recs + p.gate_off,
                                true, true, c.keep, 0, a.zmask, zacc);
         zacc = batch_sum(zacc, s_red);
         if (threadIdx.x == 0) a.out[ci] = zacc;
@@ -228,8 +163,7 @@ __global__ __launch_bounds__(kBatchThreads) void k_batch_wide(BatchArgs a, SV_BA
                                                               const int32_t *__restrict__ wide,
                                                               const BatchGroup *__restrict__ all_groups,
                                                               BatchLevel lv, int level) {
-    extern __shared__ char lds_raw[];
-    cpx<T> *lds = reinterpret_cast<cpx<T> *>(lds_raw);
+    extern __shared__ char lds[];
     __shared__ double s_red[kBatchThreads / 64];
     const BatchGroup *groups = all_groups + lv.group_off;
     for (int64_t item = blockIdx.x; item < lv.items; item += gridDim.x) {
@@ -258,7 +192,7 @@ __global__ __launch_bounds__(kBatchThreads) void k_batch_wide(BatchArgs a, SV_BA
             continue;
         }
         double zacc = 0.0;
-        batch_tile<T, W, TWOQ>(state, lds, p.sp, m, base, sweeps + p.sweep_off, p.n_sweeps,
+        batch_tile<T, W, TWOQ>(state, lds, m, base, sweeps + p.sweep_off, p.n_sweeps,
                                recs + p.gate_off, level == 0, last, !last || c.keep, dead, a.zmask, zacc);
         if (last) {
             zacc = batch_sum(zacc, s_red);

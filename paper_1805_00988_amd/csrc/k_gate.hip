@@ -455,174 +455,89 @@ int batch_tile_qubits(int dtype) { return dtype == SV_C64 ? 13 : 12; }
 // threads.
 int sweep_width(int dtype) { return dtype == SV_C64 ? 4 : 3; }
 
-__device__ __forceinline__ uint64_t tile_global(const TileSpec &sp, uint64_t base, uint32_t l) {
-    uint64_t g = base | (l & ((1u << sp.L) - 1u));
-    uint32_t hi = l >> sp.L;
-#pragma unroll
-    for (int i = 0; i < kMaxTileHigh; ++i) {
-        if (i >= sp.K) break;
-        if ((hi >> i) & 1u) g |= 1ull << sp.high[i];
-    }
-    return g;
-}
-
-// The pass's sweeps over one tile.  The first sweep reads its groups
-// straight from the state and the last writes them straight back, so the
-// tile crosses LDS only between sweeps (a pass of one sweep never touches
-// it); each sweep ends with a barrier, which also keeps the next tile's
-// first LDS writes behind this tile's last LDS reads.
+// One pass: the first sweep reads its groups straight from the state and
+// the last writes them straight back, so the tile crosses LDS only between
+// sweeps (a pass of one sweep never touches it).  One workgroup per tile and
+// one register group per thread.
 //
-// ZSKIP: a tile of zeros is left as it is (see launch_tile; one register
-// group per thread).  Each wave reports the magnitude bits of its groups in
-// the first words of the tile's LDS, which nothing else uses before the
-// first sweep stores its groups there.
+// ZSKIP: a tile of zeros is left as it is (see launch_tile).  Each wave
+// reports the magnitude bits of its groups in the first words of the tile's
+// LDS, which nothing else uses before the first sweep stores its groups
+// there.
 template <typename T, int W, bool TWOQ, bool LPH, bool ZSKIP>
-__device__ void tile_pass_direct(cpx<T> *__restrict__ state, cpx<T> *lds, const TileSpec &sp, uint64_t base,
-                                 int m, const TileSweep *__restrict__ sweeps, int n_sweeps,
-                                 const char *__restrict__ recs, uint32_t direct) {
+__global__ __launch_bounds__(kTileThreads) void k_tile(typename Vec<T>::type *vec, TileSpec sp,
+                                                       const TileSweep *__restrict__ sweeps, int n_sweeps,
+                                                       const char *__restrict__ recs) {
     constexpr int D = 1 << W;
-    const uint32_t n_groups = (1u << m) >> W;
-    using V = typename Vec<T>::type;
-    if (!(direct & kDirectFirst)) {
-        tile_load<T, kTileThreads, 8>(reinterpret_cast<const V *>(state), lds, sp, base, 1u << m);
-        __syncthreads();
-    }
+    extern __shared__ char lds[];
+    uint64_t base = (uint64_t)blockIdx.x << sp.L;
+    for (int i = 0; i < sp.K; ++i) base = insert_zero(base, sp.high[i]);
+    cpx<T> *tile = reinterpret_cast<cpx<T> *>(vec) + base;
+    const uint32_t g = threadIdx.x;
     for (int si = 0; si < n_sweeps; ++si) {
         const TileSweep &S = sweeps[si];
-        const int ng = S.n_gates;
-        const bool first = si == 0 && (direct & kDirectFirst), last = si == n_sweeps - 1 && (direct & kDirectLast);
-        // both offsets of register index j combine per-bit parts: the LDS
-        // swizzle by XOR, the global offset by OR (disjoint bits)
-        uint32_t pb[W];
-        uint64_t gbit[W];
+        const bool first = si == 0, last = si == n_sweeps - 1;
+        cpx<T> v[D];
+        if (first) {
+            const cpx<T> *row = tile + group_columns(S.at_lane, g);
 #pragma unroll
-        for (int b = 0; b < W; ++b) {
-            pb[b] = lds_phys<T>(1u << S.qpos[b]);
-            gbit[b] = tile_offset(sp, 1u << S.qpos[b]);
-        }
-        auto goff_of = [&](int j) {
-            uint64_t o = 0;
+            for (int j = 0; j < D; ++j) v[j] = row[register_columns<W>(S.at_reg, j)];
+            if constexpr (ZSKIP) {
+                uint32_t bits = 0;
 #pragma unroll
-            for (int b = 0; b < W; ++b)
-                if ((j >> b) & 1) o |= gbit[b];
-            return o;
-        };
-        auto poff_of = [&](int j) {
-            uint32_t o = 0;
-#pragma unroll
-            for (int b = 0; b < W; ++b)
-                if ((j >> b) & 1) o ^= pb[b];
-            return o;
-        };
-        for (uint32_t g = threadIdx.x; g < n_groups; g += blockDim.x) {
-            const uint32_t gb = group_bits<W>(S, g);
-            const uint32_t pg = lds_phys<T>(gb);
-            cpx<T> *row = state + (base | tile_offset(sp, gb));
-            cpx<T> v[D];
-            if (first) {
-#pragma unroll
-                for (int j = 0; j < D; ++j) v[j] = row[goff_of(j)];
-                if constexpr (ZSKIP) {
-                    uint32_t bits = 0;
-#pragma unroll
-                    for (int j = 0; j < D; ++j) bits |= magnitude_bits(v[j].re) | magnitude_bits(v[j].im);
-                    volatile uint32_t *seen = reinterpret_cast<volatile uint32_t *>(lds);
-                    const uint32_t wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
-                    const uint32_t any = wave_zero(bits) ? 0u : 1u;
-                    if ((threadIdx.x & 63u) == 0u) seen[wave] = any;
-                    __syncthreads();
-                    uint32_t tile_any = 0;
-                    for (uint32_t w = 0; w < n_waves; ++w) tile_any |= seen[w];
-                    __syncthreads(); // the words are read before the tile is written over them
-                    if (__builtin_amdgcn_readfirstlane(tile_any) == 0u) return;
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < D; ++j) v[j] = lds[pg ^ poff_of(j)];
+                for (int j = 0; j < D; ++j) bits |= magnitude_bits(v[j].re) | magnitude_bits(v[j].im);
+                volatile uint32_t *seen = reinterpret_cast<volatile uint32_t *>(lds);
+                const uint32_t wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
+                const uint32_t any = wave_zero(bits) ? 0u : 1u;
+                if ((threadIdx.x & 63u) == 0u) seen[wave] = any;
+                __syncthreads();
+                uint32_t tile_any = 0;
+                for (uint32_t w = 0; w < n_waves; ++w) tile_any |= seen[w];
+                __syncthreads(); // the words are read before the tile is written over them
+                if (__builtin_amdgcn_readfirstlane(tile_any) == 0u) return;
             }
-            PhaseAcc<T, W> acc;
-            acc.init();
-            run_records<T, W, TWOQ, LPH>(v, acc, gb, recs + S.rec_off, ng, base);
+        } else {
+            lds_load_group<T, W>(lds, group_columns(S.in_lane, g), S.in_reg, v);
+        }
+        PhaseAcc<T, W> acc;
+        acc.init();
+        run_records<T, W, TWOQ, LPH>(v, acc, g, recs + S.rec_off, S.n_gates, base);
+        // results that go to other groups' places wait until every group of
+        // this sweep has been read (after a first sweep's loads from the
+        // state nothing reads the LDS tile)
+        if (S.perm && first == last) __syncthreads();
+        if (last) {
             if (S.perm) {
-                // the results go to other groups' places, once every group
-                // of this sweep has been read (after a first sweep's loads
-                // from the state nothing reads the LDS tile)
-                if (first == last) __syncthreads();
-                const uint32_t to = permuted_group(S, recs, g, base);
-                if (last) {
-                    const uint64_t rt = tile_offset(sp, to);
-                    uint64_t tbit[W];
+                const uint64_t to = to_constant(S, recs, base) ^ group_columns(S.to_lane, g);
 #pragma unroll
-                    for (int b = 0; b < W; ++b) tbit[b] = tile_offset(sp, S.reg_col[b]);
-#pragma unroll
-                    for (int j = 0; j < D; ++j) {
-                        uint64_t o = rt;
-#pragma unroll
-                        for (int b = 0; b < W; ++b)
-                            if ((j >> b) & 1) o ^= tbit[b];
-                        state[base | o] = v[j];
-                    }
-                } else {
-#pragma unroll
-                    for (int j = 0; j < D; ++j) {
-                        uint32_t o = to;
-#pragma unroll
-                        for (int b = 0; b < W; ++b)
-                            if ((j >> b) & 1) o ^= S.reg_col[b];
-                        lds[o] = v[j];
-                    }
-                }
-            } else if (last) {
-#pragma unroll
-                for (int j = 0; j < D; ++j) row[goff_of(j)] = v[j];
+                for (int j = 0; j < D; ++j) tile[to ^ register_columns<W>(S.to_reg, j)] = v[j];
             } else {
+                cpx<T> *row = tile + group_columns(S.to_lane, g);
 #pragma unroll
-                for (int j = 0; j < D; ++j) lds[pg ^ poff_of(j)] = v[j];
+                for (int j = 0; j < D; ++j) row[register_columns<W>(S.to_reg, j)] = v[j];
             }
+        } else {
+            lds_store_group<T, W>(lds, out_constant(S, recs, base) ^ group_columns(S.out_lane, g), S.out_reg, v);
+            __syncthreads();
         }
-        __syncthreads();
-    }
-    if (!(direct & kDirectLast)) {
-        tile_store<T, kTileThreads, 8>(reinterpret_cast<V *>(state), lds, sp, base, 1u << m);
-        __syncthreads();
-    }
-}
-
-template <typename T, int W, bool TWOQ, bool LPH, bool ZSKIP>
-__global__ __launch_bounds__(kTileThreads) void k_tile(typename Vec<T>::type *v, TileSpec sp, int m,
-                                                       const TileSweep *__restrict__ sweeps, int n_sweeps,
-                                                       const char *__restrict__ recs,
-                                                       uint64_t n_tiles, uint32_t direct) {
-    extern __shared__ char lds_raw[];
-    cpx<T> *lds = reinterpret_cast<cpx<T> *>(lds_raw);
-    cpx<T> *state = reinterpret_cast<cpx<T> *>(v);
-    // 32-bit tile counter (at most 2^27 tiles): the loop test stays on the
-    // scalar unit
-    const uint32_t nt = (uint32_t)n_tiles;
-    for (uint32_t tile = blockIdx.x; tile < nt; tile += gridDim.x) {
-        uint64_t base = (uint64_t)tile << sp.L;
-        for (int i = 0; i < sp.K; ++i) base = insert_zero(base, sp.high[i]);
-        tile_pass_direct<T, W, TWOQ, LPH, ZSKIP>(state, lds, sp, base, m, sweeps, n_sweeps, recs, direct);
     }
 }
 
 template <typename T, int W, bool TWOQ, bool LPH = std::is_same<T, double>::value>
 static void launch_tile_t(typename Vec<T>::type *v, const TileSpec &spec, int m, const TileSweep *sw,
-                          int n_sweeps, const char *g, uint64_t n_tiles, uint32_t direct, size_t lds,
+                          int n_sweeps, const char *g, uint64_t n_tiles, bool skip_zero, size_t lds,
                           hipStream_t s) {
     // one workgroup per tile (measured faster than a capped grid looping
     // over tiles), and one thread per register group
-    const unsigned grid = (unsigned)std::min<uint64_t>(n_tiles, 1u << 30);
-    const unsigned threads = (unsigned)std::max(64, std::min(kTileThreads, (1 << m) >> W));
+    const unsigned threads = 1u << (m - W);
     auto launch = [&](auto kernel) {
         (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        kernel<<<grid, threads, lds, s>>>(v, spec, m, sw, n_sweeps, g, n_tiles, direct);
+        kernel<<<(unsigned)n_tiles, threads, lds, s>>>(v, spec, sw, n_sweeps, g);
     };
-    // the zero test needs every thread to hold one group of a direct first
-    // sweep; narrower tiles are states of one tile
+    // tiles of less than a wave are states of one tile
     constexpr bool FULL = W == (std::is_same<T, float>::value ? 4 : 3);
     if constexpr (FULL) {
-        if ((direct & kSkipZero) && (direct & kDirectFirst) && ((1u << m) >> W) == threads) {
+        if (skip_zero && threads >= 64) {
             launch(k_tile<T, W, TWOQ, LPH, true>);
             return;
         }
@@ -630,15 +545,7 @@ static void launch_tile_t(typename Vec<T>::type *v, const TileSpec &spec, int m,
     launch(k_tile<T, W, TWOQ, LPH, false>);
 }
 
-template <int W>
-static bool tile_staging_ok(int m, uint32_t direct) {
-    // staging the whole tile through LDS (a pass without direct first and
-    // last sweeps) moves it with kTileThreads threads
-    const int threads = std::max(64, std::min(kTileThreads, (1 << m) >> W));
-    return (direct & (kDirectFirst | kDirectLast)) == (kDirectFirst | kDirectLast) || threads == kTileThreads;
-}
-
-// kSkipZero: the pass may leave a tile that holds only zeros as it is.  A
+// skip_zero: the pass may leave a tile that holds only zeros as it is.  A
 // register starts as a basis state and spreads over the qubits of one tile
 // after the other: until every qubit has been acted on, most tiles hold
 // zeros, and zeros stay zeros under any gate.  Such a tile costs its read.
@@ -649,36 +556,37 @@ static bool tile_staging_ok(int m, uint32_t direct) {
 // host sets the flag only while some qubit outside the tile has not been
 // acted on since the register was set to a basis state (sv_state::moved).
 hipError_t launch_tile(void *amps, int n, int dtype, const TileSpec &spec, const TileSweep *dev_sweeps,
-                       int n_sweeps, const char *dev_gates, bool two_qubit, bool lane_phases, uint32_t direct,
+                       int n_sweeps, const char *dev_gates, bool two_qubit, bool lane_phases, bool skip_zero,
                        hipStream_t s) {
     const int m = spec.L + spec.K;
     const int vbits = dtype == SV_C64 ? 1 : 0;
-    if (m > n || m > tile_launch_qubits(dtype) || spec.L < vbits || spec.K > kMaxTileHigh || m < 1)
+    if (m > n || m > tile_launch_qubits(dtype) || spec.L < vbits || spec.K > kMaxTileHigh || m < 1 ||
+        n - m > 30 || n_sweeps < 1)
         return hipErrorInvalidValue;
     const uint64_t n_tiles = 1ull << (n - m);
     const size_t lds = (size_t)(1u << m) * (dtype == SV_C64 ? 8 : 16);
     const int W = std::min(m, sweep_width(dtype));
+    if ((1 << (m - W)) > kTileThreads) return hipErrorInvalidValue; // one group per thread
     // complex64 lane-bit phase lists: only the full-width instances hold
     // them (the complex128 instances always do)
     if (lane_phases && dtype == SV_C64) {
-        if (W != sweep_width(SV_C64) || !tile_staging_ok<4>(m, direct)) return hipErrorInvalidValue;
+        if (W != sweep_width(SV_C64)) return hipErrorInvalidValue;
         if (two_qubit)
             launch_tile_t<float, 4, true, true>((float4 *)amps, spec, m, dev_sweeps, n_sweeps, dev_gates, n_tiles,
-                                                direct, lds, s);
+                                                skip_zero, lds, s);
         else
             launch_tile_t<float, 4, false, true>((float4 *)amps, spec, m, dev_sweeps, n_sweeps, dev_gates,
-                                                 n_tiles, direct, lds, s);
+                                                 n_tiles, skip_zero, lds, s);
         return hipGetLastError();
     }
 #define SV_TILE_CASE(WW, Q)                                                                        \
     if (W == WW && two_qubit == Q) {                                                               \
-        if (!tile_staging_ok<WW>(m, direct)) return hipErrorInvalidValue;                          \
         if (dtype == SV_C64)                                                                       \
             launch_tile_t<float, WW, Q>((float4 *)amps, spec, m, dev_sweeps, n_sweeps, dev_gates,  \
-                                        n_tiles, direct, lds, s);                                  \
+                                        n_tiles, skip_zero, lds, s);                                  \
         else                                                                                       \
             launch_tile_t<double, WW, Q>((double2 *)amps, spec, m, dev_sweeps, n_sweeps,           \
-                                         dev_gates, n_tiles, direct, lds, s);                      \
+                                         dev_gates, n_tiles, skip_zero, lds, s);                      \
         return hipGetLastError();                                                                  \
     }
     SV_TILE_CASE(4, false)

@@ -331,9 +331,12 @@ static uint64_t tile_qubits(const TileSpec &sp) {
 }
 
 // Some qubit outside the tile is as the basis state left it: most of the
-// pass's tiles are likely to hold zeros.
+// pass's tiles are likely to hold zeros.  Up to 1024 tiles the chip runs all
+// at once, and skipping some leaves the others' time: there the test only
+// adds its barrier (the QFT's first pass at 16 qubits complex128, 46 us with
+// it and 41 without).
 static bool untouched_outside(const sv_state *h, const TileSpec &sp) {
-    return (((1ull << h->n) - 1ull) & ~tile_qubits(sp) & ~h->moved) != 0;
+    return h->n - sp.L - sp.K > 10 && (((1ull << h->n) - 1ull) & ~tile_qubits(sp) & ~h->moved) != 0;
 }
 
 // X on local bit t where the tile holds the index bits 'cout' and, if c >= 0,
@@ -351,10 +354,10 @@ struct PassCode {
     double flops_per_amp = 0.0; // algorithmic flops of the pass per state amplitude
     bool two_qubit = false;     // holds SK_2Q records
     bool lane_phases = false;   // holds SK_LPH records
-    uint32_t direct = 0;        // kDirectFirst / kDirectLast (launch_tile)
     uint64_t moves = 0;         // targets of its gates that are not diagonal
     bool finite = true;         // every matrix entry is, in the state's precision
     std::vector<TileSweep> sweeps;
+    std::vector<std::vector<int>> qsets;      // per sweep: its register positions, ascending
     std::vector<std::vector<PermGate>> perms; // per sweep: the X gates its stores apply
     std::vector<TileGate> gates; // records in sweep order (host form)
     std::vector<std::vector<char>> tables; // SK_PTAB payloads (descriptors and tables)
@@ -374,11 +377,68 @@ static size_t record_payload(const TileGate &r, bool f32) {
     }
 }
 
+static uint64_t tile_global_offset(const TileSpec &sp, uint32_t l);
+
+// Address columns of a sweep (TileSweep), its results permuted by the
+// sweep's X gates; the conditional constants follow the records.
+static void sweep_addresses(PassCode &pc, size_t si, int amp_bytes) {
+    TileSweep &S = pc.sweeps[si];
+    uint32_t regs = 0;
+    for (int b : pc.qsets[si]) regs |= 1u << b;
+    std::vector<uint32_t> col(pc.m); // images of the tile index's bits
+    for (int b = 0; b < pc.m; ++b) col[b] = 1u << b;
+    uint32_t cst = 0;
+    std::vector<std::pair<uint64_t, uint32_t>> conds;
+    if (si < pc.perms.size())
+        for (const PermGate &p : pc.perms[si]) {
+            const uint32_t tb = 1u << p.t;
+            S.perm = 1;
+            if (p.c >= 0) {
+                for (uint32_t &x : col)
+                    if ((x >> p.c) & 1u) x ^= tb;
+                if ((cst >> p.c) & 1u) cst ^= tb;
+                for (auto &q : conds)
+                    if ((q.second >> p.c) & 1u) q.second ^= tb;
+            } else if (p.cout == 0) {
+                cst ^= tb;
+            } else {
+                conds.push_back({p.cout, tb});
+            }
+        }
+    auto lds = [&](uint32_t l) { return lds_swizzle(l, amp_bytes) * (uint32_t)amp_bytes; };
+    auto idx = [&](uint32_t l) { return tile_global_offset(pc.sp, l); };
+    for (int b = 0, i = 0, r = 0; b < pc.m; ++b) {
+        if ((regs >> b) & 1u) {
+            S.in_reg[r] = lds(1u << b);
+            S.out_reg[r] = lds(col[b]);
+            S.at_reg[r] = idx(1u << b);
+            S.to_reg[r++] = idx(col[b]);
+        } else {
+            S.in_lane[i] = lds(1u << b);
+            S.out_lane[i] = lds(col[b]);
+            S.at_lane[i] = idx(1u << b);
+            S.to_lane[i++] = idx(col[b]);
+        }
+    }
+    S.out_cst = lds(cst);
+    S.to_cst = idx(cst);
+    S.n_cond = (int32_t)conds.size();
+    S.cond_off = (int32_t)pc.recs.size();
+    for (const auto &q : conds) {
+        const PermCond e{q.first, idx(q.second), lds(q.second), 0u};
+        const char *src = reinterpret_cast<const char *>(&e);
+        pc.recs.insert(pc.recs.end(), src, src + sizeof(e));
+    }
+}
+
 // Pack the records (each cut after its entries, 8-byte aligned sizes) and
 // point every sweep at its first record.
 static void pack_records(PassCode &pc, bool f32) {
     pc.recs.clear();
-    size_t gi = 0;
+    size_t gi = 0, bytes = kRecordTail;
+    for (const TileGate &r : pc.gates) bytes += kRecordHead + record_payload(r, f32) + 8;
+    for (const auto &t : pc.tables) bytes += t.size();
+    pc.recs.reserve(bytes + 512);
     for (TileSweep &S : pc.sweeps) {
         S.rec_off = (int32_t)pc.recs.size();
         for (int k = 0; k < S.n_gates; ++k, ++gi) {
@@ -399,49 +459,8 @@ static void pack_records(PassCode &pc, bool f32) {
             pc.recs.insert(pc.recs.end(), src, src + sz);
         }
     }
-    // the sweeps' permutations: images of the group-index bits, the register
-    // bits and 0, and the conditional constants
-    for (size_t si = 0; si < pc.sweeps.size(); ++si) {
-        TileSweep &S = pc.sweeps[si];
-        S.perm = si < pc.perms.size() && !pc.perms[si].empty();
-        if (!S.perm) continue;
-        const int W = std::min(pc.m, kSweepW), ab = f32 ? 8 : 16;
-        uint32_t regs = 0;
-        int n_reg = 0;
-        for (int b = 0; b < W && (b == 0 || S.qpos[b] > S.qpos[b - 1]); ++b, ++n_reg) regs |= 1u << S.qpos[b];
-        std::vector<uint32_t> col(pc.m); // images of the tile index's bits
-        for (int b = 0; b < pc.m; ++b) col[b] = 1u << b;
-        uint32_t cst = 0;
-        std::vector<PermCond> conds;
-        for (const PermGate &p : pc.perms[si]) {
-            const uint32_t tb = 1u << p.t;
-            if (p.c >= 0) {
-                for (uint32_t &x : col)
-                    if ((x >> p.c) & 1u) x ^= tb;
-                if ((cst >> p.c) & 1u) cst ^= tb;
-                for (PermCond &q : conds)
-                    if ((q.vec >> p.c) & 1u) q.vec ^= tb;
-            } else if (p.cout == 0) {
-                cst ^= tb;
-            } else {
-                conds.push_back({p.cout, tb, 0u});
-            }
-        }
-        const bool last = si + 1 == pc.sweeps.size();
-        auto out = [&](uint32_t l) { return last ? l : lds_swizzle(l, ab); };
-        for (int b = 0, i = 0, r = 0; b < pc.m; ++b) {
-            if ((regs >> b) & 1u) S.reg_col[r++] = out(col[b]);
-            else S.lane_col[i++] = out(col[b]);
-        }
-        S.cst = out(cst);
-        S.n_cond = (int32_t)conds.size();
-        S.cond_off = (int32_t)pc.recs.size();
-        for (PermCond &q : conds) {
-            q.vec = out(q.vec);
-            const char *src = reinterpret_cast<const char *>(&q);
-            pc.recs.insert(pc.recs.end(), src, src + sizeof(q));
-        }
-    }
+    for (size_t si = 0; si < pc.sweeps.size(); ++si)
+        sweep_addresses(pc, si, f32 ? 8 : 16);
     pc.recs.resize(pc.recs.size() + kRecordTail, 0);
 }
 
@@ -453,13 +472,13 @@ static bool is_x(const Gate &g) {
 
 // Controls of a gate: bits outside the tile go to the record (tested once
 // per tile on its base index); the local bits inside the tile are returned.
-static uint32_t encode_controls(const TileSpec &sp, uint64_t ctrl, TileGate *r) {
+static uint32_t encode_controls(const TileSpec &sp, uint64_t ctrl, uint64_t *cout) {
     uint32_t cin = 0;
     for (uint64_t c = ctrl; c; c &= c - 1) {
         const int b = __builtin_ctzll(c);
         const int lb = local_bit(sp, b);
         if (lb >= 0) cin |= 1u << lb;
-        else r->cout |= 1ull << b;
+        else *cout |= 1ull << b;
     }
     return cin;
 }
@@ -517,7 +536,7 @@ static TileGate encode_sweep_gate(const TileSpec &sp, const std::vector<int> &qs
                                   bool f32) {
     TileGate r;
     std::memset(&r, 0, sizeof(r));
-    const uint32_t cin = encode_controls(sp, g.ctrl, &r);
+    const uint32_t cin = encode_controls(sp, g.ctrl, &r.cout);
     auto pos = [&](int q) {
         const int lb = local_bit(sp, q);
         for (size_t j = 0; j < qset.size(); ++j)
@@ -666,7 +685,7 @@ static TileGate encode_probe(const TileSpec &sp, const std::vector<int> &qset, c
                              bool f32) {
     TileGate r;
     std::memset(&r, 0, sizeof(r));
-    const uint32_t cin = encode_controls(sp, g.ctrl, &r);
+    const uint32_t cin = encode_controls(sp, g.ctrl, &r.cout);
     // the probes of RX, RY, RZ and U1 have their own kinds (no matrix)
     auto is_m = [&](const double *m) { return std::memcmp(pr.M, m, sizeof(pr.M)) == 0; };
     const double mx[8] = {0, 0, 1, 0, 1, 0, 0, 0}, my[8] = {0, 0, 0, -1, 0, 1, 0, 0};
@@ -695,6 +714,7 @@ static PassCode compile_pass(const TileSpec &sp, const std::vector<const Gate *>
     PassCode pc;
     pc.sp = sp;
     pc.m = sp.L + sp.K;
+    pc.gates.reserve(gs.size() + 8);
     const int W = std::min(pc.m, sweep_w);
     // stores can permute where every thread of whole waves holds one group
     const bool perms = store_perms && W == sweep_w && pc.m - W >= 6 && pc.m - W <= kPermLane;
@@ -725,9 +745,9 @@ static PassCode compile_pass(const TileSpec &sp, const std::vector<const Gate *>
                 while (b < cur.size()) {
                     const Gate &g = *gs[cur[b]];
                     if (!is_diag1(g) || !(is_one(g.U) || outside(g))) break;
-                    TileGate tmp{};
+                    uint64_t cout = 0;
                     const int lt = local_bit(sp, g.t[0]);
-                    const uint32_t cond = encode_controls(sp, g.ctrl, &tmp) | (lt >= 0 ? 1u << lt : 0u);
+                    const uint32_t cond = encode_controls(sp, g.ctrl, &cout) | (lt >= 0 ? 1u << lt : 0u);
                     const uint32_t reg = cond & fall;
                     if (__builtin_popcount(reg) > 1) break;
                     int s = W;
@@ -889,9 +909,9 @@ static PassCode compile_pass(const TileSpec &sp, const std::vector<const Gate *>
             const size_t i = cur[ci];
             if (slot[ci] >= 0) {
                 const Gate &g = *gs[i];
-                TileGate r{};
+                uint64_t cout = 0;
                 const int lt = local_bit(sp, g.t[0]);
-                const uint32_t cond = encode_controls(sp, g.ctrl, &r) | (lt >= 0 ? 1u << lt : 0u);
+                const uint32_t cond = encode_controls(sp, g.ctrl, &cout) | (lt >= 0 ? 1u << lt : 0u);
                 const std::pair<int, uint32_t> key{slot[ci], cond & ~fall};
                 auto it = std::find_if(groups.begin(), groups.end(), [&](const auto &x) { return x.first == key; });
                 if (it == groups.end()) {
@@ -899,14 +919,14 @@ static PassCode compile_pass(const TileSpec &sp, const std::vector<const Gate *>
                     it = groups.end() - 1;
                 }
                 if (lt >= 0) {
-                    it->second.push_back({r.cout, {g.U[6], g.U[7]}});
+                    it->second.push_back({cout, {g.U[6], g.U[7]}});
                 } else {
                     // target outside the tile: diag(d0, d1) = d0 on the
                     // condition, times d1 / d0 where the target is 1
                     const std::complex<double> d0{g.U[0], g.U[1]}, d1{g.U[6], g.U[7]};
-                    if (!is_one(g.U)) it->second.push_back({r.cout, {d0.real(), d0.imag()}});
+                    if (!is_one(g.U)) it->second.push_back({cout, {d0.real(), d0.imag()}});
                     const std::complex<double> q = is_one(g.U) ? d1 : d1 / d0;
-                    it->second.push_back({r.cout | (1ull << g.t[0]), {q.real(), q.imag()}});
+                    it->second.push_back({cout | (1ull << g.t[0]), {q.real(), q.imag()}});
                 }
                 pending |= 1u << slot[ci];
                 pc.flops_per_amp += gate_flops_per_amp(g);
@@ -925,8 +945,28 @@ static PassCode compile_pass(const TileSpec &sp, const std::vector<const Gate *>
             pc.flops_per_amp += (probes ? 2.0 : 1.0) * gate_flops_per_amp(*gs[i]);
         }
         flush();
-        for (int j = 0; j < kSweepW; ++j) sw.qpos[j] = j < W ? qset[j] : 0;
+        // tile positions outside the registers -> bits of the group index
+        auto group_bit = [&](int pos) { return pos - __builtin_popcount(fall & ((1u << pos) - 1u)); };
+        auto group_mask = [&](uint32_t mask) {
+            uint32_t r = 0;
+            for (; mask; mask &= mask - 1) r |= 1u << group_bit(__builtin_ctz(mask));
+            return r;
+        };
+        for (size_t k = pc.gates.size() - (size_t)sw.n_gates; k < pc.gates.size(); ++k) {
+            TileGate &r = pc.gates[k];
+            r.lane = group_mask(r.lane);
+            if (r.kind == SK_DIAG) r.b0 = group_bit(r.b0);
+            if (r.kind == SK_LPH)
+                for (int e = 0; e < r.b1; ++e) {
+                    uint64_t lm;
+                    char *at = reinterpret_cast<char *>(r.m) + (size_t)e * entry_bytes;
+                    std::memcpy(&lm, at, 8);
+                    lm = group_mask((uint32_t)lm);
+                    std::memcpy(at, &lm, 8);
+                }
+        }
         pc.sweeps.push_back(sw);
+        pc.qsets.push_back(qset);
         cur.clear();
         qset.clear();
     };
@@ -951,10 +991,10 @@ static PassCode compile_pass(const TileSpec &sp, const std::vector<const Gate *>
     std::vector<PermGate> perm(gs.size(), PermGate{-1, -1, 0}); // t < 0: none
     for (size_t i = 0; i < gs.size() && perms; ++i) {
         if (!is_x(*gs[i])) continue;
-        TileGate tmp{};
-        const uint32_t cin = encode_controls(sp, gs[i]->ctrl, &tmp);
-        if (__builtin_popcount(cin) > 1 || (cin && tmp.cout)) continue;
-        perm[i] = {local_bit(sp, gs[i]->t[0]), cin ? __builtin_ctz(cin) : -1, tmp.cout};
+        uint64_t cout = 0;
+        const uint32_t cin = encode_controls(sp, gs[i]->ctrl, &cout);
+        if (__builtin_popcount(cin) > 1 || (cin && cout)) continue;
+        perm[i] = {local_bit(sp, gs[i]->t[0]), cin ? __builtin_ctz(cin) : -1, cout};
     }
     while (first < gs.size()) {
         uint64_t blocked = 0; // qubits of the gates left behind by this sweep
@@ -1058,10 +1098,6 @@ static PassCode compile_pass(const TileSpec &sp, const std::vector<const Gate *>
         for (int i = 0; i < 2 << (2 * g->k); ++i) pc.finite = pc.finite && std::fabs(g->U[i]) <= (f32 ? FLT_MAX : DBL_MAX);
     }
     pack_records(pc, f32);
-    // the first and last sweeps read / write the state directly (measured
-    // faster than staging the tile through LDS for every register layout,
-    // most when the register positions leave the low tile bits to the lanes)
-    pc.direct = kDirectFirst | kDirectLast;
     return pc;
 }
 
@@ -1078,7 +1114,7 @@ static int launch_pass(sv_state *h, const PassCode &pc, size_t off) {
     Timed tm(h, K_TILE, 2.0 * state_bytes(h), pc.flops_per_amp * (double)(1ull << h->n));
     const bool zeros = pc.finite && untouched_outside(h, pc.sp);
     SV_HIP(launch_tile(h->amps, h->n, h->dtype, pc.sp, sw, (int)pc.sweeps.size(), gt, pc.two_qubit, pc.lane_phases,
-                       pc.direct | (zeros ? kSkipZero : 0u), h->stream));
+                       zeros, h->stream));
     h->moved |= pc.moves;
     return SV_OK;
 }
@@ -1384,11 +1420,19 @@ static int run_gates(sv_state *h, const std::vector<Gate> &gs, int mode) {
             for (int gi : p.gates) needed |= tile_need(gs[gi]);
             TileSpec sp{};
             tile_layout(h->n, mmax, lmin, needed, &sp);
-            std::vector<Gate> local;
+            const uint64_t S = tile_qubits(sp);
+            std::vector<Gate> local; // retargeted copies
             local.reserve(p.gates.size());
-            for (int gi : p.gates) local.push_back(retarget_phase(gs[gi], tile_qubits(sp)));
             std::vector<const Gate *> ptrs;
-            for (const Gate &g : local) ptrs.push_back(&g);
+            ptrs.reserve(p.gates.size());
+            for (int gi : p.gates) {
+                const Gate *g = &gs[gi];
+                if (!((S >> g->t[0]) & 1ull)) {
+                    local.push_back(retarget_phase(*g, S));
+                    g = &local.back();
+                }
+                ptrs.push_back(g);
+            }
             r.code = compile_pass(sp, ptrs, sweep_width(h->dtype), h->dtype == SV_C64, nullptr, true, true);
         }
         ready.push_back(std::move(r));
@@ -2327,11 +2371,11 @@ static BatchProgram compile_batch(const std::vector<int> &widths,
             if (pc.sweeps.empty()) {
                 // a circuit without gates still needs one sweep: the batch
                 // kernel synthesises |0...0> and reduces in a sweep's registers
-                TileSweep sw{};
                 const int W = std::min(pc.m, sweep_w);
-                for (int b = 0; b < W; ++b) sw.qpos[b] = pc.m - W + b;
-                sw.rec_off = 0;
-                pc.sweeps.push_back(sw);
+                pc.sweeps.push_back(TileSweep{});
+                pc.qsets.push_back({});
+                for (int b = 0; b < W; ++b) pc.qsets[0].push_back(pc.m - W + b);
+                sweep_addresses(pc, 0, dtype == SV_C64 ? 8 : 16);
             }
             BatchPass q{};
             q.sp = sp;

@@ -116,7 +116,7 @@ __device__ __forceinline__ uint64_t expand(const Enum &e, uint64_t i) {
 enum SweepKind : int32_t {
     SK_GEN = 1,   // general 2x2 on sweep position b0
     SK_REAL = 2,  // real 2x2 (m[0], m[2], m[4], m[6] hold the entries)
-    SK_DIAG = 3,  // diag(d0, d1) on tile bit b0 outside the registers; m: d0, d1
+    SK_DIAG = 3,  // diag(d0, d1) on group index bit b0; m: d0, d1
     SK_SWAP = 4,  // X: exchange the pair (per-lane controls: complex64 only)
     SK_2Q = 5,    // 4x4 on sweep positions b0 < b1 (bit 0 of the matrix index <-> b0)
     SK_PARAM = 6, // adjoint sweep: add Im<lam|M|psi> for M (entries 0-3) on position b0
@@ -175,7 +175,7 @@ constexpr int kPtabDesc = 16 * kPtabWindows; // descriptor bytes after the recor
 struct TileGate {
     int32_t kind;
     int32_t b0, b1;
-    uint32_t lane;     // control bits on tile positions outside the registers
+    uint32_t lane;     // control bits outside the registers (bits of the group index)
     uint32_t amask;    // register indices updated (see above)
     int32_t size;      // bytes of the packed record
     uint64_t cout;     // control bits outside the tile (global positions)
@@ -197,23 +197,36 @@ constexpr int kSweepW = 4; // tile qubits held in registers per sweep (fewer for
 // 12-qubit register 25 instead of 42.
 constexpr int kPermLane = 9; // most group-index bits of a sweep whose stores permute: one group per
                              // thread of at most 512 threads
+// A sweep's register group g holds the amplitudes that differ in the
+// sweep's register positions; its index bits are the other tile positions in
+// ascending order, and a thread's group is its own index.  Controls and
+// diagonal targets outside the registers are kept as bits of g.  Addresses
+// are linear over XOR in g and the register index, so the host lays them
+// out as one column per bit, as LDS byte offsets (swizzled) and as
+// index offsets from the tile's first amplitude: where the group is read
+// ('in', 'at') and where its results go ('out', 'to'; they differ where the
+// stores permute).  The kernels used to derive them per sweep from the tile
+// layout and the register positions: of the 1840 vector instructions of a
+// wave in a pass at 28 qubits complex128, 970 were such work and the reloads
+// of scalars it displaced.
+constexpr int kGroupBits = 10;
 struct TileSweep {
     int32_t n_gates;       // records of this sweep, stored consecutively
-    int32_t qpos[kSweepW]; // ascending local positions held in registers
     int32_t rec_off;       // byte offset of its first record in the pass's stream
-    int32_t perm;          // the results are stored permuted
+    int32_t perm;          // the results go to other groups' places
     int32_t n_cond;        // conditional constants (PermCond) in the stream at cond_off
     int32_t cond_off;
-    // images of the group index's bits, the register positions and 0 under
-    // the permutation: tile indices on the pass's last sweep, their LDS
-    // swizzles on the others (both linear)
-    uint32_t cst;
-    uint32_t lane_col[kPermLane];
-    uint32_t reg_col[kSweepW];
+    uint32_t out_cst;      // image of 0
+    uint32_t in_lane[kGroupBits], in_reg[kSweepW];
+    uint32_t out_lane[kGroupBits], out_reg[kSweepW];
+    uint64_t at_lane[kGroupBits], at_reg[kSweepW];
+    uint64_t to_lane[kGroupBits], to_reg[kSweepW];
+    uint64_t to_cst;
 };
 struct PermCond {
     uint64_t cond; // index bits outside the tile
-    uint32_t vec;  // constant for the tiles that hold them all
+    uint64_t to;   // constants for the tiles that hold them all
+    uint32_t out;
     uint32_t pad;
 };
 
@@ -251,16 +264,14 @@ hipError_t launch_gate2(void *amps, int n, int dtype, int t0, int t1, uint64_t c
 hipError_t launch_scale(void *amps, int n, int dtype, uint64_t set_mask, const double *factor,
                         hipStream_t s);
 // two_qubit: the pass holds SK_2Q records (selects the kernel instance with that
-// path).  direct: kDirectFirst / kDirectLast let the first sweep read its
-// register groups straight from the state / the last sweep write them straight
-// back instead of staging the tile through LDS (worth it when the sweep's
-// register positions leave the lowest tile bits to the lanes, so that a
-// wave's accesses stay contiguous).
-// kSkipZero: test the tile for zeros after the first sweep's loads.
-constexpr uint32_t kDirectFirst = 1, kDirectLast = 2, kSkipZero = 4;
+// path).  skip_zero: test each tile for zeros.
 hipError_t launch_tile(void *amps, int n, int dtype, const TileSpec &spec, const TileSweep *dev_sweeps,
-                       int n_sweeps, const char *dev_recs, bool two_qubit, bool lane_phases, uint32_t direct,
+                       int n_sweeps, const char *dev_recs, bool two_qubit, bool lane_phases, bool skip_zero,
                        hipStream_t s);
+// launch_dense_pass on the matrix cores: kDirectFirst / kDirectLast let the
+// first block read the state and the last block write it without staging the
+// tile in LDS; kSkipZero: test the tile for zeros in the first block.
+constexpr uint32_t kDirectFirst = 1, kDirectLast = 2, kSkipZero = 4;
 int tile_max_qubits(int dtype);
 int tile_launch_qubits(int dtype);
 int batch_tile_qubits(int dtype);
@@ -301,8 +312,6 @@ struct DenseBlock {
 };
 // launch_dense_pass precision code for complex128 blocks on the FP64 matrix cores
 constexpr int kPrecMfma64 = 100;
-// direct (matrix cores): kDirectFirst / kDirectLast let the first block read
-// the state and the last block write it without staging the tile in LDS
 hipError_t launch_dense_pass(void *amps, int n, int dtype, const TileSpec &sp, int k,
                              const DenseBlock *dev_blocks, int n_blocks, const char *dev_base, int prec,
                              uint32_t direct, hipStream_t s);

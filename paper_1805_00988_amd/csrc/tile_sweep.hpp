@@ -595,41 +595,61 @@ __device__ __forceinline__ void run_records(cpx<T> (&v)[1 << W], PhaseAcc<T, W> 
     }
 }
 
-// Tile bits of the sweep's register positions: gb (the group's own bits,
-// per lane) spreads group index g around them.
-template <int W>
-__device__ __forceinline__ uint32_t group_bits(const TileSweep &S, uint32_t g) {
+// XOR of the columns of g's bits.  A wave's threads share the bits from the
+// seventh on: those columns are picked on the scalar unit.
+template <typename U>
+__device__ __forceinline__ U group_columns(const U (&col)[kGroupBits], uint32_t g) {
+    const uint32_t gu = __builtin_amdgcn_readfirstlane(g);
+    U r = 0;
 #pragma unroll
-    for (int b = 0; b < W; ++b) {
-        const uint32_t low = (1u << S.qpos[b]) - 1u;
-        g = (g & low) | ((g & ~low) << 1);
+    for (int i = 6; i < kGroupBits; ++i) r ^= (gu >> i) & 1u ? col[i] : U(0);
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+        const uint32_t m = 0u - ((g >> i) & 1u);
+        if constexpr (sizeof(U) == 8) r ^= (((uint64_t)m << 32) | m) & col[i];
+        else r ^= m & col[i];
     }
-    return g;
-}
-
-// LDS offsets (swizzled) of the register indices' bits, uniform per sweep.
-template <typename T, int W>
-__device__ __forceinline__ void register_offsets(const TileSweep &S, uint32_t (&PF)[1 << W]) {
-#pragma unroll
-    for (int j = 0; j < (1 << W); ++j) {
-        uint32_t f = 0;
-#pragma unroll
-        for (int b = 0; b < W; ++b)
-            if ((j >> b) & 1) f |= 1u << S.qpos[b];
-        PF[j] = lds_phys<T>(f);
-    }
-}
-
-// Image of group g (register index 0) under the sweep's permutation.
-__device__ __forceinline__ uint32_t permuted_group(const TileSweep &S, const char *__restrict__ recs, uint32_t g,
-                                                   uint64_t base) {
-    const PermCond *pc = reinterpret_cast<const PermCond *>(recs + S.cond_off);
-    uint32_t c = S.cst;
-    for (int i = 0; i < S.n_cond; ++i) c ^= (base & pc[i].cond) == pc[i].cond ? pc[i].vec : 0u;
-    uint32_t r = __builtin_amdgcn_readfirstlane(c);
-#pragma unroll
-    for (int i = 0; i < kPermLane; ++i) r ^= (0u - ((g >> i) & 1u)) & S.lane_col[i];
     return r;
+}
+// XOR of the columns of register index j (a constant after unrolling).
+template <int W, typename U>
+__device__ __forceinline__ U register_columns(const U (&col)[kSweepW], int j) {
+    U o = 0;
+#pragma unroll
+    for (int b = 0; b < W; ++b)
+        if ((j >> b) & 1) o ^= col[b];
+    return o;
+}
+
+// Constant part of where a sweep's results go: the LDS byte offset, or the
+// index offset from the tile's base.
+__device__ __forceinline__ uint32_t out_constant(const TileSweep &S, const char *__restrict__ recs, uint64_t base) {
+    const PermCond *pc = reinterpret_cast<const PermCond *>(recs + S.cond_off);
+    uint32_t c = S.out_cst;
+    for (int i = 0; i < S.n_cond; ++i) c ^= (base & pc[i].cond) == pc[i].cond ? pc[i].out : 0u;
+    return c;
+}
+__device__ __forceinline__ uint64_t to_constant(const TileSweep &S, const char *__restrict__ recs, uint64_t base) {
+    const PermCond *pc = reinterpret_cast<const PermCond *>(recs + S.cond_off);
+    uint64_t c = S.to_cst;
+    for (int i = 0; i < S.n_cond; ++i) c ^= (base & pc[i].cond) == pc[i].cond ? pc[i].to : 0ull;
+    return c;
+}
+
+// A group's exchange through the LDS tile: byte offsets pg ^ the register
+// index's columns.
+template <typename T, int W>
+__device__ __forceinline__ void lds_store_group(char *lds, uint32_t pg, const uint32_t (&reg)[kSweepW],
+                                                const cpx<T> (&v)[1 << W]) {
+#pragma unroll
+    for (int j = 0; j < (1 << W); ++j) *reinterpret_cast<cpx<T> *>(lds + (pg ^ register_columns<W>(reg, j))) = v[j];
+}
+template <typename T, int W>
+__device__ __forceinline__ void lds_load_group(const char *lds, uint32_t pg, const uint32_t (&reg)[kSweepW],
+                                               cpx<T> (&v)[1 << W]) {
+#pragma unroll
+    for (int j = 0; j < (1 << W); ++j)
+        v[j] = *reinterpret_cast<const cpx<T> *>(lds + (pg ^ register_columns<W>(reg, j)));
 }
 
 } // namespace sv
