@@ -197,7 +197,6 @@ __device__ __forceinline__ double probe_pos(const cpx<T> (&v)[1 << W], const cpx
                                             uint32_t gb, const TileGate &G) {
     constexpr int D = 1 << W;
     double acc = 0.0;
-    if ((gb & G.lane) != G.lane) return acc;
 #pragma unroll
     for (int j = 0; j < D; ++j) {
         if (j & (1 << P)) continue;
@@ -205,7 +204,7 @@ __device__ __forceinline__ double probe_pos(const cpx<T> (&v)[1 << W], const cpx
         const int c = j | (1 << P);
         acc += probe_pair<T, KIND>(v[j], v[c], w[j], w[c], G);
     }
-    return acc;
+    return (gb & G.lane) == G.lane ? acc : 0.0;
 }
 
 template <typename T, int W, int KIND>
@@ -235,7 +234,15 @@ __device__ __forceinline__ double probe_gate(const cpx<T> (&v)[1 << W], const cp
     }
 }
 
-template <typename T, int W, bool TWOQ>
+// The record walk holds no branch on a lane's own values: one would have the
+// compiler structurize the whole loop, which merges its paths by copies
+// (every gate then moved both groups to other registers and back, 64 of the
+// 96 to 160 instructions of its path, in 168 vector registers instead of 104:
+// loss and gradient at 24 qubits complex128 21.2 ms instead of 16.9; the
+// complex64 instances still hold such copies).
+// FULL: one group per thread, whole waves.  The other instances serve states
+// of less than a wave of groups, whose idle threads hold zeros.
+template <typename T, int W, bool TWOQ, bool FULL>
 __global__ __launch_bounds__(kAdjThreads) void k_adjoint_tile(typename AV<T>::type *psi, typename AV<T>::type *lam,
                                                       TileSpec sp, int m, const TileSweep *__restrict__ sweeps,
                                                       int n_sweeps, const char *__restrict__ recs,
@@ -258,7 +265,7 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint_tile(typename AV<T>::ty
     // probes' wave sums and takes part in every barrier
     const uint32_t n_groups = tsize >> W;
     const uint32_t g = threadIdx.x;
-    const bool act = g < n_groups;
+    const bool act = FULL || g < n_groups;
     cpx<T> *ps = reinterpret_cast<cpx<T> *>(psi);
     cpx<T> *ls = reinterpret_cast<cpx<T> *>(lam);
     for (uint64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
@@ -293,10 +300,11 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint_tile(typename AV<T>::ty
                 const TileGate &G = *reinterpret_cast<const TileGate *>(rp);
                 rp += G.size;
                 if (is_probe(G.kind)) {
-                    if ((base & G.cout) != G.cout) continue; // uniform
-                    const double mine = act ? probe_gate<T, W>(v, w, g, G) : 0.0;
-                    const double c = wave_sum_d(mine);
-                    if ((threadIdx.x & 63) == 0) slot_acc[threadIdx.x >> 6][G.b1] += c;
+                    // every lane holds the wave's sum and adds it to the
+                    // same word; nothing where the controls outside the tile
+                    // do not hold (uniform)
+                    const double c = wave_sum_d(probe_gate<T, W>(v, w, g, G));
+                    slot_acc[threadIdx.x >> 6][G.b1] += (base & G.cout) == G.cout ? c : 0.0;
                 } else {
                     // adjoint passes carry no gathered phases (their probes
                     // read the amplitudes between gates); the register-index
@@ -356,21 +364,21 @@ hipError_t launch_adjoint_tile(void *psi, void *lam, int n, int dtype, const Til
     const size_t lds = (size_t)(1u << m) * (dtype == SV_C64 ? 8 : 16);
     const int W = std::min(m, sweep_width(dtype));
     if (((1u << m) >> W) > (unsigned)kAdjThreads) return hipErrorInvalidValue; // one group per thread
+    // one thread per group, at least a wave
+    const unsigned threads = std::max(64u, (1u << m) >> W);
+    auto launch = [&](auto kernel, auto *v) {
+        (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        using VT = std::remove_pointer_t<decltype(v)>;
+        kernel<<<n_blocks, threads, lds, s>>>((VT *)psi, (VT *)lam, spec, m, dev_sweeps, n_sweeps, dev_gates, slot0,
+                                              n_slots, partials, n_tiles);
+    };
+    const bool full = threads == (1u << m) >> W;
 #define SV_ADJ_CASE(TT, VT, WW)                                                                    \
     if (W == WW) {                                                                                 \
-        if (two_qubit) {                                                                           \
-            (void)hipFuncSetAttribute((const void *)k_adjoint_tile<TT, WW, true>,                  \
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);       \
-            k_adjoint_tile<TT, WW, true><<<n_blocks, 256, lds, s>>>(                               \
-                (VT *)psi, (VT *)lam, spec, m, dev_sweeps, n_sweeps, dev_gates, slot0, n_slots,    \
-                partials, n_tiles);                                                                \
-        } else {                                                                                   \
-            (void)hipFuncSetAttribute((const void *)k_adjoint_tile<TT, WW, false>,                 \
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);       \
-            k_adjoint_tile<TT, WW, false><<<n_blocks, 256, lds, s>>>(                              \
-                (VT *)psi, (VT *)lam, spec, m, dev_sweeps, n_sweeps, dev_gates, slot0, n_slots,    \
-                partials, n_tiles);                                                                \
-        }                                                                                          \
+        if (two_qubit && full) launch(k_adjoint_tile<TT, WW, true, true>, (VT *)nullptr);          \
+        else if (two_qubit) launch(k_adjoint_tile<TT, WW, true, false>, (VT *)nullptr);            \
+        else if (full) launch(k_adjoint_tile<TT, WW, false, true>, (VT *)nullptr);                 \
+        else launch(k_adjoint_tile<TT, WW, false, false>, (VT *)nullptr);                          \
         return hipGetLastError();                                                                  \
     }
     if (dtype == SV_C64) {
