@@ -434,10 +434,12 @@ hipError_t launch_scale(void *amps, int n, int dtype, uint64_t set_mask, const d
 // The pass's gates, grouped into register sweeps by the host, are applied
 // to the tile (tile_sweep.hpp); controls outside the tile are constant over a
 // tile and tested once on its base index.
-constexpr int kTileThreads = 512;
+// one register group of 16 amplitudes per thread
+template <typename T>
+constexpr int kTileThreads = std::is_same<T, float>::value ? 512 : 256;
 
-// Tiles of 4096 amplitudes: 32 KiB of LDS for complex64 (five 256-thread
-// workgroups per CU, the register file's limit too), 64 KiB for complex128.
+// Tiles of 4096 amplitudes: 32 KiB of LDS (five 256-thread workgroups per CU
+// for complex64; four for complex128, whose registers allow no more).
 // Measured on the 32-qubit headline circuits: complex64 tiles of 8192
 // amplitudes need fewer passes (44 against 53) but hold only four waves
 // per SIMD, and were slower overall; tiles of 16384 slower still.  The
@@ -450,10 +452,19 @@ int tile_max_qubits(int dtype) { return dtype == SV_C64 ? 12 : 12; }
 int tile_launch_qubits(int dtype) { return dtype == SV_C64 ? 13 : 12; }
 int batch_tile_qubits(int dtype) { return dtype == SV_C64 ? 13 : 12; }
 
-// Register qubits per sweep: 16 complex64 or 8 complex128 amplitudes per
-// group (64 and 32 VGPRs); a 4096-amplitude tile then takes 256 or 512
-// threads.
+// Register qubits per sweep of the batch and adjoint kernels, which hold 8
+// complex128 amplitudes per group.  The tile pass holds 16 (kSweepW) in both
+// precisions.  For complex128 that doubled what a CU has in flight at its
+// four waves per SIMD: a group of 8 in a 512-thread workgroup took the LDS of
+// a whole complex128 tile, 64 KiB, of which two fit; now the two components
+// cross LDS one after the other, in 32 KiB and with two more barriers, and
+// four workgroups of 256 threads fit.  Half the records per amplitude and
+// fewer sweeps come with it: depth 20 at 28 qubits 49.6 -> 40.1 ms.
 int sweep_width(int dtype) { return dtype == SV_C64 ? 4 : 3; }
+
+// Waves per SIMD the register allocation aims at.
+template <typename T>
+constexpr int kTileWaves = std::is_same<T, double>::value ? 4 : 7;
 
 // One pass: the first sweep reads its groups straight from the state and
 // the last writes them straight back, so the tile crosses LDS only between
@@ -465,61 +476,75 @@ int sweep_width(int dtype) { return dtype == SV_C64 ? 4 : 3; }
 // LDS, which nothing else uses before the first sweep stores its groups
 // there.
 template <typename T, int W, bool TWOQ, bool LPH, bool ZSKIP>
-__global__ __launch_bounds__(kTileThreads) void k_tile(typename Vec<T>::type *vec, TileSpec sp,
-                                                       const TileSweep *__restrict__ sweeps, int n_sweeps,
-                                                       const char *__restrict__ recs) {
+__global__ __launch_bounds__(kTileThreads<T>, kTileWaves<T>) void k_tile(typename Vec<T>::type *vec, TileSpec sp,
+                                                                      const TileSweep *__restrict__ sweeps,
+                                                                      int n_sweeps, const char *__restrict__ recs) {
     constexpr int D = 1 << W;
+    constexpr bool SPLIT = std::is_same<T, double>::value;
     extern __shared__ char lds[];
     uint64_t base = (uint64_t)blockIdx.x << sp.L;
     for (int i = 0; i < sp.K; ++i) base = insert_zero(base, sp.high[i]);
     cpx<T> *tile = reinterpret_cast<cpx<T> *>(vec) + base;
     const uint32_t g = threadIdx.x;
-    for (int si = 0; si < n_sweeps; ++si) {
+    cpx<T> v[D];
+    {
+        const TileSweep &S = sweeps[0];
+        const cpx<T> *row = tile + group_columns(S.at_lane, g);
+#pragma unroll
+        for (int j = 0; j < D; ++j) v[j] = row[register_columns<W>(S.at_reg, j)];
+    }
+    if constexpr (ZSKIP) {
+        uint32_t bits = 0;
+#pragma unroll
+        for (int j = 0; j < D; ++j) bits |= magnitude_bits(v[j].re) | magnitude_bits(v[j].im);
+        volatile uint32_t *seen = reinterpret_cast<volatile uint32_t *>(lds);
+        const uint32_t wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
+        const uint32_t any = wave_zero(bits) ? 0u : 1u;
+        if ((threadIdx.x & 63u) == 0u) seen[wave] = any;
+        __syncthreads();
+        uint32_t tile_any = 0;
+        for (uint32_t w = 0; w < n_waves; ++w) tile_any |= seen[w];
+        __syncthreads(); // the words are read before the tile is written over them
+        if (__builtin_amdgcn_readfirstlane(tile_any) == 0u) return;
+    }
+    for (int si = 0;; ++si) {
         const TileSweep &S = sweeps[si];
-        const bool first = si == 0, last = si == n_sweeps - 1;
-        cpx<T> v[D];
-        if (first) {
-            const cpx<T> *row = tile + group_columns(S.at_lane, g);
-#pragma unroll
-            for (int j = 0; j < D; ++j) v[j] = row[register_columns<W>(S.at_reg, j)];
-            if constexpr (ZSKIP) {
-                uint32_t bits = 0;
-#pragma unroll
-                for (int j = 0; j < D; ++j) bits |= magnitude_bits(v[j].re) | magnitude_bits(v[j].im);
-                volatile uint32_t *seen = reinterpret_cast<volatile uint32_t *>(lds);
-                const uint32_t wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
-                const uint32_t any = wave_zero(bits) ? 0u : 1u;
-                if ((threadIdx.x & 63u) == 0u) seen[wave] = any;
-                __syncthreads();
-                uint32_t tile_any = 0;
-                for (uint32_t w = 0; w < n_waves; ++w) tile_any |= seen[w];
-                __syncthreads(); // the words are read before the tile is written over them
-                if (__builtin_amdgcn_readfirstlane(tile_any) == 0u) return;
-            }
-        } else {
-            lds_load_group<T, W>(lds, group_columns(S.in_lane, g), S.in_reg, v);
-        }
         PhaseAcc<T, W> acc;
         acc.init();
         run_records<T, W, TWOQ, LPH>(v, acc, g, recs + S.rec_off, S.n_gates, base);
-        // results that go to other groups' places wait until every group of
-        // this sweep has been read (after a first sweep's loads from the
-        // state nothing reads the LDS tile)
-        if (S.perm && first == last) __syncthreads();
-        if (last) {
-            if (S.perm) {
-                const uint64_t to = to_constant(S, recs, base) ^ group_columns(S.to_lane, g);
-#pragma unroll
-                for (int j = 0; j < D; ++j) tile[to ^ register_columns<W>(S.to_reg, j)] = v[j];
-            } else {
-                cpx<T> *row = tile + group_columns(S.to_lane, g);
-#pragma unroll
-                for (int j = 0; j < D; ++j) row[register_columns<W>(S.to_reg, j)] = v[j];
-            }
-        } else {
-            lds_store_group<T, W>(lds, out_constant(S, recs, base) ^ group_columns(S.out_lane, g), S.out_reg, v);
+        if (si == n_sweeps - 1) break;
+        const TileSweep &N = sweeps[si + 1];
+        const uint32_t pg = out_constant(S, recs, base) ^ group_columns(S.out_lane, g);
+        const uint32_t pn = group_columns(N.in_lane, g);
+        if constexpr (SPLIT) {
+            // the real parts, then the imaginary parts
+            lds_store_part<T, W, 0>(lds, pg, S.out_reg, v);
             __syncthreads();
+            lds_load_part<T, W, 0>(lds, pn, N.in_reg, v);
+            __syncthreads();
+            lds_store_part<T, W, 1>(lds, pg, S.out_reg, v);
+            __syncthreads();
+            lds_load_part<T, W, 1>(lds, pn, N.in_reg, v);
+        } else {
+            lds_store_group<T, W>(lds, pg, S.out_reg, v);
+            __syncthreads();
+            lds_load_group<T, W>(lds, pn, N.in_reg, v);
         }
+        // every group is read before the next exchange writes; the last
+        // sweep's results go to the state
+        if (si + 2 < n_sweeps) __syncthreads();
+    }
+    const TileSweep &S = sweeps[n_sweeps - 1];
+    if (S.perm) {
+        // other groups' places, once every group has been read
+        if (n_sweeps == 1) __syncthreads();
+        const uint64_t to = to_constant(S, recs, base) ^ group_columns(S.to_lane, g);
+#pragma unroll
+        for (int j = 0; j < D; ++j) tile[to ^ register_columns<W>(S.to_reg, j)] = v[j];
+    } else {
+        cpx<T> *row = tile + group_columns(S.to_lane, g);
+#pragma unroll
+        for (int j = 0; j < D; ++j) row[register_columns<W>(S.to_reg, j)] = v[j];
     }
 }
 
@@ -535,7 +560,7 @@ static void launch_tile_t(typename Vec<T>::type *v, const TileSpec &spec, int m,
         kernel<<<(unsigned)n_tiles, threads, lds, s>>>(v, spec, sw, n_sweeps, g);
     };
     // tiles of less than a wave are states of one tile
-    constexpr bool FULL = W == (std::is_same<T, float>::value ? 4 : 3);
+    constexpr bool FULL = W == kSweepW;
     if constexpr (FULL) {
         if (skip_zero && threads >= 64) {
             launch(k_tile<T, W, TWOQ, LPH, true>);
@@ -564,13 +589,13 @@ hipError_t launch_tile(void *amps, int n, int dtype, const TileSpec &spec, const
         n - m > 30 || n_sweeps < 1)
         return hipErrorInvalidValue;
     const uint64_t n_tiles = 1ull << (n - m);
-    const size_t lds = (size_t)(1u << m) * (dtype == SV_C64 ? 8 : 16);
-    const int W = std::min(m, sweep_width(dtype));
-    if ((1 << (m - W)) > kTileThreads) return hipErrorInvalidValue; // one group per thread
+    const size_t lds = (size_t)(1u << m) * kTileLdsBytes;
+    const int W = std::min(m, kSweepW);
+    if ((1 << (m - W)) > (dtype == SV_C64 ? kTileThreads<float> : kTileThreads<double>)) return hipErrorInvalidValue; // one group per thread
     // complex64 lane-bit phase lists: only the full-width instances hold
     // them (the complex128 instances always do)
     if (lane_phases && dtype == SV_C64) {
-        if (W != sweep_width(SV_C64)) return hipErrorInvalidValue;
+        if (W != kSweepW) return hipErrorInvalidValue;
         if (two_qubit)
             launch_tile_t<float, 4, true, true>((float4 *)amps, spec, m, dev_sweeps, n_sweeps, dev_gates, n_tiles,
                                                 skip_zero, lds, s);

@@ -351,6 +351,7 @@ struct PermGate {
 struct PassCode {
     TileSpec sp{};
     int m = 0;
+    int lds_bytes = 8;          // LDS bytes per amplitude of the kernel that runs it
     double flops_per_amp = 0.0; // algorithmic flops of the pass per state amplitude
     bool two_qubit = false;     // holds SK_2Q records
     bool lane_phases = false;   // holds SK_LPH records
@@ -381,7 +382,8 @@ static uint64_t tile_global_offset(const TileSpec &sp, uint32_t l);
 
 // Address columns of a sweep (TileSweep), its results permuted by the
 // sweep's X gates; the conditional constants follow the records.
-static void sweep_addresses(PassCode &pc, size_t si, int amp_bytes) {
+static void sweep_addresses(PassCode &pc, size_t si) {
+    const int amp_bytes = pc.lds_bytes;
     TileSweep &S = pc.sweeps[si];
     uint32_t regs = 0;
     for (int b : pc.qsets[si]) regs |= 1u << b;
@@ -460,7 +462,7 @@ static void pack_records(PassCode &pc, bool f32) {
         }
     }
     for (size_t si = 0; si < pc.sweeps.size(); ++si)
-        sweep_addresses(pc, si, f32 ? 8 : 16);
+        sweep_addresses(pc, si);
     pc.recs.resize(pc.recs.size() + kRecordTail, 0);
 }
 
@@ -710,8 +712,9 @@ constexpr int kMinPhaseRun = 4;
 
 static PassCode compile_pass(const TileSpec &sp, const std::vector<const Gate *> &gs, int sweep_w, bool f32,
                              const std::vector<const Probe *> *probes = nullptr, bool lph_f32 = false,
-                             bool store_perms = false) {
+                             bool store_perms = false, int lds_bytes = kTileLdsBytes) {
     PassCode pc;
+    pc.lds_bytes = lds_bytes;
     pc.sp = sp;
     pc.m = sp.L + sp.K;
     pc.gates.reserve(gs.size() + 8);
@@ -1123,7 +1126,7 @@ static int tile_single(sv_state *h, const Gate &g) {
     TileSpec sp{};
     tile_layout(h->n, std::min(h->n, tile_max_qubits(h->dtype)), std::min(h->n, 6), g.tmask(), &sp);
     std::vector<const Gate *> one{&g};
-    const PassCode pc = compile_pass(sp, one, sweep_width(h->dtype), h->dtype == SV_C64);
+    const PassCode pc = compile_pass(sp, one, kSweepW, h->dtype == SV_C64);
     int rc = ensure_arena(h, pc.bytes());
     if (rc) return rc;
     if ((rc = stage_wait(h))) return rc;
@@ -1433,7 +1436,7 @@ static int run_gates(sv_state *h, const std::vector<Gate> &gs, int mode) {
                 }
                 ptrs.push_back(g);
             }
-            r.code = compile_pass(sp, ptrs, sweep_width(h->dtype), h->dtype == SV_C64, nullptr, true, true);
+            r.code = compile_pass(sp, ptrs, kSweepW, h->dtype == SV_C64, nullptr, true, true);
         }
         ready.push_back(std::move(r));
         int rc;
@@ -1925,7 +1928,7 @@ static double fused_pass_cost(const sv_state *h, const FusedPass &fp) {
 
 static double plain_pass_cost(const sv_state *h, const PassCode &pc) {
     double valu = 0.0, entries = 0.0;
-    const int D = 1 << std::min(pc.m, sweep_width(h->dtype));
+    const int D = 1 << std::min(pc.m, kSweepW);
     for (const TileGate &r : pc.gates) {
         const int en = __builtin_popcount(r.amask);
         switch (r.kind) {
@@ -2007,7 +2010,7 @@ static int compile_fused_gates(const sv_state *h, const std::vector<Gate> &gs, i
             fp.plain = true;
             fp.sp = sp;
             fp.m = mtile;
-            fp.code = compile_pass(sp, ptrs, sweep_width(h->dtype), h->dtype == SV_C64, nullptr, true, true);
+            fp.code = compile_pass(sp, ptrs, kSweepW, h->dtype == SV_C64, nullptr, true, true);
             fp.cost = plain_pass_cost(h, fp.code);
             if (fp.cost < best.cost) {
                 best = std::move(fp);
@@ -2367,7 +2370,7 @@ static BatchProgram compile_batch(const std::vector<int> &widths,
             } else {
                 tile_layout(w, m, lmin, needed, &sp);
             }
-            PassCode pc = compile_pass(sp, ptrs, sweep_w, dtype == SV_C64, nullptr, false, true);
+            PassCode pc = compile_pass(sp, ptrs, sweep_w, dtype == SV_C64, nullptr, false, true, dtype == SV_C64 ? 8 : 16);
             if (pc.sweeps.empty()) {
                 // a circuit without gates still needs one sweep: the batch
                 // kernel synthesises |0...0> and reduces in a sweep's registers
@@ -2375,7 +2378,7 @@ static BatchProgram compile_batch(const std::vector<int> &widths,
                 pc.sweeps.push_back(TileSweep{});
                 pc.qsets.push_back({});
                 for (int b = 0; b < W; ++b) pc.qsets[0].push_back(pc.m - W + b);
-                sweep_addresses(pc, 0, dtype == SV_C64 ? 8 : 16);
+                sweep_addresses(pc, 0);
             }
             BatchPass q{};
             q.sp = sp;
@@ -3170,7 +3173,8 @@ int sv_adjoint_grad(sv_handle h, sv_handle lam, const sv_op *ops, int n_ops, con
         nslot[pi] = ns;
         TileSpec sp{};
         tile_layout(h->n, mmax, lmin, needed, &sp);
-        code[pi] = compile_pass(sp, ptrs, sweep_width(h->dtype), h->dtype == SV_C64, &prs, false, true);
+        code[pi] = compile_pass(sp, ptrs, sweep_width(h->dtype), h->dtype == SV_C64, &prs, false, true,
+                                h->dtype == SV_C64 ? 8 : 16);
         offs[pi] = total;
         total += align256(code[pi].bytes());
     }

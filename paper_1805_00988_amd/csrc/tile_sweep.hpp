@@ -652,4 +652,23 @@ __device__ __forceinline__ void lds_load_group(const char *lds, uint32_t pg, con
         v[j] = *reinterpret_cast<const cpx<T> *>(lds + (pg ^ register_columns<W>(reg, j)));
 }
 
+// One component of the groups through an LDS tile of that component.
+template <typename T, int W, int PART>
+__device__ __forceinline__ void lds_store_part(char *lds, uint32_t pg, const uint32_t (&reg)[kSweepW],
+                                               const cpx<T> (&v)[1 << W]) {
+#pragma unroll
+    for (int j = 0; j < (1 << W); ++j)
+        *reinterpret_cast<T *>(lds + (pg ^ register_columns<W>(reg, j))) = PART ? v[j].im : v[j].re;
+}
+template <typename T, int W, int PART>
+__device__ __forceinline__ void lds_load_part(const char *lds, uint32_t pg, const uint32_t (&reg)[kSweepW],
+                                              cpx<T> (&v)[1 << W]) {
+#pragma unroll
+    for (int j = 0; j < (1 << W); ++j) {
+        const T x = *reinterpret_cast<const T *>(lds + (pg ^ register_columns<W>(reg, j)));
+        if (PART) v[j].im = x;
+        else v[j].re = x;
+    }
+}
+
 } // namespace sv
