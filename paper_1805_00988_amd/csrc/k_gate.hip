@@ -438,8 +438,9 @@ hipError_t launch_scale(void *amps, int n, int dtype, uint64_t set_mask, const d
 template <typename T>
 constexpr int kTileThreads = std::is_same<T, float>::value ? 512 : 256;
 
-// Tiles of 4096 amplitudes: 32 KiB of LDS (five 256-thread workgroups per CU
-// for complex64; four for complex128, whose registers allow no more).
+// Tiles of 4096 amplitudes, of which the sweeps exchange one component at a
+// time: 16 KiB of LDS for complex64 (seven 256-thread workgroups per CU), 32
+// KiB for complex128 (four); the registers allow no more of either.
 // Measured on the 32-qubit headline circuits: complex64 tiles of 8192
 // amplitudes need fewer passes (44 against 53) but hold only four waves
 // per SIMD, and were slower overall; tiles of 16384 slower still.  The
@@ -459,7 +460,9 @@ int batch_tile_qubits(int dtype) { return dtype == SV_C64 ? 13 : 12; }
 // a whole complex128 tile, 64 KiB, of which two fit; now the two components
 // cross LDS one after the other, in 32 KiB and with two more barriers, and
 // four workgroups of 256 threads fit.  Half the records per amplitude and
-// fewer sweeps come with it: depth 20 at 28 qubits 49.6 -> 40.1 ms.
+// fewer sweeps come with it: depth 20 at 28 qubits 49.6 -> 40.1 ms.  The same
+// exchange takes complex64 from five to seven waves per SIMD (29 qubits 48.3
+// -> 44.7 ms).
 int sweep_width(int dtype) { return dtype == SV_C64 ? 4 : 3; }
 
 // Waves per SIMD the register allocation aims at.
@@ -480,7 +483,6 @@ __global__ __launch_bounds__(kTileThreads<T>, kTileWaves<T>) void k_tile(typenam
                                                                       const TileSweep *__restrict__ sweeps,
                                                                       int n_sweeps, const char *__restrict__ recs) {
     constexpr int D = 1 << W;
-    constexpr bool SPLIT = std::is_same<T, double>::value;
     extern __shared__ char lds[];
     uint64_t base = (uint64_t)blockIdx.x << sp.L;
     for (int i = 0; i < sp.K; ++i) base = insert_zero(base, sp.high[i]);
@@ -516,20 +518,14 @@ __global__ __launch_bounds__(kTileThreads<T>, kTileWaves<T>) void k_tile(typenam
         const TileSweep &N = sweeps[si + 1];
         const uint32_t pg = out_constant(S, recs, base) ^ group_columns(S.out_lane, g);
         const uint32_t pn = group_columns(N.in_lane, g);
-        if constexpr (SPLIT) {
-            // the real parts, then the imaginary parts
-            lds_store_part<T, W, 0>(lds, pg, S.out_reg, v);
-            __syncthreads();
-            lds_load_part<T, W, 0>(lds, pn, N.in_reg, v);
-            __syncthreads();
-            lds_store_part<T, W, 1>(lds, pg, S.out_reg, v);
-            __syncthreads();
-            lds_load_part<T, W, 1>(lds, pn, N.in_reg, v);
-        } else {
-            lds_store_group<T, W>(lds, pg, S.out_reg, v);
-            __syncthreads();
-            lds_load_group<T, W>(lds, pn, N.in_reg, v);
-        }
+        // the real parts, then the imaginary parts
+        lds_store_part<T, W, 0>(lds, pg, S.out_reg, v);
+        __syncthreads();
+        lds_load_part<T, W, 0>(lds, pn, N.in_reg, v);
+        __syncthreads();
+        lds_store_part<T, W, 1>(lds, pg, S.out_reg, v);
+        __syncthreads();
+        lds_load_part<T, W, 1>(lds, pn, N.in_reg, v);
         // every group is read before the next exchange writes; the last
         // sweep's results go to the state
         if (si + 2 < n_sweeps) __syncthreads();
@@ -589,7 +585,7 @@ hipError_t launch_tile(void *amps, int n, int dtype, const TileSpec &spec, const
         n - m > 30 || n_sweeps < 1)
         return hipErrorInvalidValue;
     const uint64_t n_tiles = 1ull << (n - m);
-    const size_t lds = (size_t)(1u << m) * kTileLdsBytes;
+    const size_t lds = (size_t)(1u << m) * (dtype == SV_C64 ? 4 : 8); // one component
     const int W = std::min(m, kSweepW);
     if ((1 << (m - W)) > (dtype == SV_C64 ? kTileThreads<float> : kTileThreads<double>)) return hipErrorInvalidValue; // one group per thread
     // complex64 lane-bit phase lists: only the full-width instances hold

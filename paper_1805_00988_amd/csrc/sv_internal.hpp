@@ -243,10 +243,6 @@ __host__ __device__ inline uint32_t lds_swizzle(uint32_t l, int amp_bytes) {
     return l ^ (((l >> 3) ^ (l >> 4) ^ (l >> 5)) & 7u);
 }
 
-// LDS bytes per amplitude of a tile pass: a complex64 amplitude, or one
-// component of a complex128 amplitude (they cross one after the other).
-constexpr int kTileLdsBytes = 8;
-
 constexpr int kMaxTileHigh = 8; // extra tile qubits beyond the low block
 struct TileSpec {
     int L;                    // low qubits 0..L-1 are in the tile
