@@ -190,8 +190,10 @@ enum sv_run_mode { SV_RUN_PER_GATE = 0, SV_RUN_TILED = 1 };
 int sv_run(sv_handle h, const sv_op *ops, int n_ops, const double *params, int n_params,
            int mode);
 
-/* The passes sv_run's tiled mode forms for a register of n_qubits of the
- * given dtype (host only: no state, no device call).  Gates apply in the
+/* The passes of sv_run's scheduler for a register of n_qubits of the given
+ * dtype with tiles of 12 qubits (host only: no state, no device call; sv_run
+ * itself forms passes by the same rules for tiles of 14 qubits, complex64,
+ * or 13, complex128).  Gates apply in the
  * order of Sec. 2.3 (the ops in sequence); a pass may take a gate ahead of
  * gates left behind only when they share no qubit.  level 0 is the greedy
  * scheduler, 1 the lookahead, 2 the two-pass lookahead, -1 the level sv_run

@@ -436,21 +436,20 @@ hipError_t launch_scale(void *amps, int n, int dtype, uint64_t set_mask, const d
 // tile and tested once on its base index.
 // one register group of 16 amplitudes per thread
 template <typename T>
-constexpr int kTileThreads = std::is_same<T, float>::value ? 512 : 256;
+constexpr int kTileThreads = std::is_same<T, float>::value ? 1024 : 512;
 
-// Tiles of 4096 amplitudes, of which the sweeps exchange one component at a
-// time: 16 KiB of LDS for complex64 (seven 256-thread workgroups per CU), 32
-// KiB for complex128 (four); the registers allow no more of either.
-// Measured on the 32-qubit headline circuits: complex64 tiles of 8192
-// amplitudes need fewer passes (44 against 53) but hold only four waves
-// per SIMD, and were slower overall; tiles of 16384 slower still.  The
-// batch kernel keeps 8192-amplitude complex64 tiles (whole circuits of up
-// to 13 qubits in one workgroup).
-int tile_max_qubits(int dtype) { return dtype == SV_C64 ? 12 : 12; }
-// Largest tile a tile pass accepts: the fused path's complex64 passes keep
-// 8192-amplitude tiles (64 KiB of LDS, 512 threads) when they run as plain
-// sweeps.
-int tile_launch_qubits(int dtype) { return dtype == SV_C64 ? 13 : 12; }
+// Tiles of 16384 complex64 or 8192 complex128 amplitudes, of which the sweeps
+// exchange one component at a time: 64 KiB of LDS, two workgroups of 1024
+// and 512 threads per CU, which fill the eight (complex64) and four
+// (complex128) waves per SIMD that their registers allow.  A larger tile
+// takes more gates per trip of the state: depth 20 at 29 qubits complex64
+// takes 44.3, 39.9 and 36.1 ms with tiles of 2^12, 2^13 and 2^14, at 28
+// qubits complex128 40.0, 35.6 and 38.7 (of 2^14 a CU holds one workgroup,
+// and nothing runs while it loads or stores).  The order is the same for
+// random circuits and QFTs from 13 to 27 qubits.  The batch kernel keeps
+// 8192-amplitude complex64 tiles (whole circuits of up to 13 qubits in one
+// workgroup).
+int tile_max_qubits(int dtype) { return dtype == SV_C64 ? 14 : 13; }
 int batch_tile_qubits(int dtype) { return dtype == SV_C64 ? 13 : 12; }
 
 // Register qubits per sweep of the batch and adjoint kernels, which hold 8
@@ -467,7 +466,7 @@ int sweep_width(int dtype) { return dtype == SV_C64 ? 4 : 3; }
 
 // Waves per SIMD the register allocation aims at.
 template <typename T>
-constexpr int kTileWaves = std::is_same<T, double>::value ? 4 : 7;
+constexpr int kTileWaves = std::is_same<T, double>::value ? 4 : 8;
 
 // One pass: the first sweep reads its groups straight from the state and
 // the last writes them straight back, so the tile crosses LDS only between
@@ -581,7 +580,7 @@ hipError_t launch_tile(void *amps, int n, int dtype, const TileSpec &spec, const
                        hipStream_t s) {
     const int m = spec.L + spec.K;
     const int vbits = dtype == SV_C64 ? 1 : 0;
-    if (m > n || m > tile_launch_qubits(dtype) || spec.L < vbits || spec.K > kMaxTileHigh || m < 1 ||
+    if (m > n || m > tile_max_qubits(dtype) || spec.L < vbits || spec.K > kMaxTileHigh || m < 1 ||
         n - m > 30 || n_sweeps < 1)
         return hipErrorInvalidValue;
     const uint64_t n_tiles = 1ull << (n - m);

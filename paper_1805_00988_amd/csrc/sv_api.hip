@@ -331,12 +331,12 @@ static uint64_t tile_qubits(const TileSpec &sp) {
 }
 
 // Some qubit outside the tile is as the basis state left it: most of the
-// pass's tiles are likely to hold zeros.  Up to 1024 tiles the chip runs all
-// at once, and skipping some leaves the others' time: there the test only
-// adds its barrier (the QFT's first pass at 16 qubits complex128, 46 us with
-// it and 41 without).
+// pass's tiles are likely to hold zeros.  States of up to 64 MiB are as many
+// tiles as the chip holds at once, and skipping some leaves the others'
+// time: there the test only adds its barrier (the QFT's first pass at 16
+// qubits complex128, 46 us with it and 41 without).
 static bool untouched_outside(const sv_state *h, const TileSpec &sp) {
-    return h->n - sp.L - sp.K > 10 && (((1ull << h->n) - 1ull) & ~tile_qubits(sp) & ~h->moved) != 0;
+    return state_bytes(h) > 64.0 * (1 << 20) && (((1ull << h->n) - 1ull) & ~tile_qubits(sp) & ~h->moved) != 0;
 }
 
 // X on local bit t where the tile holds the index bits 'cout' and, if c >= 0,
@@ -733,7 +733,7 @@ constexpr int kMinPhaseRun = 4;
 
 static PassCode compile_pass(const TileSpec &sp, const std::vector<const Gate *> &gs, int sweep_w, bool f32,
                              const std::vector<const Probe *> *probes = nullptr, bool lph_f32 = false,
-                             bool store_perms = false, int lds_bytes = 0) {
+                             int perm_bits = 0, int lds_bytes = 0) {
     PassCode pc;
     // the tile pass exchanges one component at a time
     pc.lds_bytes = lds_bytes ? lds_bytes : (f32 ? 4 : 8);
@@ -742,7 +742,8 @@ static PassCode compile_pass(const TileSpec &sp, const std::vector<const Gate *>
     pc.gates.reserve(gs.size() + 8);
     const int W = std::min(pc.m, sweep_w);
     // stores can permute where every thread of whole waves holds one group
-    const bool perms = store_perms && W == sweep_w && pc.m - W >= 6 && pc.m - W <= kPermLane;
+    // (perm_bits: thread index bits of the kernel's workgroups, 0: never)
+    const bool perms = W == sweep_w && pc.m - W >= 6 && pc.m - W <= perm_bits;
     std::vector<int> qset;
     std::vector<size_t> cur;
     auto probe_of = [&](size_t i) -> const Probe * { return probes ? (*probes)[i] : nullptr; };
@@ -1389,6 +1390,7 @@ static bool needs_tile(int dtype, const Gate &g) {
 // Tile size and low block of sv_run's plain passes: runs of 128 complex64 /
 // 64 complex128 amplitudes (shorter runs cut the number of passes but cost
 // more per pass, measured).
+constexpr int kScheduleTile = 12; // sv_schedule's tiles
 static int plain_tile_qubits(int n, int dtype) { return std::min(n, tile_max_qubits(dtype)); }
 static int plain_low_qubits(int n, int dtype) { return std::min(n, dtype == SV_C64 ? 7 : 6); }
 
@@ -1458,7 +1460,7 @@ static int run_gates(sv_state *h, const std::vector<Gate> &gs, int mode) {
                 }
                 ptrs.push_back(g);
             }
-            r.code = compile_pass(sp, ptrs, kSweepW, h->dtype == SV_C64, nullptr, true, true);
+            r.code = compile_pass(sp, ptrs, kSweepW, h->dtype == SV_C64, nullptr, true, kGroupBits);
         }
         ready.push_back(std::move(r));
         int rc;
@@ -2018,7 +2020,7 @@ static int compile_fused_gates(const sv_state *h, const std::vector<Gate> &gs, i
             }
         }
         const int mtile = sp.L + sp.K;
-        bool plain_ok = mtile <= tile_launch_qubits(h->dtype);
+        bool plain_ok = mtile <= tile_max_qubits(h->dtype);
         std::vector<Gate> local;
         local.reserve(sub.size());
         for (const Gate &g : sub) {
@@ -2032,7 +2034,7 @@ static int compile_fused_gates(const sv_state *h, const std::vector<Gate> &gs, i
             fp.plain = true;
             fp.sp = sp;
             fp.m = mtile;
-            fp.code = compile_pass(sp, ptrs, kSweepW, h->dtype == SV_C64, nullptr, true, true);
+            fp.code = compile_pass(sp, ptrs, kSweepW, h->dtype == SV_C64, nullptr, true, kGroupBits);
             fp.cost = plain_pass_cost(h, fp.code);
             if (fp.cost < best.cost) {
                 best = std::move(fp);
@@ -2392,7 +2394,7 @@ static BatchProgram compile_batch(const std::vector<int> &widths,
             } else {
                 tile_layout(w, m, lmin, needed, &sp);
             }
-            PassCode pc = compile_pass(sp, ptrs, sweep_w, dtype == SV_C64, nullptr, false, true, dtype == SV_C64 ? 8 : 16);
+            PassCode pc = compile_pass(sp, ptrs, sweep_w, dtype == SV_C64, nullptr, false, 9, dtype == SV_C64 ? 8 : 16);
             if (pc.sweeps.empty()) {
                 // a circuit without gates still needs one sweep: the batch
                 // kernel synthesises |0...0> and reduces in a sweep's registers
@@ -2989,7 +2991,7 @@ int sv_schedule(int n_qubits, int dtype, const sv_op *ops, int n_ops, const doub
     std::vector<Gate> gs;
     int rc = parse_ops(nullptr, n_qubits, ops, n_ops, params, n_params, gs);
     if (rc) return rc;
-    const int mmax = plain_tile_qubits(n_qubits, dtype), lmin = plain_low_qubits(n_qubits, dtype);
+    const int mmax = std::min(n_qubits, kScheduleTile), lmin = plain_low_qubits(n_qubits, dtype);
     const int lv = level < 0 ? lookahead_level_for(n_qubits, dtype) : level;
     const std::vector<Pass> passes = schedule(gs, n_qubits, mmax, lmin, true, lv);
     *n_passes = (int)passes.size();
@@ -3195,7 +3197,7 @@ int sv_adjoint_grad(sv_handle h, sv_handle lam, const sv_op *ops, int n_ops, con
         nslot[pi] = ns;
         TileSpec sp{};
         tile_layout(h->n, mmax, lmin, needed, &sp);
-        code[pi] = compile_pass(sp, ptrs, sweep_width(h->dtype), h->dtype == SV_C64, &prs, false, true,
+        code[pi] = compile_pass(sp, ptrs, sweep_width(h->dtype), h->dtype == SV_C64, &prs, false, 8,
                                 h->dtype == SV_C64 ? 8 : 16);
         offs[pi] = total;
         total += align256(code[pi].bytes());

@@ -195,8 +195,6 @@ constexpr int kSweepW = 4; // tile qubits held in registers per sweep (fewer for
 // depth 20 at 28 qubits complex128 has 79 sweeps instead of 95 (61.2 -> 55.4
 // ms), at 29 qubits complex64 62 instead of 74 (61.6 -> 57.8 ms), a
 // 12-qubit register 25 instead of 42.
-constexpr int kPermLane = 9; // most group-index bits of a sweep whose stores permute: one group per
-                             // thread of at most 512 threads
 // A sweep's register group g holds the amplitudes that differ in the
 // sweep's register positions; its index bits are the other tile positions in
 // ascending order, and a thread's group is its own index.  Controls and
@@ -273,7 +271,6 @@ hipError_t launch_tile(void *amps, int n, int dtype, const TileSpec &spec, const
 // tile in LDS; kSkipZero: test the tile for zeros in the first block.
 constexpr uint32_t kDirectFirst = 1, kDirectLast = 2, kSkipZero = 4;
 int tile_max_qubits(int dtype);
-int tile_launch_qubits(int dtype);
 int batch_tile_qubits(int dtype);
 int sweep_width(int dtype);
 // Dense blocks of a fused tile pass: positions of the block's qubits in the

@@ -597,8 +597,12 @@ __device__ __forceinline__ void run_records(cpx<T> (&v)[1 << W], PhaseAcc<T, W> 
 
 // XOR of the columns of g's bits.  A wave's threads share the bits from the
 // seventh on: those columns are picked on the scalar unit.
+// The masks of g's bits are formed anew for each use: kept from the first
+// loads to the last stores they cost 12 registers through all records (67
+// instead of 55 for complex64, 122 instead of 110 for complex128).
 template <typename U>
 __device__ __forceinline__ U group_columns(const U (&col)[kGroupBits], uint32_t g) {
+    asm volatile("" : "+v"(g));
     const uint32_t gu = __builtin_amdgcn_readfirstlane(g);
     U r = 0;
 #pragma unroll
