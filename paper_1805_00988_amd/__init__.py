@@ -176,6 +176,21 @@ def ops_from_gates(gates) -> np.ndarray:
     arr = np.zeros(max(1, n), dtype=SV_OP_DTYPE)
     if n == 0:
         return arr
+    matrices = _lib.fill_ops(gates, arr.ctypes.data, n)
+    if matrices < 0:
+        _convert_gates(gates, arr, n)
+    if matrices:
+        for i, g in enumerate(gates):
+            if g.name == "U":
+                m = _mat(g.matrix)
+                if m.size > 32:
+                    raise ValueError("sv_op holds at most a 4x4 matrix")
+                arr["matrix"][i, :m.size] = m
+    return arr
+
+
+def _convert_gates(gates, arr: np.ndarray, n: int) -> None:
+    """The fields of any gate sequence (all but the matrices)."""
     arr["kind"][:n] = [GATE_KINDS[g.name] for g in gates]
     arr["n_targets"][:n] = [len(g.targets) for g in gates]
     t = arr["targets"]
@@ -184,13 +199,6 @@ def ops_from_gates(gates) -> np.ndarray:
     arr["ctrl_mask"][:n] = [sum(1 << c for c in g.controls) for g in gates]
     arr["param_index"][:n] = [g.param for g in gates]
     arr["theta"][:n] = [g.theta for g in gates]
-    for i, g in enumerate(gates):
-        if g.name == "U":
-            m = _mat(g.matrix)
-            if m.size > 32:
-                raise ValueError("sv_op holds at most a 4x4 matrix")
-            arr["matrix"][i, :m.size] = m
-    return arr
 
 
 def _opptr(arr: np.ndarray):
@@ -357,8 +365,8 @@ class _Op:
 
     def __init__(self, name, targets, controls=(), theta=0.0, matrix=None):
         self.name = name
-        self.targets = tuple(int(q) for q in targets)
-        self.controls = tuple(int(q) for q in controls)
+        self.targets = tuple(map(int, targets))
+        self.controls = tuple(map(int, controls))
         self.theta = float(theta)
         self.param = -1
         self.matrix = matrix

@@ -12,6 +12,7 @@ import os
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libsv.so")
+PY_LIB_PATH = os.path.join(HERE, "libsvpy.so")
 
 SV_C64, SV_C128 = 1, 2
 SV_OK, SV_EINVAL, SV_ENOMEM, SV_EDEVICE, SV_EUNSUPPORTED = 0, -1, -2, -3, -4
@@ -116,6 +117,24 @@ def load():
             f.argtypes = args
         _lib = L
     return _lib
+
+
+_fill = None
+
+
+def fill_ops(gates, out_ptr: int, n: int) -> int:
+    """Records of n gates written at out_ptr by libsvpy.so: the number of
+    gates that carry a matrix, -1 where the gates are not of the plain form
+    (or the helper is not there): then the caller converts them."""
+    global _fill
+    if _fill is None:
+        if os.path.exists(PY_LIB_PATH):
+            _fill = ctypes.PyDLL(PY_LIB_PATH).sv_py_fill_ops
+            _fill.restype = ctypes.c_ssize_t
+            _fill.argtypes = [ctypes.py_object, ctypes.py_object, _P, ctypes.c_ssize_t]
+        else:
+            _fill = lambda *args: -1  # noqa: E731
+    return _fill(gates, GATE_KINDS, out_ptr, n)
 
 
 def check(code: int) -> None:

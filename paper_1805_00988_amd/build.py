@@ -12,11 +12,13 @@ import re
 import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libsv.so")
+PY_OUT = os.path.join(HERE, "libsvpy.so")
 OBJ = os.path.join(HERE, "_build")
 ARCH = "gfx950"
 
@@ -93,7 +95,20 @@ def build(verbose: bool = False) -> str:
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
     os.replace(tmp, OUT)
+    build_py()
     return OUT
+
+
+def build_py() -> str:
+    """The binding's C helper (host code of the running interpreter's ABI)."""
+    tmp = PY_OUT + ".tmp"
+    cmd = [os.environ.get("CXX") or "g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall",
+           "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "py_ops.cpp"), "-o", tmp]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"building {PY_OUT} failed:\n{r.stdout}\n{r.stderr}")
+    os.replace(tmp, PY_OUT)
+    return PY_OUT
 
 
 if __name__ == "__main__":
