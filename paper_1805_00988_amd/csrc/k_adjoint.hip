@@ -332,14 +332,17 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint_tile(typename AV<T>::ty
                 const uint32_t pn = group_columns(N.in_lane, g);
                 // each barrier orders one vector's writes before its reads,
                 // and its reads before the next writes to the tile
-                if (act) lds_store_group<T, W>(lds, pg, S.out_reg, v);
-                __syncthreads();
-                if (act) lds_load_group<T, W>(lds, pn, N.in_reg, v);
-                __syncthreads();
-                if (act) lds_store_group<T, W>(lds, pg, S.out_reg, w);
-                __syncthreads();
-                if (act) lds_load_group<T, W>(lds, pn, N.in_reg, w);
-                __syncthreads();
+                auto part = [&](auto component, cpx<T>(&x)[D]) {
+                    constexpr int C = decltype(component)::value;
+                    if (act) lds_store_part<T, W, C>(lds, pg, S.out_reg, x);
+                    __syncthreads();
+                    if (act) lds_load_part<T, W, C>(lds, pn, N.in_reg, x);
+                    __syncthreads();
+                };
+                part(std::integral_constant<int, 0>{}, v);
+                part(std::integral_constant<int, 1>{}, v);
+                part(std::integral_constant<int, 0>{}, w);
+                part(std::integral_constant<int, 1>{}, w);
             }
         }
     }
@@ -361,7 +364,7 @@ hipError_t launch_adjoint_tile(void *psi, void *lam, int n, int dtype, const Til
         return hipErrorInvalidValue;
     const uint64_t n_tiles = 1ull << (n - m);
     if ((uint64_t)n_blocks > n_tiles) return hipErrorInvalidValue; // every workgroup owns a tile
-    const size_t lds = (size_t)(1u << m) * (dtype == SV_C64 ? 8 : 16);
+    const size_t lds = (size_t)(1u << m) * (dtype == SV_C64 ? 4 : 8); // one component
     const int W = std::min(m, sweep_width(dtype));
     if (((1u << m) >> W) > (unsigned)kAdjThreads) return hipErrorInvalidValue; // one group per thread
     // one thread per group, at least a wave

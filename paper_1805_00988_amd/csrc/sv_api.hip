@@ -3197,8 +3197,7 @@ int sv_adjoint_grad(sv_handle h, sv_handle lam, const sv_op *ops, int n_ops, con
         nslot[pi] = ns;
         TileSpec sp{};
         tile_layout(h->n, mmax, lmin, needed, &sp);
-        code[pi] = compile_pass(sp, ptrs, sweep_width(h->dtype), h->dtype == SV_C64, &prs, false, 8,
-                                h->dtype == SV_C64 ? 8 : 16);
+        code[pi] = compile_pass(sp, ptrs, sweep_width(h->dtype), h->dtype == SV_C64, &prs, false, 8);
         offs[pi] = total;
         total += align256(code[pi].bytes());
     }
