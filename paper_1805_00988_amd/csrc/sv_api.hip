@@ -727,6 +727,42 @@ static TileGate encode_probe(const TileSpec &sp, const std::vector<int> &qset, c
 // target, since they act per amplitude.  With probes (adjoint passes), a
 // parametrised gate needs its target in registers and is encoded as a probe
 // record followed by its own record.
+// FP32 entries of a gate make it longer or shorter by up to 2^-25 relative,
+// the same way each time the gate is applied (sqrt(1/2) by 1.7e-8), which
+// was most of a deep complex64 circuit's error.  The pass's last full
+// one-qubit gate is scaled back by the product before it is rounded.
+struct NormDrift {
+    double log_norm = 0.0;
+    const Gate *gate = nullptr; // the last such gate and its record
+    size_t record = 0;
+    void add(const Gate &g, size_t rec, bool f32) {
+        if (!f32 || g.k != 1 || g.ctrl != 0 || is_x(g) || (is_diag1(g) && is_one(g.U))) return;
+        double exact = 0.0, rounded = 0.0;
+        for (int i = 0; i < 8; ++i) {
+            const double r = (float)g.U[i];
+            exact += g.U[i] * g.U[i];
+            rounded += r * r;
+        }
+        if (!(exact > 1e-30 && exact < 1e30 && rounded > 0.0)) return;
+        log_norm += 0.5 * std::log(rounded / exact);
+        gate = &g;
+        record = rec;
+    }
+    void settle(PassCode &pc) const {
+        if (!gate || log_norm == 0.0) return;
+        const double f = std::exp(-log_norm);
+        double U[8];
+        for (int i = 0; i < 8; ++i) U[i] = f * gate->U[i];
+        TileGate &r = pc.gates[record];
+        if (is_diag1(*gate)) {
+            const double d[4] = {U[0], U[1], U[6], U[7]};
+            put_matrix(r, d, 2, true);
+        } else {
+            put_matrix(r, U, 4, true);
+        }
+    }
+};
+
 // shortest run of phase gates gathered into per-lane factors (a flush costs
 // about as much as applying three of them one by one)
 constexpr int kMinPhaseRun = 4;
@@ -746,6 +782,7 @@ static PassCode compile_pass(const TileSpec &sp, const std::vector<const Gate *>
     const bool perms = W == sweep_w && pc.m - W >= 6 && pc.m - W <= perm_bits;
     std::vector<int> qset;
     std::vector<size_t> cur;
+    NormDrift drift;
     auto probe_of = [&](size_t i) -> const Probe * { return probes ? (*probes)[i] : nullptr; };
     auto close = [&](bool empty_too) {
         if (cur.empty() && !empty_too) return;
@@ -966,6 +1003,7 @@ static PassCode compile_pass(const TileSpec &sp, const std::vector<const Gate *>
                 pc.flops_per_amp += 8.0 / (double)(1ull << __builtin_popcountll(gs[i]->ctrl));
             }
             pc.gates.push_back(encode_sweep_gate(sp, qset, *gs[i], f32));
+            drift.add(*gs[i], pc.gates.size() - 1, f32);
             pc.two_qubit = pc.two_qubit || pc.gates.back().kind == SK_2Q;
             ++sw.n_gates;
             pc.flops_per_amp += (probes ? 2.0 : 1.0) * gate_flops_per_amp(*gs[i]);
@@ -1123,6 +1161,7 @@ static PassCode compile_pass(const TileSpec &sp, const std::vector<const Gate *>
         if (!is_diag1(*g)) pc.moves |= g->tmask();
         for (int i = 0; i < 2 << (2 * g->k); ++i) pc.finite = pc.finite && std::fabs(g->U[i]) <= (f32 ? FLT_MAX : DBL_MAX);
     }
+    drift.settle(pc);
     pack_records(pc, f32);
     return pc;
 }
