@@ -1433,38 +1433,7 @@ constexpr int kScheduleTile = 12; // sv_schedule's tiles
 static int plain_tile_qubits(int n, int dtype) { return std::min(n, tile_max_qubits(dtype)); }
 static int plain_low_qubits(int n, int dtype) { return std::min(n, dtype == SV_C64 ? 7 : 6); }
 
-// diag(d0, d1) = d0 diag(1, d1 / d0): the uncontrolled diagonal gates (RZ)
-// become phase gates, which change half of the amplitudes, and the last of
-// them takes the others' d0.  The factors are formed in extended precision.
-// (RY and RZ on every qubit: a third of the vector work of the rotations.)
-static void relative_phases(std::vector<Gate> &gs) {
-    using wide = std::complex<long double>;
-    auto candidate = [](const Gate &g) {
-        return is_diag1(g) && g.ctrl == 0 && !is_one(g.U) && std::abs(std::hypot(g.U[0], g.U[1]) - 1.0) < 1e-9;
-    };
-    size_t last = gs.size();
-    for (size_t i = 0; i < gs.size(); ++i)
-        if (candidate(gs[i])) last = i;
-    wide common = 1.0L;
-    for (size_t i = 0; i < last && last < gs.size(); ++i) {
-        if (!candidate(gs[i])) continue;
-        double *U = gs[i].U;
-        const wide d0(U[0], U[1]), r = wide(U[6], U[7]) / d0;
-        common *= d0;
-        U[0] = 1.0;
-        U[1] = 0.0;
-        U[6] = (double)r.real();
-        U[7] = (double)r.imag();
-    }
-    if (common == wide(1.0L)) return;
-    for (int k = 0; k < 8; k += 6) {
-        const wide d = common * wide(gs[last].U[k], gs[last].U[k + 1]);
-        gs[last].U[k] = (double)d.real();
-        gs[last].U[k + 1] = (double)d.imag();
-    }
-}
-
-static int run_gates(sv_state *h, std::vector<Gate> &gs, int mode) {
+static int run_gates(sv_state *h, const std::vector<Gate> &gs, int mode) {
     if (mode == SV_RUN_PER_GATE) {
         for (const Gate &g : gs) {
             const int rc = apply_one(h, g);
@@ -1472,7 +1441,6 @@ static int run_gates(sv_state *h, std::vector<Gate> &gs, int mode) {
         }
         return SV_OK;
     }
-    relative_phases(gs);
     const int mmax = plain_tile_qubits(h->n, h->dtype), lmin = plain_low_qubits(h->n, h->dtype);
     // Passes are compiled, staged and uploaded together while they are few
     // and short; from the size that gets the lookahead on, each is launched
@@ -2240,8 +2208,7 @@ static int run_fused_passes(sv_state *h, std::vector<FusedPass> &fps, ArenaRoom 
 
 // Fuse and run a gate list.  Each pass is launched as soon as it is compiled
 // (about a millisecond of host time, on any size of state).
-static int run_fused_gates(sv_state *h, std::vector<Gate> &gs, int k_max, int prec, int *n_blocks) {
-    relative_phases(gs);
+static int run_fused_gates(sv_state *h, const std::vector<Gate> &gs, int k_max, int prec, int *n_blocks) {
     ArenaRoom room;
     std::vector<FusedPass> ready(1);
     return compile_fused_gates(h, gs, k_max, prec, n_blocks, [&](FusedPass fp) -> int {
@@ -3222,7 +3189,6 @@ int sv_adjoint_grad(sv_handle h, sv_handle lam, const sv_op *ops, int n_ops, con
         std::memcpy(pr.M, M, sizeof(M));
         probes_store.push_back(pr);
     }
-    relative_phases(rev);
     const int mmax = std::min(h->n, adjoint_tile_qubits(h->dtype));
     const int lmin = std::min(h->n, h->dtype == SV_C64 ? 7 : 6);
     const int B = (int)std::min<uint64_t>((uint64_t)adjoint_blocks(), 1ull << (h->n - mmax));
@@ -3357,7 +3323,6 @@ int sv_batch_create(int n_circuits, const int *widths, const int64_t *op_offsets
                 return fail(rc, "circuit " + std::to_string(i) + " op " + std::to_string(j - lo) + ": " + g_last_error);
             }
         }
-        relative_phases(gs);
     }
     hipError_t e;
     if ((e = hipMalloc((void **)&b->d_out, sizeof(double) * n_circuits)) != hipSuccess ||
