@@ -246,8 +246,11 @@ template <typename T, int W, bool TWOQ, bool FULL>
 __global__ __launch_bounds__(kAdjThreads) void k_adjoint_tile(typename AV<T>::type *psi, typename AV<T>::type *lam,
                                                       TileSpec sp, int m, const TileSweep *__restrict__ sweeps,
                                                       int n_sweeps, const char *__restrict__ recs,
-                                                      int slot0, int n_slots, double *partials,
+                                                      uint32_t bytes, int slot0, int n_slots, double *partials,
                                                       uint64_t n_tiles) {
+    if constexpr (!TWOQ) { // the 4x4 path leaves no scalar registers for it
+        if (blockIdx.x < kWarmGroups) warm_records(sweeps, bytes);
+    }
     constexpr int D = 1 << W;
     // one LDS tile, used by psi and then by lam at each exchange (half the
     // LDS of a tile per vector: more workgroups per CU)
@@ -355,7 +358,7 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint_tile(typename AV<T>::ty
 }
 
 hipError_t launch_adjoint_tile(void *psi, void *lam, int n, int dtype, const TileSpec &spec,
-                               const TileSweep *dev_sweeps, int n_sweeps, const char *dev_gates,
+                               const TileSweep *dev_sweeps, int n_sweeps, const char *dev_gates, size_t bytes,
                                int slot0, int n_slots, double *partials, int n_blocks, bool two_qubit,
                                hipStream_t s) {
     const int m = spec.L + spec.K;
@@ -372,7 +375,8 @@ hipError_t launch_adjoint_tile(void *psi, void *lam, int n, int dtype, const Til
     auto launch = [&](auto kernel, auto *v) {
         (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         using VT = std::remove_pointer_t<decltype(v)>;
-        kernel<<<n_blocks, threads, lds, s>>>((VT *)psi, (VT *)lam, spec, m, dev_sweeps, n_sweeps, dev_gates, slot0,
+        kernel<<<n_blocks, threads, lds, s>>>((VT *)psi, (VT *)lam, spec, m, dev_sweeps, n_sweeps, dev_gates, (uint32_t)bytes,
+                                              slot0,
                                               n_slots, partials, n_tiles);
     };
     const bool full = threads == (1u << m) >> W;

@@ -144,6 +144,8 @@ __global__ __launch_bounds__(kBatchThreads) void k_batch(BatchArgs a, SV_BATCH_P
         const int ci = order[qi];
         const BatchCircuit &c = circuits[ci];
         const BatchPass &p = passes[c.pass_off];
+        warm_records(sweeps + p.sweep_off, p.n_sweeps * (uint32_t)sizeof(TileSweep));
+        warm_records(recs + p.gate_off, p.rec_bytes);
         cpx<T> *state = reinterpret_cast<cpx<T> *>(reinterpret_cast<char *>(a.states) + c.state_off);
         double zacc = 0.0;
         batch_tile<T, W, TWOQ>(state, lds, c.w, 0, sweeps + p.sweep_off, p.n_sweeps, recs + p.gate_off,
@@ -178,6 +180,10 @@ __global__ __launch_bounds__(kBatchThreads) void k_batch_wide(BatchArgs a, SV_BA
         uint32_t tile = 0, rest = (uint32_t)local & ((1u << tl) - 1u);
         for (uint32_t b = p.tiles; b; b &= b - 1u, rest >>= 1)
             if (rest & 1u) tile |= b & (0u - b);
+        if ((local & ((1ll << tl) - 1)) < 8) { // the first tiles, one on each XCD
+            warm_records(sweeps + p.sweep_off, p.n_sweeps * (uint32_t)sizeof(TileSweep));
+            warm_records(recs + p.gate_off, p.rec_bytes);
+        }
         cpx<T> *state = reinterpret_cast<cpx<T> *>(reinterpret_cast<char *>(a.states) + c.state_off);
         uint64_t base = (uint64_t)tile << p.sp.L;
         for (int i = 0; i < p.sp.K; ++i) base = insert_zero(base, p.sp.high[i]);

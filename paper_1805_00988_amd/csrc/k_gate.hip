@@ -480,9 +480,13 @@ constexpr int kTileWaves = std::is_same<T, double>::value ? 4 : 8;
 template <typename T, int W, bool TWOQ, bool LPH, bool ZSKIP>
 __global__ __launch_bounds__(kTileThreads<T>, kTileWaves<T>) void k_tile(typename Vec<T>::type *vec, TileSpec sp,
                                                                       const TileSweep *__restrict__ sweeps,
-                                                                      int n_sweeps, const char *__restrict__ recs) {
+                                                                      int n_sweeps, const char *__restrict__ recs,
+                                                                      uint32_t bytes) {
     constexpr int D = 1 << W;
     extern __shared__ char lds[];
+    // the workgroups that start together (see warm_records); sweeps and
+    // records lie one after the other
+    if (blockIdx.x < kWarmGroups) warm_records(sweeps, bytes);
     uint64_t base = (uint64_t)blockIdx.x << sp.L;
     for (int i = 0; i < sp.K; ++i) base = insert_zero(base, sp.high[i]);
     cpx<T> *tile = reinterpret_cast<cpx<T> *>(vec) + base;
@@ -545,14 +549,14 @@ __global__ __launch_bounds__(kTileThreads<T>, kTileWaves<T>) void k_tile(typenam
 
 template <typename T, int W, bool TWOQ, bool LPH = std::is_same<T, double>::value>
 static void launch_tile_t(typename Vec<T>::type *v, const TileSpec &spec, int m, const TileSweep *sw,
-                          int n_sweeps, const char *g, uint64_t n_tiles, bool skip_zero, size_t lds,
+                          int n_sweeps, const char *g, uint32_t bytes, uint64_t n_tiles, bool skip_zero, size_t lds,
                           hipStream_t s) {
     // one workgroup per tile (measured faster than a capped grid looping
     // over tiles), and one thread per register group
     const unsigned threads = 1u << (m - W);
     auto launch = [&](auto kernel) {
         (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        kernel<<<(unsigned)n_tiles, threads, lds, s>>>(v, spec, sw, n_sweeps, g);
+        kernel<<<(unsigned)n_tiles, threads, lds, s>>>(v, spec, sw, n_sweeps, g, bytes);
     };
     // tiles of less than a wave are states of one tile
     constexpr bool FULL = W == kSweepW;
@@ -576,7 +580,7 @@ static void launch_tile_t(typename Vec<T>::type *v, const TileSpec &spec, int m,
 // host sets the flag only while some qubit outside the tile has not been
 // acted on since the register was set to a basis state (sv_state::moved).
 hipError_t launch_tile(void *amps, int n, int dtype, const TileSpec &spec, const TileSweep *dev_sweeps,
-                       int n_sweeps, const char *dev_gates, bool two_qubit, bool lane_phases, bool skip_zero,
+                       int n_sweeps, const char *dev_gates, size_t bytes, bool two_qubit, bool lane_phases, bool skip_zero,
                        hipStream_t s) {
     const int m = spec.L + spec.K;
     const int vbits = dtype == SV_C64 ? 1 : 0;
@@ -592,21 +596,21 @@ hipError_t launch_tile(void *amps, int n, int dtype, const TileSpec &spec, const
     if (lane_phases && dtype == SV_C64) {
         if (W != kSweepW) return hipErrorInvalidValue;
         if (two_qubit)
-            launch_tile_t<float, 4, true, true>((float4 *)amps, spec, m, dev_sweeps, n_sweeps, dev_gates, n_tiles,
+            launch_tile_t<float, 4, true, true>((float4 *)amps, spec, m, dev_sweeps, n_sweeps, dev_gates, bytes, n_tiles,
                                                 skip_zero, lds, s);
         else
             launch_tile_t<float, 4, false, true>((float4 *)amps, spec, m, dev_sweeps, n_sweeps, dev_gates,
-                                                 n_tiles, skip_zero, lds, s);
+                                                 bytes, n_tiles, skip_zero, lds, s);
         return hipGetLastError();
     }
 #define SV_TILE_CASE(WW, Q)                                                                        \
     if (W == WW && two_qubit == Q) {                                                               \
         if (dtype == SV_C64)                                                                       \
             launch_tile_t<float, WW, Q>((float4 *)amps, spec, m, dev_sweeps, n_sweeps, dev_gates,  \
-                                        n_tiles, skip_zero, lds, s);                                  \
+                                        bytes, n_tiles, skip_zero, lds, s);                                  \
         else                                                                                       \
             launch_tile_t<double, WW, Q>((double2 *)amps, spec, m, dev_sweeps, n_sweeps,           \
-                                         dev_gates, n_tiles, skip_zero, lds, s);                      \
+                                         dev_gates, bytes, n_tiles, skip_zero, lds, s);                      \
         return hipGetLastError();                                                                  \
     }
     SV_TILE_CASE(4, false)

@@ -1178,7 +1178,7 @@ static int launch_pass(sv_state *h, const PassCode &pc, size_t off) {
     const char *gt = h->d_arena + off + align256(pc.sweeps.size() * sizeof(TileSweep));
     Timed tm(h, K_TILE, 2.0 * state_bytes(h), pc.flops_per_amp * (double)(1ull << h->n));
     const bool zeros = pc.finite && untouched_outside(h, pc.sp);
-    SV_HIP(launch_tile(h->amps, h->n, h->dtype, pc.sp, sw, (int)pc.sweeps.size(), gt, pc.two_qubit, pc.lane_phases,
+    SV_HIP(launch_tile(h->amps, h->n, h->dtype, pc.sp, sw, (int)pc.sweeps.size(), gt, pc.bytes(), pc.two_qubit, pc.lane_phases,
                        zeros, h->stream));
     h->moved |= pc.moves;
     return SV_OK;
@@ -2447,7 +2447,10 @@ static BatchProgram compile_batch(const std::vector<int> &widths,
             q.sp = sp;
             q.n_sweeps = (int)pc.sweeps.size();
             q.sweep_off = (int)bp.sweeps.size();
+            // records of every pass start on 16 bytes and end on them
+            bp.recs.resize((bp.recs.size() + 15) & ~(size_t)15, 0);
             q.gate_off = (int)bp.recs.size();
+            q.rec_bytes = (int32_t)(pc.recs.size() & ~(size_t)15);
             q.live = live;
             live |= pc.moves;
             finite = finite && pc.finite;
@@ -3270,6 +3273,7 @@ int sv_adjoint_grad(sv_handle h, sv_handle lam, const sv_op *ops, int n_ops, con
         const char *gt = h->d_arena + offs[pi] + align256(pc.sweeps.size() * sizeof(TileSweep));
         Timed tm(h, K_ADJOINT, 4.0 * state_bytes(h), pc.flops_per_amp * (double)(1ull << h->n));
         hipError_t e = launch_adjoint_tile(h->amps, lam->amps, h->n, h->dtype, pc.sp, sw, (int)pc.sweeps.size(), gt,
+                                           pc.bytes(),
                                            slot0[pi], nslot[pi], partials + loss_n, B, pc.two_qubit, h->stream);
         if (e != hipSuccess) return restore(hip_fail(e, "launch_adjoint_tile"));
     }

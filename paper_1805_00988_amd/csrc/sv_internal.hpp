@@ -262,9 +262,10 @@ hipError_t launch_gate2(void *amps, int n, int dtype, int t0, int t1, uint64_t c
 hipError_t launch_scale(void *amps, int n, int dtype, uint64_t set_mask, const double *factor,
                         hipStream_t s);
 // two_qubit: the pass holds SK_2Q records (selects the kernel instance with that
-// path).  skip_zero: test each tile for zeros.
+// path).  bytes: the sweeps and the records, from dev_sweeps on.  skip_zero:
+// test each tile for zeros.
 hipError_t launch_tile(void *amps, int n, int dtype, const TileSpec &spec, const TileSweep *dev_sweeps,
-                       int n_sweeps, const char *dev_recs, bool two_qubit, bool lane_phases, bool skip_zero,
+                       int n_sweeps, const char *dev_recs, size_t bytes, bool two_qubit, bool lane_phases, bool skip_zero,
                        hipStream_t s);
 // launch_dense_pass on the matrix cores: kDirectFirst / kDirectLast let the
 // first block read the state and the last block write it without staging the
@@ -342,6 +343,8 @@ struct BatchPass {
     int32_t n_sweeps;
     int32_t sweep_off;
     int32_t gate_off;      // byte offset of the pass's records in the stream
+    int32_t rec_bytes;     // their length
+    int32_t pad;
     uint32_t tiles;        // bits of the tile index that the listed tiles take
     // qubits that gates of earlier passes have moved off |0>; an amplitude
     // with any other bit set is zero, whatever the state buffer holds there
@@ -417,7 +420,7 @@ hipError_t launch_sum_slots(const double *partials, int n_slots, int n_blocks, d
 // Probes of the pass's parametrised gates accumulate per workgroup and are
 // written to partials[(slot0 + i) * n_blocks + workgroup] for i < n_slots.
 hipError_t launch_adjoint_tile(void *psi, void *lam, int n, int dtype, const TileSpec &spec,
-                               const TileSweep *dev_sweeps, int n_sweeps, const char *dev_recs,
+                               const TileSweep *dev_sweeps, int n_sweeps, const char *dev_recs, size_t bytes,
                                int slot0, int n_slots, double *partials, int n_blocks, bool two_qubit,
                                hipStream_t s);
 int adjoint_tile_qubits(int dtype);
