@@ -1968,20 +1968,20 @@ static std::vector<FusedPass> compile_fused(const sv_state *h, const std::vector
 // of its qubits there (those outside select a variant of its block's
 // matrix per tile).
 // Cost model of one pass, in ms per 2^30 amplitudes, fitted to kernel times
-// measured on the MI355X (30-qubit complex64 fusion workload and the 32-qubit
-// complex64 headline passes; complex128 scaled by its measured per-amplitude
-// ratio).  A matrix-core pass costs its streaming floor plus a share per
-// block by width and engine; a plain pass its floor plus shares per sweep
-// (LDS exchange and barrier), per record, per gathered phase and per vector
-// ALU operation.  It only ranks the alternatives of one pass.
+// measured on the MI355X (28-qubit complex64 fusion workload, 25 passes,
+// within 10 %; complex128 from the 28-qubit random circuits).  A matrix-core
+// pass costs its streaming floor plus a share per block by width and engine;
+// a plain pass its records' vector operations on top of a share for its
+// loads, stores and exchanges, at least the time of its trip of the state.
+// It only ranks the alternatives of one pass.
 static double fused_pass_cost(const sv_state *h, const FusedPass &fp) {
     const bool c64 = h->dtype == SV_C64;
-    double t = c64 ? 3.4 : 6.5;
+    double t = c64 ? (fp.engine == SV_PREC_FP32 ? 3.0 : 3.6) : 6.5;
     for (const DenseBlock &db : fp.blocks) {
         const int k = db.bp.k;
         switch (fp.engine) {
-        case SV_PREC_SPLIT_BF16: t += k <= 4 ? 0.34 : 0.65; break;
-        case SV_PREC_FP32: t += k <= 4 ? 0.77 : 1.83; break;
+        case SV_PREC_SPLIT_BF16: t += k <= 4 ? 0.42 : 0.8; break;
+        case SV_PREC_FP32: t += k <= 4 ? 0.93 : 2.2; break;
         case kPrecMfma64: t += k <= 4 ? 1.5 : 3.2; break;
         default: t += c64 ? 0.12 * (1 << k) : 0.25 * (1 << k); break; // vector ALUs
         }
@@ -1990,7 +1990,7 @@ static double fused_pass_cost(const sv_state *h, const FusedPass &fp) {
 }
 
 static double plain_pass_cost(const sv_state *h, const PassCode &pc) {
-    double valu = 0.0, entries = 0.0;
+    double valu = 0.0;
     const int D = 1 << std::min(pc.m, kSweepW);
     for (const TileGate &r : pc.gates) {
         const int en = __builtin_popcount(r.amask);
@@ -2000,16 +2000,14 @@ static double plain_pass_cost(const sv_state *h, const PassCode &pc) {
         case SK_SWAP: valu += 2 * en; break;
         case SK_DIAG: case SK_DIAGR: valu += 8 + 4 * en; break;
         case SK_2Q: valu += 64 * en; break;
-        case SK_PHASE: valu += 6 + 6 * r.b1; entries += r.b1; break;
-        case SK_PTAB: valu += 6 + 6 * r.b1; entries += r.b1; break;
-        case SK_LPH: valu += 6 + 8 * r.b1; entries += r.b1; break;
+        case SK_PHASE: valu += 6 + 6 * r.b1; break;
+        case SK_PTAB: valu += 6 + 6 * r.b1; break;
+        case SK_LPH: valu += 6 + 8 * r.b1; break;
         case SK_FLUSH: valu += 4.0 * D * __builtin_popcount(r.amask); break;
         default: break;
         }
     }
-    const double t = 1.31 + 0.58 * (double)pc.sweeps.size() + 0.057 * (double)pc.gates.size() + 0.017 * entries +
-                     4.4e-5 * valu;
-    return h->dtype == SV_C64 ? t : 2.5 * t;
+    return h->dtype == SV_C64 ? std::max(3.1, 1.5 + 1.18e-3 * valu) : std::max(6.2, 3.0 + 2.4e-3 * valu);
 }
 
 // Each pass goes to 'emit' as soon as it is compiled.
