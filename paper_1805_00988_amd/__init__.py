@@ -219,9 +219,11 @@ def sv_run(h, gates, params=None, mode: int = SV_RUN_TILED) -> None:
 
 
 def sv_schedule(n_qubits: int, dtype, gates, level: int = -1, params=None):
-    """The passes of sv_run's tiled mode (host library, no GPU): (pass index
-    of every gate as an int array, list of each pass's tile-qubit mask, 0 for
-    a gate sv_run streams)."""
+    """The scheduler's passes on tiles of 12 qubits (host library, no GPU):
+    (pass index of every gate as an int array, list of each pass's tile-qubit
+    mask, 0 for a gate of its own that is streamed).  sv_run forms its passes
+    by the same rules on its own tiles, of 14 qubits in complex64 and 13 in
+    complex128."""
     ops = ops_from_gates(gates)
     pp, n_p, keep = _params(params)
     cap = max(1, len(gates))

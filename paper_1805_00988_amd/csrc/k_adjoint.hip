@@ -128,9 +128,9 @@ __global__ __launch_bounds__(kAdjThreads) void k_sum_slots(const double *partial
 
 // Workgroups of the adjoint launches (each owns at least one tile and writes
 // one partial per slot): more of them than fit at once, so that tiles are
-// handed out as workgroups finish; at 24 qubits one tile each (measured:
-// 24.9 ms per loss and gradient against 25.3 with 4096 workgroups and 26.5
-// with 768 looping ones).
+// handed out as workgroups finish; at 24 qubits one tile each (measured when
+// a loss and gradient took 24.9 ms: 25.3 with 4096 workgroups and 26.5 with
+// 768 looping ones; it takes 15.2 now).
 int adjoint_blocks() { return 8192; }
 
 hipError_t launch_adjoint_init(const void *psi, void *lam, int n, int dtype, int n_terms,

@@ -22,10 +22,11 @@
 // passes before this one have moved (BatchPass::live), so tiles that still
 // hold only zeros are not listed: the first pass, which holds most of a
 // ladder's gates, runs one tile of each circuit instead of 2 to 32 (0.36
-// instead of 2.47 ms on the 1024 circuits, whose run takes 3.6 ms).  Listed and left at once by
-// their workgroups they saved nothing: the tiles that remained were every
-// 2nd to 32nd workgroup, which the dispatcher had dealt to the same XCD and
-// compute units.
+// instead of 2.47 ms on the 1024 circuits; their whole run takes 2.55 ms
+// with the later changes to the sweeps).  Listed and left at once by their
+// workgroups they saved nothing: the tiles that remained were every 2nd to
+// 32nd workgroup, which the dispatcher had dealt to the same XCD and compute
+// units.
 #include "sv_internal.hpp"
 #include "tile_sweep.hpp"
 

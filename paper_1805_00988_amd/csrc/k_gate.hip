@@ -429,11 +429,11 @@ hipError_t launch_scale(void *amps, int n, int dtype, uint64_t set_mask, const d
 }
 
 // ------------------------------------------------------------ tile pass
-// A workgroup stages one tile of 2^m amplitudes in LDS: the low qubits
-// 0..L-1 (contiguous runs of 2^L amplitudes in HBM) plus K further qubits.
-// The pass's gates, grouped into register sweeps by the host, are applied
-// to the tile (tile_sweep.hpp); controls outside the tile are constant over a
-// tile and tested once on its base index.
+// A workgroup holds one tile of 2^m amplitudes in registers and exchanges it
+// through LDS: the low qubits 0..L-1 (contiguous runs of 2^L amplitudes in
+// HBM) plus K further qubits.  The pass's gates, grouped into register sweeps
+// by the host, are applied to the tile (tile_sweep.hpp); controls outside the
+// tile are constant over a tile and tested once on its base index.
 // one register group of 16 amplitudes per thread
 template <typename T>
 constexpr int kTileThreads = std::is_same<T, float>::value ? 1024 : 512;
@@ -575,10 +575,12 @@ static void launch_tile_t(typename Vec<T>::type *v, const TileSpec &spec, int m,
 // zeros, and zeros stay zeros under any gate.  Such a tile costs its read.
 // On |x> at 30 qubits complex128 the QFT's first pass (phases conditioned on
 // 18 outside qubits) takes 4.6 ms instead of 18.4, its second and third
-// 2.7 and 3.2 instead of 7.0 and 7.2 (the whole circuit 43.1 -> 21.0 ms).  The test itself (a barrier per tile before the
-// first sweep's updates) made passes over a dense state up to 16 % slower, so the
-// host sets the flag only while some qubit outside the tile has not been
-// acted on since the register was set to a basis state (sv_state::moved).
+// 2.7 and 3.2 instead of 7.0 and 7.2 (the whole circuit 43.1 -> 21.0 ms, on
+// tiles of 2^12; 18.9 on tiles of 2^13).  The test itself (a barrier per tile
+// before the first sweep's updates) made passes over a dense state up to 16 %
+// slower, so the host sets the flag only while some qubit outside the tile
+// has not been acted on since the register was set to a basis state
+// (sv_state::moved).
 hipError_t launch_tile(void *amps, int n, int dtype, const TileSpec &spec, const TileSweep *dev_sweeps,
                        int n_sweeps, const char *dev_gates, size_t bytes, bool two_qubit, bool lane_phases, bool skip_zero,
                        hipStream_t s) {

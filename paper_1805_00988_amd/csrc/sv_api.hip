@@ -189,7 +189,9 @@ static int op_to_gate(int n, const sv_op &op, const double *params, int n_params
 }
 
 // ---------------------------------------------------------------- buffers
-static int ensure_arena(sv_state *h, size_t bytes) {
+// A larger arena, or, drained, the old one as it was when there is no memory
+// for it (*no_memory).
+static int ensure_arena(sv_state *h, size_t bytes, bool *no_memory = nullptr) {
     if (bytes <= h->arena_cap) return SV_OK;
     size_t cap = std::max<size_t>(1 << 16, h->arena_cap);
     while (cap < bytes) cap *= 2;
@@ -197,13 +199,18 @@ static int ensure_arena(sv_state *h, size_t bytes) {
     // the old device arena may still be read by queued kernels: drain first
     SV_HIP(hipStreamSynchronize(h->stream));
     h->stage_pending = false;
-    if (h->d_arena) SV_HIP(hipFree(h->d_arena));
-    if (h->h_arena) SV_HIP(hipHostFree(h->h_arena));
-    h->d_arena = nullptr;
-    h->h_arena = nullptr;
-    h->arena_cap = 0;
-    SV_HIP(hipMalloc((void **)&h->d_arena, cap));
-    SV_HIP(hipHostMalloc((void **)&h->h_arena, cap, hipHostMallocDefault));
+    char *dev = nullptr, *host = nullptr;
+    hipError_t e = hipMalloc((void **)&dev, cap);
+    if (e == hipSuccess && (e = hipHostMalloc((void **)&host, cap, hipHostMallocDefault)) != hipSuccess) (void)hipFree(dev);
+    if (e != hipSuccess) {
+        (void)hipGetLastError(); // or the next launch reports it
+        if (no_memory) *no_memory = true;
+        return hip_fail(e, "staging arena");
+    }
+    if (h->d_arena) (void)hipFree(h->d_arena);
+    if (h->h_arena) (void)hipHostFree(h->h_arena);
+    h->d_arena = dev;
+    h->h_arena = host;
     h->arena_cap = cap;
     return SV_OK;
 }
@@ -227,15 +234,20 @@ static int stage_wait(sv_state *h) {
 
 // Room in the arena for the passes that one call stages and launches part
 // by part, each at an offset of its own.  A part that does not fit gets a
-// larger arena and starts it anew, for which the stream is drained: later
-// calls find the larger one.
+// larger arena and starts it anew, for which the stream is drained; without
+// memory for a larger one it starts the old one anew, so that a call that
+// has launched passes goes on.  At its end the call leaves an arena that
+// would have held all its parts, so that the same call again neither
+// allocates nor waits.
 struct ArenaRoom {
-    size_t off = 0;
+    size_t off = 0, sum = 0;
     bool fresh = true; // nothing staged by this call yet
     int take(sv_state *h, size_t bytes, size_t *at) {
         int rc = SV_OK;
         if (off + bytes > h->arena_cap) {
-            rc = ensure_arena(h, std::max(off + bytes, h->arena_cap ? 2 * h->arena_cap : (size_t)1 << 20));
+            bool no_memory = false;
+            rc = ensure_arena(h, std::max(off + bytes, h->arena_cap ? 4 * h->arena_cap : (size_t)1 << 20), &no_memory);
+            if (no_memory && bytes <= h->arena_cap) rc = SV_OK;
             off = 0;
         }
         // the host copy is free once the last call's upload has left it
@@ -243,7 +255,13 @@ struct ArenaRoom {
         fresh = false;
         *at = off;
         off += bytes;
+        sum += bytes;
         return rc;
+    }
+    int done(sv_state *h) {
+        bool no_memory = false;
+        const int rc = ensure_arena(h, sum, &no_memory);
+        return no_memory ? SV_OK : rc;
     }
 };
 
@@ -732,7 +750,7 @@ static TileGate encode_probe(const TileSpec &sp, const std::vector<int> &qset, c
 // was most of a deep complex64 circuit's error.  The pass's last full
 // one-qubit gate is scaled back by the product before it is rounded.
 struct NormDrift {
-    double log_norm = 0.0;
+    double norm2 = 1.0;         // the square of the factor by which the entries move the norm
     const Gate *gate = nullptr; // the last such gate and its record
     size_t record = 0;
     void add(const Gate &g, size_t rec, bool f32) {
@@ -744,13 +762,13 @@ struct NormDrift {
             rounded += r * r;
         }
         if (!(exact > 1e-30 && exact < 1e30 && rounded > 0.0)) return;
-        log_norm += 0.5 * std::log(rounded / exact);
+        norm2 *= rounded / exact;
         gate = &g;
         record = rec;
     }
     void settle(PassCode &pc) const {
-        if (!gate || log_norm == 0.0) return;
-        const double f = std::exp(-log_norm);
+        if (!gate || norm2 == 1.0) return;
+        const double f = 1.0 / std::sqrt(norm2);
         double U[8];
         for (int i = 0; i < 8; ++i) U[i] = f * gate->U[i];
         TileGate &r = pc.gates[record];
@@ -769,7 +787,7 @@ constexpr int kMinPhaseRun = 4;
 
 static PassCode compile_pass(const TileSpec &sp, const std::vector<const Gate *> &gs, int sweep_w, bool f32,
                              const std::vector<const Probe *> *probes = nullptr, bool lph_f32 = false,
-                             int perm_bits = 0, int lds_bytes = 0) {
+                             int perm_bits = 0, int lds_bytes = 0, bool pack = true) {
     PassCode pc;
     // the tile pass exchanges one component at a time
     pc.lds_bytes = lds_bytes ? lds_bytes : (f32 ? 4 : 8);
@@ -779,7 +797,8 @@ static PassCode compile_pass(const TileSpec &sp, const std::vector<const Gate *>
     const int W = std::min(pc.m, sweep_w);
     // stores can permute where every thread of whole waves holds one group
     // (perm_bits: thread index bits of the kernel's workgroups, 0: never)
-    const bool perms = W == sweep_w && pc.m - W >= 6 && pc.m - W <= perm_bits;
+    const bool perms = W == sweep_w && pc.m - W >= 6 && pc.m - W <= perm_bits &&
+                       std::any_of(gs.begin(), gs.end(), [](const Gate *g) { return is_x(*g); });
     std::vector<int> qset;
     std::vector<size_t> cur;
     NormDrift drift;
@@ -1162,7 +1181,7 @@ static PassCode compile_pass(const TileSpec &sp, const std::vector<const Gate *>
         for (int i = 0; i < 2 << (2 * g->k); ++i) pc.finite = pc.finite && std::fabs(g->U[i]) <= (f32 ? FLT_MAX : DBL_MAX);
     }
     drift.settle(pc);
-    pack_records(pc, f32);
+    if (pack) pack_records(pc, f32);
     return pc;
 }
 
@@ -1447,7 +1466,7 @@ static int run_gates(sv_state *h, const std::vector<Gate> &gs, int mode) {
     // as soon as it is compiled, so that the device runs it while the host
     // prepares the next (depth 20 at 29 qubits complex64, 5 ms of scheduling
     // and compiling: 62.8 -> 61.2 ms; depth 40 in FP32 blocks of 5 at 28
-    // qubits, 30 ms: 79.9 -> 53.2 ms).
+    // qubits, 30 ms: 79.9 -> 53.2 ms; with the later kernels 36 and 36).
     const bool each = lookahead_level(h) > 0;
     struct Ready {
         PassCode code;
@@ -1505,7 +1524,8 @@ static int run_gates(sv_state *h, const std::vector<Gate> &gs, int mode) {
         int rc;
         if (each && (rc = launch_ready())) return rc;
     }
-    return launch_ready();
+    const int rc = launch_ready();
+    return rc ? rc : room.done(h);
 }
 
 
@@ -1817,7 +1837,6 @@ struct FusedPass {
     int engine = SV_PREC_NATIVE;
     uint32_t direct = 0; // kDirectFirst / kDirectLast (matrix cores)
     uint64_t moves = 0;  // qubits of its blocks
-    bool finite = true;  // every matrix entry is, in FP32
     std::vector<DenseBlock> blocks;
     // per block, its padded matrix for each variant of its outside qubits
     std::vector<std::vector<std::vector<std::complex<double>>>> mats;
@@ -1931,8 +1950,6 @@ static FusedPass build_fused_pass(const sv_state *h, const TileSpec &sp, const s
         std::vector<std::vector<std::complex<double>>> vs;
         for (const auto &M : B.var.empty() ? std::vector<std::vector<std::complex<double>>>{B.M} : B.var)
             vs.push_back(B.k == fp.k ? M : pad_matrix(M, B.k, fp.k));
-        for (const auto &M : vs)
-            for (const auto &z : M) fp.finite = fp.finite && std::abs(z.real()) <= FLT_MAX && std::abs(z.imag()) <= FLT_MAX;
         fp.mats.push_back(std::move(vs));
         fp.flops_per_amp += 8.0 * (double)(1 << B.k);
     }
@@ -1974,13 +1991,20 @@ static std::vector<FusedPass> compile_fused(const sv_state *h, const std::vector
 // a plain pass its records' vector operations on top of a share for its
 // loads, stores and exchanges, at least the time of its trip of the state.
 // It only ranks the alternatives of one pass.
+//
+// Split-BF16 calls rank theirs by the model fitted to the first kernels, on
+// the records without permuted stores.  A block's operands there are rounded
+// to 2^-17, a plain pass's to 2^-24, so the ranking decides the result from
+// its fifth digit on: it has to follow from the gates, not from how fast the
+// plain sweeps have become.  The present figures would gain them nothing on
+// the 28-qubit fusion workload (31.4 and 31.5 ms; 3.08 and 2.84 at 24 qubits).
 static double fused_pass_cost(const sv_state *h, const FusedPass &fp) {
     const bool c64 = h->dtype == SV_C64;
-    double t = c64 ? (fp.engine == SV_PREC_FP32 ? 3.0 : 3.6) : 6.5;
+    double t = c64 ? (fp.engine == SV_PREC_FP32 ? 3.0 : 3.4) : 6.5;
     for (const DenseBlock &db : fp.blocks) {
         const int k = db.bp.k;
         switch (fp.engine) {
-        case SV_PREC_SPLIT_BF16: t += k <= 4 ? 0.42 : 0.8; break;
+        case SV_PREC_SPLIT_BF16: t += k <= 4 ? 0.34 : 0.65; break;
         case SV_PREC_FP32: t += k <= 4 ? 0.93 : 2.2; break;
         case kPrecMfma64: t += k <= 4 ? 1.5 : 3.2; break;
         default: t += c64 ? 0.12 * (1 << k) : 0.25 * (1 << k); break; // vector ALUs
@@ -1989,8 +2013,8 @@ static double fused_pass_cost(const sv_state *h, const FusedPass &fp) {
     return t;
 }
 
-static double plain_pass_cost(const sv_state *h, const PassCode &pc) {
-    double valu = 0.0;
+static double plain_pass_cost(const sv_state *h, const PassCode &pc, int prec) {
+    double valu = 0.0, entries = 0.0;
     const int D = 1 << std::min(pc.m, kSweepW);
     for (const TileGate &r : pc.gates) {
         const int en = __builtin_popcount(r.amask);
@@ -2000,13 +2024,15 @@ static double plain_pass_cost(const sv_state *h, const PassCode &pc) {
         case SK_SWAP: valu += 2 * en; break;
         case SK_DIAG: case SK_DIAGR: valu += 8 + 4 * en; break;
         case SK_2Q: valu += 64 * en; break;
-        case SK_PHASE: valu += 6 + 6 * r.b1; break;
-        case SK_PTAB: valu += 6 + 6 * r.b1; break;
-        case SK_LPH: valu += 6 + 8 * r.b1; break;
+        case SK_PHASE: valu += 6 + 6 * r.b1; entries += r.b1; break;
+        case SK_PTAB: valu += 6 + 6 * r.b1; entries += r.b1; break;
+        case SK_LPH: valu += 6 + 8 * r.b1; entries += r.b1; break;
         case SK_FLUSH: valu += 4.0 * D * __builtin_popcount(r.amask); break;
         default: break;
         }
     }
+    if (prec == SV_PREC_SPLIT_BF16)
+        return 1.31 + 0.58 * (double)pc.sweeps.size() + 0.057 * (double)pc.gates.size() + 0.017 * entries + 4.4e-5 * valu;
     return h->dtype == SV_C64 ? std::max(3.1, 1.5 + 1.18e-3 * valu) : std::max(6.2, 3.0 + 2.4e-3 * valu);
 }
 
@@ -2071,9 +2097,14 @@ static int compile_fused_gates(const sv_state *h, const std::vector<Gate> &gs, i
             fp.plain = true;
             fp.sp = sp;
             fp.m = mtile;
-            fp.code = compile_pass(sp, ptrs, kSweepW, h->dtype == SV_C64, nullptr, true, kGroupBits);
-            fp.cost = plain_pass_cost(h, fp.code);
+            const bool f32 = h->dtype == SV_C64;
+            // packed only if it is chosen
+            fp.code = compile_pass(sp, ptrs, kSweepW, f32, nullptr, true, kGroupBits, 0, false);
+            // without X gates no store permutes
+            const bool as_fitted = prec == SV_PREC_SPLIT_BF16 && std::any_of(local.begin(), local.end(), is_x);
+            fp.cost = plain_pass_cost(h, as_fitted ? compile_pass(sp, ptrs, kSweepW, f32, nullptr, true, 0, 0, false) : fp.code, prec);
             if (fp.cost < best.cost) {
+                pack_records(fp.code, f32);
                 best = std::move(fp);
                 best_blocks = 0;
             }
@@ -2172,10 +2203,19 @@ static void stage_fused(sv_state *h, FusedPass &fp, size_t off) {
     std::memcpy(h->h_arena + off, fp.blocks.data(), fp.blocks.size() * sizeof(DenseBlock));
 }
 
+// Every matrix entry is finite, in FP32.
+static bool finite_blocks(const FusedPass &fp) {
+    bool ok = true;
+    for (const auto &vs : fp.mats)
+        for (const auto &M : vs)
+            for (const auto &z : M) ok &= (std::fabs(z.real()) <= FLT_MAX) & (std::fabs(z.imag()) <= FLT_MAX);
+    return ok;
+}
+
 static int launch_fused(sv_state *h, const FusedPass &fp, size_t off) {
     if (fp.plain) return launch_pass(h, fp.code, off);
     Timed tm(h, K_FUSED, 2.0 * state_bytes(h), fp.flops_per_amp * (double)(1ull << h->n));
-    const uint32_t zeros = fp.finite && untouched_outside(h, fp.sp) ? kSkipZero : 0u;
+    const uint32_t zeros = untouched_outside(h, fp.sp) && finite_blocks(fp) ? kSkipZero : 0u;
     SV_HIP(launch_dense_pass(h->amps, h->n, h->dtype, fp.sp, fp.k,
                              reinterpret_cast<const DenseBlock *>(h->d_arena + off), (int)fp.blocks.size(),
                              h->d_arena, fp.engine, fp.direct | zeros, h->stream));
@@ -2209,10 +2249,11 @@ static int run_fused_passes(sv_state *h, std::vector<FusedPass> &fps, ArenaRoom 
 static int run_fused_gates(sv_state *h, const std::vector<Gate> &gs, int k_max, int prec, int *n_blocks) {
     ArenaRoom room;
     std::vector<FusedPass> ready(1);
-    return compile_fused_gates(h, gs, k_max, prec, n_blocks, [&](FusedPass fp) -> int {
+    const int rc = compile_fused_gates(h, gs, k_max, prec, n_blocks, [&](FusedPass fp) -> int {
         ready[0] = std::move(fp);
         return run_fused_passes(h, ready, room);
     });
+    return rc ? rc : room.done(h);
 }
 
 static int parse_ops(const sv_state *h, int n, const sv_op *ops, int n_ops, const double *params,

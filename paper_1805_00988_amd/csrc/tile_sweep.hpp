@@ -1,17 +1,19 @@
 // Applying a run of gates to a tile of amplitudes staged in LDS.
 //
-// A tile holds 2^m amplitudes (local index l, m <= 13).  The gates of a pass
+// A tile holds 2^m amplitudes (local index l, m <= 14).  The gates of a pass
 // are grouped by the host into sweeps: a sweep names W = 4 local qubit
 // positions and a list of gates whose targets lie among them (diagonal
 // gates may target any tile position).  For each sweep every thread takes
 // groups of 2^W amplitudes that differ only in those positions, holds them
-// in registers, applies the sweep's gates in order and writes them back, so
-// the tile crosses LDS once per sweep instead of once per gate.
+// in registers, applies the sweep's gates in order and hands them to the next
+// sweep through LDS, so the tile crosses LDS once per sweep instead of once
+// per gate (a pass's first sweep reads the state and its last writes it).
 //
-// LDS addresses are swizzled (lds_swizzle): positions within one 128-byte
-// LDS row (16 complex64 or 8 complex128 amplitudes) are XOR-ed with a fold of
-// the row index, so the lanes of a wave, whose groups differ in arbitrary
-// tile bits, spread over the banks.
+// A sweep's addresses come from the host as columns to XOR (TileSweep), the
+// LDS ones already swizzled.  tile_load and tile_store, of the fused passes,
+// swizzle as they go (lds_swizzle): positions within one 128-byte LDS row
+// (16 complex64 or 8 complex128 amplitudes) are XOR-ed with a fold of the row
+// index.
 #pragma once
 
 #include "sv_internal.hpp"
