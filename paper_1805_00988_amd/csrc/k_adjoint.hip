@@ -6,8 +6,8 @@
 // M a 2x2 "probe": the Pauli of a rotation, or the projector |1><1| of the
 // phase gate) the gradient term 2 Re <lam| U' |psi_before> equals a real
 // multiple of Im <lam| M |psi_after>, evaluated on the vectors before the
-// gate is undone.  The sweep runs as tile passes over both vectors staged in
-// LDS; each probe's FP64 partial sums go to one slot per gate.
+// gate is undone.  The sweep runs as tile passes over both vectors; each
+// probe's FP64 partial sums go to one slot per gate.
 #include "sv_internal.hpp"
 #include "tile_sweep.hpp"
 
@@ -155,13 +155,14 @@ hipError_t launch_adjoint_init(const void *psi, void *lam, int n, int dtype, int
 }
 
 // ------------------------------------------------------ tiled reverse sweep
-// Both vectors of a tile sit in LDS; each register sweep loads the same group
-// of psi and lam and undoes the sweep's gates on both.  A parametrised gate
+// A thread holds the same register group of psi and lam for the whole pass,
+// exchanged through LDS between sweeps one component of one vector at a time,
+// and undoes each sweep's gates on both.  A parametrised gate
 // is preceded by a probe record that adds the group's share of
 // Im <lam| M |psi> to the gate's slot (wave reduction, then lane 0 adds it
 // to its wave's row of slots).  The slot sums of a workgroup cover all its
 // tiles and are written once at the end.
-int adjoint_tile_qubits(int dtype) { return dtype == SV_C64 ? 12 : 11; } // 2 x 32 KiB of LDS
+int adjoint_tile_qubits(int dtype) { return dtype == SV_C64 ? 12 : 11; } // one group per thread
 
 // Re(conj(y) z) in FP64
 template <typename T>
