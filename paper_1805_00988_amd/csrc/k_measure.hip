@@ -220,7 +220,7 @@ __global__ __launch_bounds__(kPrefixThreads) void k_run_prefix(const double *__r
         double c = 0.0;
         run[0] = 0.0;
 #pragma unroll 32
-        for (int i = 1; i <= kPrefixThreads; ++i) {
+        for (int i = 1; i <= (n_runs + kPrefixRuns - 1) / kPrefixRuns; ++i) { // the threads that hold runs
             c += run[i];
             run[i] = c;
         }
