@@ -162,7 +162,9 @@ hipError_t launch_adjoint_init(const void *psi, void *lam, int n, int dtype, int
 // Im <lam| M |psi> to the gate's slot (wave reduction, then lane 0 adds it
 // to its wave's row of slots).  The slot sums of a workgroup cover all its
 // tiles and are written once at the end.
-int adjoint_tile_qubits(int dtype) { return dtype == SV_C64 ? 12 : 11; } // one group per thread
+static_assert(1 << (adjoint_tile_qubits(SV_C64) - 4) == kAdjThreads &&
+                  1 << (adjoint_tile_qubits(SV_C128) - 3) == kAdjThreads,
+              "one group per thread of sweep_width registers");
 
 // Re(conj(y) z) in FP64
 template <typename T>

@@ -449,8 +449,9 @@ constexpr int kTileThreads = std::is_same<T, float>::value ? 1024 : 512;
 // random circuits and QFTs from 13 to 27 qubits.  The batch kernel keeps
 // 8192-amplitude complex64 tiles (whole circuits of up to 13 qubits in one
 // workgroup).
-int tile_max_qubits(int dtype) { return dtype == SV_C64 ? 14 : 13; }
-int batch_tile_qubits(int dtype) { return dtype == SV_C64 ? 13 : 12; }
+static_assert(1 << (tile_max_qubits(SV_C64) - kSweepW) == kTileThreads<float> &&
+                  1 << (tile_max_qubits(SV_C128) - kSweepW) == kTileThreads<double>,
+              "one group per thread");
 
 // Register qubits per sweep of the batch and adjoint kernels, which hold 8
 // complex128 amplitudes per group.  The tile pass holds 16 (kSweepW) in both

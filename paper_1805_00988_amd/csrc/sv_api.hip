@@ -398,27 +398,6 @@ static size_t record_payload(const TileGate &r, bool f32) {
 
 static uint64_t tile_global_offset(const TileSpec &sp, uint32_t l);
 
-// LDS layout of the sweeps' exchanges: the index bits within one row of the
-// 64 banks (64, 32 or 16 entries of 4, 8 or 16 bytes) are XOR-ed with a fixed
-// linear function of the higher bits, one constant per bit.  The constants
-// are the best of a random search over all sets of 4 (16 bytes: 3) register
-// positions in a 12-bit tile, by the cycles that lanes 0 to 31 (16 bytes: 15)
-// take in a model of the banks: 1.03, 1.25 and 1.14 on average, 2 at worst.
-// The columns are the host's, so any linear function costs the same; folds by
-// shifts of the index, which the kernels could compute, gave 1.6 for 8 bytes
-// (conflict cycles 14 % of a complex128 pass's busy cycles before, 3 % now).
-static uint32_t sweep_swizzle(uint32_t l, int bytes) {
-    static const uint8_t k4[] = {0x3e, 0x39, 0x0d, 0x0e, 0x1c, 0x22, 0x12};
-    static const uint8_t k8[] = {0x1d, 0x0b, 0x1a, 0x0e, 0x1a, 0x10, 0x19, 0x0d};
-    static const uint8_t k16[] = {0x0f, 0x0a, 0x0d, 0x05, 0x00, 0x02, 0x0d, 0x0a, 0x09};
-    const uint8_t *k = bytes == 4 ? k4 : bytes == 8 ? k8 : k16;
-    const int row = bytes == 4 ? 6 : bytes == 8 ? 5 : 4;
-    uint32_t r = l;
-    for (int i = 0; l >> (row + i); ++i)
-        if ((l >> (row + i)) & 1u) r ^= k[i];
-    return r;
-}
-
 // Address columns of a sweep (TileSweep), its results permuted by the
 // sweep's X gates; the conditional constants follow the records.
 static void sweep_addresses(PassCode &pc, size_t si) {

@@ -9,6 +9,7 @@
 #include <string>
 
 #include "../../include/sv.h"
+#include "lds_layout.hpp"
 
 namespace sv {
 
@@ -271,8 +272,6 @@ hipError_t launch_tile(void *amps, int n, int dtype, const TileSpec &spec, const
 // first block read the state and the last block write it without staging the
 // tile in LDS; kSkipZero: test the tile for zeros in the first block.
 constexpr uint32_t kDirectFirst = 1, kDirectLast = 2, kSkipZero = 4;
-int tile_max_qubits(int dtype);
-int batch_tile_qubits(int dtype);
 int sweep_width(int dtype);
 // Dense blocks of a fused tile pass: positions of the block's qubits in the
 // tile (bit j of the matrix index <-> qpos[j]) and of the remaining tile bits
@@ -423,7 +422,6 @@ hipError_t launch_adjoint_tile(void *psi, void *lam, int n, int dtype, const Til
                                const TileSweep *dev_sweeps, int n_sweeps, const char *dev_recs, size_t bytes,
                                int slot0, int n_slots, double *partials, int n_blocks, bool two_qubit,
                                hipStream_t s);
-int adjoint_tile_qubits(int dtype);
 constexpr int kMaxAdjSlots = 128;
 
 } // namespace sv
