@@ -691,9 +691,6 @@ static void phase_windows(const std::vector<PhaseEntry> &ents, std::vector<Phase
     }
 }
 
-// Group the pass's gates (in order) into sweeps of at most W register
-// qubits; diagonal one-qubit gates join the current sweep whatever their
-// target, since they act per amplitude.
 // Probe of a parametrised gate in an adjoint pass: slot within the pass and
 // the 2x2 probe matrix (complex, interleaved).
 struct Probe {
@@ -719,29 +716,42 @@ static TileGate encode_probe(const TileSpec &sp, const std::vector<int> &qset, c
     return r;
 }
 
-// Group the pass's gates (in order) into sweeps of at most W register
-// qubits; diagonal one-qubit gates join the current sweep whatever their
-// target, since they act per amplitude.  With probes (adjoint passes), a
-// parametrised gate needs its target in registers and is encoded as a probe
-// record followed by its own record.
 // FP32 entries of a gate make it longer or shorter by up to 2^-25 relative,
 // the same way each time the gate is applied (sqrt(1/2) by 1.7e-8), which
 // was most of a deep complex64 circuit's error.  The pass's last full
-// one-qubit gate is scaled back by the product before it is rounded.
+// one-qubit gate is scaled back by the product before it is rounded.  Only
+// what a gate does to the norm of every state alike is taken back: diag(0.5,
+// 0.7), of which only the second entry rounds, leaves amplitudes of target 0
+// exact, and diag(e^ia, 1) those of target 1.
 struct NormDrift {
     double norm2 = 1.0;         // the square of the factor by which the entries move the norm
-    const Gate *gate = nullptr; // the last such gate and its record
+    const Gate *gate = nullptr; // the last unitary gate and its record
     size_t record = 0;
+    // U^+ U for columns (a, c) and (b, d): its diagonal and its upper entry
+    static void gram(const std::complex<double> (&u)[4], double *n0, double *n1, double *cross) {
+        *n0 = std::norm(u[0]) + std::norm(u[2]);
+        *n1 = std::norm(u[1]) + std::norm(u[3]);
+        *cross = std::abs(std::conj(u[0]) * u[1] + std::conj(u[2]) * u[3]);
+    }
     void add(const Gate &g, size_t rec, bool f32) {
         if (!f32 || g.k != 1 || g.ctrl != 0 || is_x(g) || (is_diag1(g) && is_one(g.U))) return;
-        double exact = 0.0, rounded = 0.0;
-        for (int i = 0; i < 8; ++i) {
-            const double r = (float)g.U[i];
-            exact += g.U[i] * g.U[i];
-            rounded += r * r;
+        std::complex<double> u[4], r[4];
+        for (int i = 0; i < 4; ++i) {
+            u[i] = {g.U[2 * i], g.U[2 * i + 1]};
+            r[i] = {(float)g.U[2 * i], (float)g.U[2 * i + 1]};
         }
-        if (!(exact > 1e-30 && exact < 1e30 && rounded > 0.0)) return;
-        norm2 *= rounded / exact;
+        double n0, n1, cross;
+        gram(u, &n0, &n1, &cross);
+        // unitary but for a factor
+        const double tol = 1e-12 * (n0 + n1);
+        if (!(n0 > 1e-30 && n0 < 1e30) || std::fabs(n0 - n1) > tol || cross > tol) return;
+        double r0, r1, rc;
+        gram(r, &r0, &r1, &rc);
+        // the rounded gate moves squared norms by lo to hi
+        const double mid = 0.5 * (r0 + r1) / n0, half = std::hypot(0.5 * (r0 - r1), rc) / n0;
+        const double lo = mid - half, hi = mid + half;
+        if (!(lo > 0.5 && hi < 2.0)) return;
+        norm2 *= lo > 1.0 ? lo : hi < 1.0 ? hi : 1.0;
         gate = &g;
         record = rec;
     }
@@ -764,6 +774,11 @@ struct NormDrift {
 // about as much as applying three of them one by one)
 constexpr int kMinPhaseRun = 4;
 
+// Group the pass's gates (in order) into sweeps of at most W register
+// qubits; diagonal one-qubit gates join the current sweep whatever their
+// target, since they act per amplitude.  With probes (adjoint passes), a
+// parametrised gate needs its target in registers and is encoded as a probe
+// record followed by its own record.
 static PassCode compile_pass(const TileSpec &sp, const std::vector<const Gate *> &gs, int sweep_w, bool f32,
                              const std::vector<const Probe *> *probes = nullptr, bool lph_f32 = false,
                              int perm_bits = 0, int lds_bytes = 0, bool pack = true) {
