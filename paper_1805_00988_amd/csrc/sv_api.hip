@@ -2007,6 +2007,9 @@ static double fused_pass_cost(const sv_state *h, const FusedPass &fp) {
     return t;
 }
 
+// Blocks of a complex128 register are FP64, whatever the call asks for.
+static bool bf16_blocks(const sv_state *h, int prec) { return prec == SV_PREC_SPLIT_BF16 && h->dtype == SV_C64; }
+
 static double plain_pass_cost(const sv_state *h, const PassCode &pc, int prec) {
     double valu = 0.0, entries = 0.0;
     const int D = 1 << std::min(pc.m, kSweepW);
@@ -2025,7 +2028,7 @@ static double plain_pass_cost(const sv_state *h, const PassCode &pc, int prec) {
         default: break;
         }
     }
-    if (prec == SV_PREC_SPLIT_BF16)
+    if (bf16_blocks(h, prec))
         return 1.31 + 0.58 * (double)pc.sweeps.size() + 0.057 * (double)pc.gates.size() + 0.017 * entries + 4.4e-5 * valu;
     return h->dtype == SV_C64 ? std::max(3.1, 1.5 + 1.18e-3 * valu) : std::max(6.2, 3.0 + 2.4e-3 * valu);
 }
@@ -2095,7 +2098,7 @@ static int compile_fused_gates(const sv_state *h, const std::vector<Gate> &gs, i
             // packed only if it is chosen
             fp.code = compile_pass(sp, ptrs, kSweepW, f32, nullptr, true, kGroupBits, 0, false);
             // without X gates no store permutes
-            const bool as_fitted = prec == SV_PREC_SPLIT_BF16 && std::any_of(local.begin(), local.end(), is_x);
+            const bool as_fitted = bf16_blocks(h, prec) && std::any_of(local.begin(), local.end(), is_x);
             fp.cost = plain_pass_cost(h, as_fitted ? compile_pass(sp, ptrs, kSweepW, f32, nullptr, true, 0, 0, false) : fp.code, prec);
             if (fp.cost < best.cost) {
                 pack_records(fp.code, f32);
