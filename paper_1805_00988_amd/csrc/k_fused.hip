@@ -395,7 +395,10 @@ __device__ __forceinline__ uint32_t apply_block_t(cpx<typename EngCfg<ENG, K>::T
 }
 
 // ZSKIP (kSkipZero): a tile whose operands the first block found to be all
-// zero is left as it is; the first block's results, in LDS, are dropped.
+// zero is left as it is; the first block's results, in LDS, are dropped.  The
+// waves' findings are read behind the barrier that ends the block anyway: a
+// dense register pays 1 % of its passes for the test (2 to 4 with a barrier
+// more).
 // While a register spreads from a basis state most tiles are zeros: depth 40
 // at 28 qubits in split-BF16 blocks, 37.4 -> 33.4 ms.
 template <int ENG, int K, bool ZSKIP>
@@ -405,14 +408,19 @@ __global__ __launch_bounds__((EngCfg<ENG, K>::threads)) void k_dense_mfma(
     using Cf = EngCfg<ENG, K>;
     using T = typename Cf::T;
     extern __shared__ char lds_raw[];
-    __shared__ uint32_t seen[ZSKIP ? Cf::threads / 64 : 1];
     cpx<T> *lds = reinterpret_cast<cpx<T> *>(lds_raw);
     cpx<T> *state = reinterpret_cast<cpx<T> *>(v);
     const uint32_t tsize = 1u << m;
+    // ZSKIP: a word per wave behind the tile, whether its operands hold
+    // anything, and as many for the next tile, in turn: a wave may start on it
+    // before another has read this one's
+    uint32_t *seen = reinterpret_cast<uint32_t *>(lds + tsize);
     const uint32_t n_wt = (tsize >> K) / Cf::rows;
-    const int wave = wave_id(), nwaves = Cf::threads / 64;
+    constexpr int nwaves = Cf::threads / 64;
+    const int wave = wave_id();
     const bool dfirst = direct & kDirectFirst, dlast = direct & kDirectLast;
-    for (uint64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+    uint32_t turn = 0;
+    for (uint64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x, turn ^= (uint32_t)nwaves) {
         const uint64_t base = tile_base(sp, tile);
         if (!dfirst) {
             tile_load<T, Cf::threads, 8>(v, lds, sp, base, tsize);
@@ -432,17 +440,17 @@ __global__ __launch_bounds__((EngCfg<ENG, K>::threads)) void k_dense_mfma(
                                                                                nwaves);
                 if constexpr (ZSKIP) {
                     const uint32_t any = wave_zero(bits) ? 0u : 1u;
-                    if ((threadIdx.x & 63u) == 0u) seen[wave] = any;
-                    __syncthreads();
-                    uint32_t tile_any = 0;
-                    for (int w = 0; w < nwaves; ++w) tile_any |= seen[w];
-                    zero = __builtin_amdgcn_readfirstlane(tile_any) == 0u;
+                    if ((threadIdx.x & 63u) == 0u) seen[turn | (uint32_t)wave] = any;
                 }
             } else if (dg) apply_block_t<ENG, K, false, true>(lds, state, base, op, t, n_wt, wave, nwaves);
             else apply_block_t<ENG, K, false, false>(lds, state, base, op, t, n_wt, wave, nwaves);
             // the next block (or the next tile's first LDS writes) follows
             // every wave's reads of this one
             __syncthreads();
+            if constexpr (ZSKIP) {
+                static_assert((nwaves & (nwaves - 1)) == 0, "lanes read the waves' words over and over");
+                if (sg && !dg) zero = wave_zero(seen[turn | (threadIdx.x & (nwaves - 1))]);
+            }
         }
         if (!dlast) {
             tile_store<T, Cf::threads, 8>(v, lds, sp, base, tsize);
@@ -470,15 +478,15 @@ hipError_t launch_dense_pass(void *amps, int n, int dtype, const TileSpec &sp, i
 #define SV_MFMA_CASE(ENG, KK)                                                                      \
     if (prec == ENG && k == KK) {                                                                  \
         using VT = typename Amp16<typename EngCfg<ENG, KK>::T>::type;                              \
-        auto launch = [&](auto kernel) {                                                           \
-            (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, \
-                                      (int)lds);                                                   \
-            kernel<<<grid, EngCfg<ENG, KK>::threads, lds, s>>>((VT *)amps, sp, m, dev_blocks, n_blocks, \
-                                                               dev_base, n_tiles, direct);         \
+        auto launch = [&](auto kernel, size_t words) {                                             \
+            const size_t b = lds + words * sizeof(uint32_t);                                       \
+            (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)b); \
+            kernel<<<grid, EngCfg<ENG, KK>::threads, b, s>>>((VT *)amps, sp, m, dev_blocks, n_blocks, \
+                                                             dev_base, n_tiles, direct);           \
         };                                                                                         \
         const uint32_t z = kSkipZero | kDirectFirst | kDirectLast;                                 \
-        if ((direct & z) == z) launch(k_dense_mfma<ENG, KK, true>);                                \
-        else launch(k_dense_mfma<ENG, KK, false>);                                                 \
+        if ((direct & z) == z) launch(k_dense_mfma<ENG, KK, true>, 2 * (EngCfg<ENG, KK>::threads / 64)); \
+        else launch(k_dense_mfma<ENG, KK, false>, 0);                                              \
         return hipGetLastError();                                                                  \
     }
         SV_MFMA_CASE(SV_PREC_SPLIT_BF16, 4)

@@ -475,9 +475,9 @@ constexpr int kTileWaves = std::is_same<T, double>::value ? 4 : 8;
 // one register group per thread.
 //
 // ZSKIP: a tile of zeros is left as it is (see launch_tile).  Each wave
-// reports the magnitude bits of its groups in the first words of the tile's
-// LDS, which nothing else uses before the first sweep stores its groups
-// there.
+// reports whether its groups hold anything, and the waves look at all reports
+// after the first barrier of the first exchange, where they meet anyway; a
+// wave of zeros walks no records until then.
 template <typename T, int W, bool TWOQ, bool LPH, bool ZSKIP>
 __global__ __launch_bounds__(kTileThreads<T>, kTileWaves<T>) void k_tile(typename Vec<T>::type *vec, TileSpec sp,
                                                                       const TileSweep *__restrict__ sweeps,
@@ -499,32 +499,46 @@ __global__ __launch_bounds__(kTileThreads<T>, kTileWaves<T>) void k_tile(typenam
 #pragma unroll
         for (int j = 0; j < D; ++j) v[j] = row[register_columns<W>(S.at_reg, j)];
     }
+    bool zero = false;
+    // ZSKIP: a word per wave behind the tile, whether its groups hold anything
+    uint32_t *seen = reinterpret_cast<uint32_t *>(lds + blockDim.x * D * (uint32_t)sizeof(T));
     if constexpr (ZSKIP) {
-        uint32_t bits = 0;
+        // the first amplitudes settle it for a register that is not sparse
+        zero = wave_zero(magnitude_bits(v[0].re) | magnitude_bits(v[0].im));
+        if (zero) {
+            uint32_t bits = 0;
 #pragma unroll
-        for (int j = 0; j < D; ++j) bits |= magnitude_bits(v[j].re) | magnitude_bits(v[j].im);
-        volatile uint32_t *seen = reinterpret_cast<volatile uint32_t *>(lds);
-        const uint32_t wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
-        const uint32_t any = wave_zero(bits) ? 0u : 1u;
-        if ((threadIdx.x & 63u) == 0u) seen[wave] = any;
-        __syncthreads();
-        uint32_t tile_any = 0;
-        for (uint32_t w = 0; w < n_waves; ++w) tile_any |= seen[w];
-        __syncthreads(); // the words are read before the tile is written over them
-        if (__builtin_amdgcn_readfirstlane(tile_any) == 0u) return;
+            for (int j = 1; j < D; ++j) bits |= magnitude_bits(v[j].re) | magnitude_bits(v[j].im);
+            zero = wave_zero(bits);
+        }
+        if ((threadIdx.x & 63u) == 0u) seen[threadIdx.x >> 6] = zero ? 0u : 1u;
     }
+    // behind a barrier: no wave of the tile's has seen anything (their number
+    // is a power of two; a branch on the lane in the loop below would have the
+    // compiler copy the groups, and an address formed before it a register)
+    auto tile_zero = [&]() {
+        uint32_t t = g;
+        asm volatile("" : "+v"(t));
+        return wave_zero(seen[t & ((blockDim.x >> 6) - 1u)]);
+    };
     for (int si = 0;; ++si) {
         const TileSweep &S = sweeps[si];
         PhaseAcc<T, W> acc;
         acc.init();
-        run_records<T, W, TWOQ, LPH>(v, acc, g, recs + S.rec_off, S.n_gates, base);
+        run_records<T, W, TWOQ, LPH>(v, acc, g, recs + S.rec_off, ZSKIP && si == 0 && zero ? 0 : S.n_gates, base);
         if (si == n_sweeps - 1) break;
         const TileSweep &N = sweeps[si + 1];
-        const uint32_t pg = out_constant(S, recs, base) ^ group_columns(S.out_lane, g);
+        uint32_t pg = out_constant(S, recs, base) ^ group_columns(S.out_lane, g);
         const uint32_t pn = group_columns(N.in_lane, g);
         // the real parts, then the imaginary parts
         lds_store_part<T, W, 0>(lds, pg, S.out_reg, v);
         __syncthreads();
+        if constexpr (ZSKIP) {
+            if (si == 0 && tile_zero()) return;
+            // the imaginary parts' addresses are formed anew: kept across the
+            // exit they spill (complex64)
+            asm volatile("" : "+v"(pg));
+        }
         lds_load_part<T, W, 0>(lds, pn, N.in_reg, v);
         __syncthreads();
         lds_store_part<T, W, 1>(lds, pg, S.out_reg, v);
@@ -537,11 +551,17 @@ __global__ __launch_bounds__(kTileThreads<T>, kTileWaves<T>) void k_tile(typenam
     const TileSweep &S = sweeps[n_sweeps - 1];
     if (S.perm) {
         // other groups' places, once every group has been read
-        if (n_sweeps == 1) __syncthreads();
+        if (n_sweeps == 1) {
+            __syncthreads();
+            if constexpr (ZSKIP) {
+                if (tile_zero()) return;
+            }
+        }
         const uint64_t to = to_constant(S, recs, base) ^ group_columns(S.to_lane, g);
 #pragma unroll
         for (int j = 0; j < D; ++j) tile[to ^ register_columns<W>(S.to_reg, j)] = v[j];
     } else {
+        if (ZSKIP && n_sweeps == 1 && zero) return; // a group's results go where it was read
         cpx<T> *row = tile + group_columns(S.to_lane, g);
 #pragma unroll
         for (int j = 0; j < D; ++j) row[register_columns<W>(S.to_reg, j)] = v[j];
@@ -563,6 +583,7 @@ static void launch_tile_t(typename Vec<T>::type *v, const TileSpec &spec, int m,
     constexpr bool FULL = W == kSweepW;
     if constexpr (FULL) {
         if (skip_zero && threads >= 64) {
+            lds += threads / 64 * sizeof(uint32_t);
             launch(k_tile<T, W, TWOQ, LPH, true>);
             return;
         }
@@ -577,11 +598,15 @@ static void launch_tile_t(typename Vec<T>::type *v, const TileSpec &spec, int m,
 // On |x> at 30 qubits complex128 the QFT's first pass (phases conditioned on
 // 18 outside qubits) takes 4.6 ms instead of 18.4, its second and third
 // 2.7 and 3.2 instead of 7.0 and 7.2 (the whole circuit 43.1 -> 21.0 ms, on
-// tiles of 2^12; 18.9 on tiles of 2^13).  The test itself (a barrier per tile
-// before the first sweep's updates) made passes over a dense state up to 16 %
-// slower, so the host sets the flag only while some qubit outside the tile
-// has not been acted on since the register was set to a basis state
-// (sv_state::moved).
+// tiles of 2^12; on tiles of 2^13 18.9, and 18.1 since the test has no barrier
+// of its own).  On a dense register, which a caller may have written after it
+// was set to a basis state, the test costs nothing: ten rotations on 2^26
+// complex128 amplitudes take 0.417 ms with it and 0.420 without.  With a
+// barrier before the first sweep's updates, where every wave waited for the
+// last one's reads, they took 0.468 (layers of gates 1 to 5 % more, up to 16 %
+// on tiles of 2^12).  The host sets the flag only while some qubit outside the
+// tile has not been acted on since the register was set to a basis state
+// (sv_state::moved): later, a tile of zeros is no longer likely.
 hipError_t launch_tile(void *amps, int n, int dtype, const TileSpec &spec, const TileSweep *dev_sweeps,
                        int n_sweeps, const char *dev_gates, size_t bytes, bool two_qubit, bool lane_phases, bool skip_zero,
                        hipStream_t s) {
