@@ -190,10 +190,12 @@ enum sv_run_mode { SV_RUN_PER_GATE = 0, SV_RUN_TILED = 1 };
 int sv_run(sv_handle h, const sv_op *ops, int n_ops, const double *params, int n_params,
            int mode);
 
-/* The passes of sv_run's scheduler for a register of n_qubits of the given
- * dtype with tiles of 12 qubits (host only: no state, no device call; sv_run
- * itself forms passes by the same rules for tiles of 14 qubits, complex64,
- * or 13, complex128).  Gates apply in the
+/* The passes sv_run's tiled mode forms for a register of n_qubits of the
+ * given dtype (host only: no state, no device call).  tile_qubits 0 means
+ * sv_run's own tiles, of 14 qubits (SV_C64) or 13 (SV_C128) where the register
+ * has them; 7 (SV_C64) or 6 (SV_C128), the low block that every tile holds, up
+ * to these asks for the passes of the same scheduler on smaller tiles.  Gates
+ * apply in the
  * order of Sec. 2.3 (the ops in sequence); a pass may take a gate ahead of
  * gates left behind only when they share no qubit.  level 0 is the greedy
  * scheduler, 1 the lookahead, 2 the two-pass lookahead, -1 the level sv_run
@@ -201,9 +203,13 @@ int sv_run(sv_handle h, const sv_op *ops, int n_ops, const double *params, int n
  * the pass index of every op; pass_qubits (max_passes values) the qubit mask
  * of each pass's tile (bit q = qubit q), or 0 for a single gate sv_run
  * streams instead; *n_passes the pass count.  SV_EINVAL for n_qubits outside
- * [1, 40], an unknown dtype, level outside [-1, 2], NULL outputs, an invalid
- * op, or more passes than max_passes (then *n_passes still holds the
- * count). */
+ * [1, 40], an unknown dtype, tile_qubits or level outside their ranges, NULL
+ * outputs, an invalid op, or more passes than max_passes (then *n_passes still
+ * holds the count). */
+int sv_schedule_tile(int n_qubits, int dtype, int tile_qubits, const sv_op *ops, int n_ops, const double *params,
+                     int n_params, int level, int max_passes, int *gate_pass, uint64_t *pass_qubits, int *n_passes);
+
+/* sv_schedule_tile with tiles of 12 qubits. */
 int sv_schedule(int n_qubits, int dtype, const sv_op *ops, int n_ops, const double *params, int n_params,
                 int level, int max_passes, int *gate_pass, uint64_t *pass_qubits, int *n_passes);
 

@@ -218,20 +218,20 @@ def sv_run(h, gates, params=None, mode: int = SV_RUN_TILED) -> None:
     _lib.check(_lib.load().sv_run(h, _opptr(ops), len(gates), pp, n_p, int(mode)))
 
 
-def sv_schedule(n_qubits: int, dtype, gates, level: int = -1, params=None):
-    """The scheduler's passes on tiles of 12 qubits (host library, no GPU):
-    (pass index of every gate as an int array, list of each pass's tile-qubit
-    mask, 0 for a gate of its own that is streamed).  sv_run forms its passes
-    by the same rules on its own tiles, of 14 qubits in complex64 and 13 in
-    complex128."""
+def sv_schedule(n_qubits: int, dtype, gates, level: int = -1, params=None, tile_qubits: int = 12):
+    """The scheduler's passes on tiles of tile_qubits qubits (host library, no
+    GPU): (pass index of every gate as an int array, list of each pass's
+    tile-qubit mask, 0 for a gate of its own that is streamed).  tile_qubits
+    0 gives the passes that sv_run's tiled mode forms, on tiles of 14 qubits
+    in complex64 and 13 in complex128."""
     ops = ops_from_gates(gates)
     pp, n_p, keep = _params(params)
     cap = max(1, len(gates))
     gp = np.full(max(1, len(gates)), -1, np.int32)
     pq = np.zeros(cap, np.uint64)
     npass = ctypes.c_int()
-    _lib.check(_lib.load().sv_schedule(n_qubits, _dtype_code(dtype), _opptr(ops), len(gates), pp, n_p, int(level),
-                                       cap, _iptr(gp), _u64ptr(pq), ctypes.byref(npass)))
+    _lib.check(_lib.load().sv_schedule_tile(n_qubits, _dtype_code(dtype), int(tile_qubits), _opptr(ops), len(gates), pp,
+                                            n_p, int(level), cap, _iptr(gp), _u64ptr(pq), ctypes.byref(npass)))
     return gp[:len(gates)].copy(), [int(x) for x in pq[:npass.value]]
 
 

@@ -1442,7 +1442,6 @@ static bool needs_tile(int dtype, const Gate &g) {
 // Tile size and low block of sv_run's plain passes: runs of 128 complex64 /
 // 64 complex128 amplitudes (shorter runs cut the number of passes but cost
 // more per pass, measured).
-constexpr int kScheduleTile = 12; // sv_schedule's tiles
 static int plain_tile_qubits(int n, int dtype) { return std::min(n, tile_max_qubits(dtype)); }
 static int plain_low_qubits(int n, int dtype) { return std::min(n, dtype == SV_C64 ? 7 : 6); }
 
@@ -3059,17 +3058,20 @@ int sv_fuse(int n_qubits, const sv_op *ops, int n_ops, const double *params, int
     return SV_OK;
 }
 
-int sv_schedule(int n_qubits, int dtype, const sv_op *ops, int n_ops, const double *params, int n_params,
-                int level, int max_passes, int *gate_pass, uint64_t *pass_qubits, int *n_passes) {
+int sv_schedule_tile(int n_qubits, int dtype, int tile, const sv_op *ops, int n_ops, const double *params,
+                     int n_params, int level, int max_passes, int *gate_pass, uint64_t *pass_qubits, int *n_passes) {
     if (n_qubits < 1 || n_qubits > 40) return fail(SV_EINVAL, "n_qubits must be in [1, 40]");
     if (dtype != SV_C64 && dtype != SV_C128) return fail(SV_EINVAL, "dtype must be SV_C64 or SV_C128");
+    if (tile != 0 && (tile < plain_low_qubits(64, dtype) || tile > tile_max_qubits(dtype)))
+        return fail(SV_EINVAL, "tile_qubits must be 0 or hold the low block and fit sv_run's tiles");
     if (level < -1 || level > 2) return fail(SV_EINVAL, "level must be in [-1, 2]");
     if (!n_passes || max_passes < 0 || (n_ops > 0 && !gate_pass) || (max_passes > 0 && !pass_qubits))
         return fail(SV_EINVAL, "NULL output");
     std::vector<Gate> gs;
     int rc = parse_ops(nullptr, n_qubits, ops, n_ops, params, n_params, gs);
     if (rc) return rc;
-    const int mmax = std::min(n_qubits, kScheduleTile), lmin = plain_low_qubits(n_qubits, dtype);
+    const int mmax = tile ? std::min(n_qubits, tile) : plain_tile_qubits(n_qubits, dtype);
+    const int lmin = plain_low_qubits(n_qubits, dtype);
     const int lv = level < 0 ? lookahead_level_for(n_qubits, dtype) : level;
     const std::vector<Pass> passes = schedule(gs, n_qubits, mmax, lmin, true, lv);
     *n_passes = (int)passes.size();
@@ -3088,6 +3090,12 @@ int sv_schedule(int n_qubits, int dtype, const sv_op *ops, int n_ops, const doub
         pass_qubits[pi] = tiled ? tile_qubits(sp) : 0;
     }
     return SV_OK;
+}
+
+int sv_schedule(int n_qubits, int dtype, const sv_op *ops, int n_ops, const double *params, int n_params,
+                int level, int max_passes, int *gate_pass, uint64_t *pass_qubits, int *n_passes) {
+    return sv_schedule_tile(n_qubits, dtype, 12, ops, n_ops, params, n_params, level, max_passes, gate_pass, pass_qubits,
+                            n_passes);
 }
 
 int sv_run_fused(sv_handle h, const sv_op *ops, int n_ops, const double *params, int n_params,
