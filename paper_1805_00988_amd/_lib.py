@@ -9,10 +9,11 @@ from __future__ import annotations
 
 import ctypes
 import os
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libsv.so")
-PY_LIB_PATH = os.path.join(HERE, "libsvpy.so")
+PY_LIB_PATH = os.path.join(HERE, "libsvpy" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 
 SV_C64, SV_C128 = 1, 2
 SV_OK, SV_EINVAL, SV_ENOMEM, SV_EDEVICE, SV_EUNSUPPORTED = 0, -1, -2, -3, -4
@@ -124,7 +125,7 @@ _fill = None
 
 
 def fill_ops(gates, out_ptr: int, n: int) -> int:
-    """Records of n gates written at out_ptr by libsvpy.so: the number of
+    """Records of n gates written at out_ptr by the C helper: the number of
     gates that carry a matrix, -1 where the gates are not of the plain form
     (or the helper is not there): then the caller converts them."""
     global _fill

@@ -18,7 +18,8 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libsv.so")
-PY_OUT = os.path.join(HERE, "libsvpy.so")
+# uses the struct layouts of the interpreter that builds it: tagged with its ABI
+PY_OUT = os.path.join(HERE, "libsvpy" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 OBJ = os.path.join(HERE, "_build")
 ARCH = "gfx950"
 
@@ -100,10 +101,20 @@ def build(verbose: bool = False) -> str:
 
 
 def build_py() -> str:
-    """The binding's C helper (host code of the running interpreter's ABI)."""
+    """The binding's C helper (host code of the running interpreter's ABI).
+    Without the interpreter's headers or a C++ compiler there is none ('' is
+    returned, and an earlier one is removed): the binding then converts gate
+    lists in Python."""
+    include = sysconfig.get_paths()["include"]
+    cxx = shutil.which(os.environ.get("CXX") or "g++")
+    if cxx is None or not os.path.exists(os.path.join(include, "Python.h")):
+        print(f"note: {os.path.basename(PY_OUT)} is not built (no C++ compiler or no Python.h)", file=sys.stderr)
+        if os.path.exists(PY_OUT):
+            os.remove(PY_OUT)
+        return ""
     tmp = PY_OUT + ".tmp"
-    cmd = [os.environ.get("CXX") or "g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall",
-           "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "py_ops.cpp"), "-o", tmp]
+    cmd = [cxx, "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-I" + include, os.path.join(CSRC, "py_ops.cpp"),
+           "-o", tmp]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"building {PY_OUT} failed:\n{r.stdout}\n{r.stderr}")
