@@ -234,29 +234,32 @@ static int stage_wait(sv_state *h) {
 
 // Room in the arena for the passes that one call stages and launches part
 // by part, each at an offset of its own.  A part that does not fit gets a
-// larger arena and starts it anew, for which the stream is drained; without
-// memory for a larger one it starts the old one anew, so that a call that
-// has launched passes goes on.  At its end the call leaves an arena that
-// would have held all its parts, so that the same call again neither
-// allocates nor waits.
+// larger arena and starts it anew, for which the stream is drained.  Without
+// memory for that a part that fits the old one starts it anew, and another
+// gets an arena just large enough; without memory for this one either, *full
+// tells the caller to split the part, so that a call that has launched
+// passes goes on.  At its end the call leaves an arena that would have held
+// all its parts, so that the same call again neither allocates nor waits.
 struct ArenaRoom {
     size_t off = 0, sum = 0;
     bool fresh = true; // nothing staged by this call yet
-    int take(sv_state *h, size_t bytes, size_t *at) {
+    int take(sv_state *h, size_t bytes, size_t *at, bool *full) {
         int rc = SV_OK;
+        *full = false;
         if (off + bytes > h->arena_cap) {
             bool no_memory = false;
             rc = ensure_arena(h, std::max(off + bytes, h->arena_cap ? 4 * h->arena_cap : (size_t)1 << 20), &no_memory);
-            if (no_memory && bytes <= h->arena_cap) rc = SV_OK;
+            if (no_memory) rc = ensure_arena(h, bytes, full);
             off = 0;
         }
         // the host copy is free once the last call's upload has left it
         if (!rc && fresh) rc = stage_wait(h);
+        if (rc) return rc;
         fresh = false;
         *at = off;
         off += bytes;
         sum += bytes;
-        return rc;
+        return SV_OK;
     }
     int done(sv_state *h) {
         bool no_memory = false;
@@ -1462,62 +1465,95 @@ static int run_gates(sv_state *h, const std::vector<Gate> &gs, int mode) {
     // qubits, 30 ms: 79.9 -> 53.2 ms; with the later kernels 36 and 36).
     const bool each = lookahead_level(h) > 0;
     struct Ready {
+        std::vector<int> gates;
+        TileSpec sp;  // of a tiled pass
         PassCode code;
         bool tiled;
-        int single;   // the gate of an untiled pass
         size_t off;
     };
     std::vector<Ready> ready;
     ArenaRoom room;
-    auto launch_ready = [&]() -> int {
+    auto compile = [&](Ready &r) {
+        const uint64_t S = tile_qubits(r.sp);
+        std::vector<Gate> local; // retargeted copies
+        local.reserve(r.gates.size());
+        std::vector<const Gate *> ptrs;
+        ptrs.reserve(r.gates.size());
+        for (int gi : r.gates) {
+            const Gate *g = &gs[gi];
+            if (!((S >> g->t[0]) & 1ull)) {
+                local.push_back(retarget_phase(*g, S));
+                g = &local.back();
+            }
+            ptrs.push_back(g);
+        }
+        r.code = compile_pass(r.sp, ptrs, kSweepW, h->dtype == SV_C64, nullptr, true, kGroupBits);
+    };
+    auto launch_ready = [&](bool *full) -> int {
         size_t total = 0, at = 0;
+        *full = false;
         for (Ready &r : ready) {
             r.off = total;
             if (r.tiled) total += align256(r.code.bytes());
         }
         int rc = SV_OK;
         if (total) {
-            if ((rc = room.take(h, total, &at))) return rc;
+            if ((rc = room.take(h, total, &at, full))) return rc;
             for (Ready &r : ready)
                 if (r.tiled) stage_pass(h, r.code, at + r.off);
             if ((rc = upload_arena(h, total, at))) return rc;
         }
         for (const Ready &r : ready)
-            if ((rc = r.tiled ? launch_pass(h, r.code, at + r.off) : apply_one(h, gs[(size_t)r.single]))) return rc;
+            if ((rc = r.tiled ? launch_pass(h, r.code, at + r.off) : apply_one(h, gs[(size_t)r.gates[0]]))) return rc;
         ready.clear();
         return SV_OK;
+    };
+    // Launches 'ready', one pass; where it does not fit the arena, its first
+    // half of gates and then the others, on the same tile.
+    auto launch_one = [&]() -> int {
+        std::vector<Ready> rest;
+        for (;;) {
+            bool full = false;
+            const int rc = launch_ready(&full);
+            if (full && ready[0].gates.size() > 1) {
+                Ready second = std::move(ready[0]);
+                Ready first{};
+                const size_t half = second.gates.size() / 2;
+                first.gates.assign(second.gates.begin(), second.gates.begin() + (ptrdiff_t)half);
+                second.gates.erase(second.gates.begin(), second.gates.begin() + (ptrdiff_t)half);
+                first.sp = second.sp;
+                first.tiled = true;
+                rest.push_back(std::move(second));
+                ready[0] = std::move(first);
+            } else if (rc) {
+                return rc;
+            } else if (rest.empty()) {
+                return SV_OK;
+            } else {
+                ready.push_back(std::move(rest.back()));
+                rest.pop_back();
+            }
+            compile(ready[0]);
+        }
     };
     PassScheduler ps = scheduler(gs, mmax, lmin, true, lookahead_level(h));
     for (Pass p; ps.next(&p);) {
         if (p.gates.empty()) continue;
         Ready r{};
-        r.single = p.gates[0];
         r.tiled = p.gates.size() > 1 || needs_tile(h->dtype, gs[p.gates[0]]);
         if (r.tiled) {
             uint64_t needed = 0;
             for (int gi : p.gates) needed |= tile_need(gs[gi]);
-            TileSpec sp{};
-            tile_layout(h->n, mmax, lmin, needed, &sp);
-            const uint64_t S = tile_qubits(sp);
-            std::vector<Gate> local; // retargeted copies
-            local.reserve(p.gates.size());
-            std::vector<const Gate *> ptrs;
-            ptrs.reserve(p.gates.size());
-            for (int gi : p.gates) {
-                const Gate *g = &gs[gi];
-                if (!((S >> g->t[0]) & 1ull)) {
-                    local.push_back(retarget_phase(*g, S));
-                    g = &local.back();
-                }
-                ptrs.push_back(g);
-            }
-            r.code = compile_pass(sp, ptrs, kSweepW, h->dtype == SV_C64, nullptr, true, kGroupBits);
+            tile_layout(h->n, mmax, lmin, needed, &r.sp);
         }
+        r.gates = std::move(p.gates);
+        if (r.tiled) compile(r);
         ready.push_back(std::move(r));
         int rc;
-        if (each && (rc = launch_ready())) return rc;
+        if (each && (rc = launch_one())) return rc;
     }
-    const int rc = launch_ready();
+    bool full = false;
+    const int rc = launch_ready(&full);
     return rc ? rc : room.done(h);
 }
 
@@ -1822,6 +1858,7 @@ struct FusedPass {
     // register sweeps on the same tile (k_tile, 'code')
     bool plain = false;
     PassCode code;
+    std::vector<Gate> gates; // of a plain pass
     double cost = 0.0; // modelled time, ms per 2^30 amplitudes
     TileSpec sp{};
     int m = 0;
@@ -2101,6 +2138,7 @@ static int compile_fused_gates(const sv_state *h, const std::vector<Gate> &gs, i
             fp.cost = plain_pass_cost(h, as_fitted ? compile_pass(sp, ptrs, kSweepW, f32, nullptr, true, 0, 0, false) : fp.code, prec);
             if (fp.cost < best.cost) {
                 pack_records(fp.code, f32);
+                fp.gates = std::move(local);
                 best = std::move(fp);
                 best_blocks = 0;
             }
@@ -2219,35 +2257,66 @@ static int launch_fused(sv_state *h, const FusedPass &fp, size_t off) {
     return SV_OK;
 }
 
-// Stage, upload and launch a sequence of fused passes.
-static int run_fused_passes(sv_state *h, std::vector<FusedPass> &fps, ArenaRoom &room) {
-    std::vector<size_t> offs(fps.size());
-    size_t total = 0, at = 0;
-    for (size_t i = 0; i < fps.size(); ++i) {
-        offs[i] = total;
-        total += align256(fused_pass_bytes(h, fps[i]));
+// The first half of a pass that does not fit the arena; fp keeps the second,
+// on the same tile.
+static FusedPass split_fused(const sv_state *h, FusedPass &fp) {
+    FusedPass first;
+    first.plain = fp.plain;
+    first.sp = fp.sp;
+    first.m = fp.m;
+    if (fp.plain) {
+        const auto half = fp.gates.begin() + (ptrdiff_t)(fp.gates.size() / 2);
+        first.gates.assign(fp.gates.begin(), half);
+        fp.gates.erase(fp.gates.begin(), half);
+        for (FusedPass *p : {&first, &fp}) {
+            std::vector<const Gate *> ptrs;
+            for (const Gate &g : p->gates) ptrs.push_back(&g);
+            p->code = compile_pass(p->sp, ptrs, kSweepW, h->dtype == SV_C64, nullptr, true, kGroupBits);
+        }
+        return first;
     }
-    if (!total) return SV_OK;
-    int rc = room.take(h, total, &at);
+    const size_t n = fp.blocks.size(), k = n / 2;
+    first.k = fp.k;
+    first.engine = fp.engine;
+    first.direct = fp.direct;
+    first.moves = fp.moves;
+    first.flops_per_amp = fp.flops_per_amp * (double)k / (double)n;
+    fp.flops_per_amp -= first.flops_per_amp;
+    first.blocks.assign(fp.blocks.begin(), fp.blocks.begin() + (ptrdiff_t)k);
+    first.mats.assign(fp.mats.begin(), fp.mats.begin() + (ptrdiff_t)k);
+    fp.blocks.erase(fp.blocks.begin(), fp.blocks.begin() + (ptrdiff_t)k);
+    fp.mats.erase(fp.mats.begin(), fp.mats.begin() + (ptrdiff_t)k);
+    return first;
+}
+
+// Stage, upload and launch a fused pass, in parts where it does not fit the
+// arena.
+static int run_fused_pass(sv_state *h, FusedPass fp, ArenaRoom &room) {
+    const size_t bytes = align256(fused_pass_bytes(h, fp));
+    size_t at = 0;
+    bool full = false;
+    int rc = room.take(h, bytes, &at, &full);
+    if (full && (fp.plain ? fp.gates.size() : fp.blocks.size()) > 1) {
+        FusedPass first = split_fused(h, fp);
+        rc = run_fused_pass(h, std::move(first), room);
+        return rc ? rc : run_fused_pass(h, std::move(fp), room);
+    }
     if (rc) return rc;
-    for (size_t i = 0; i < fps.size(); ++i) {
-        if (fps[i].plain) stage_pass(h, fps[i].code, at + offs[i]);
-        else stage_fused(h, fps[i], at + offs[i]);
-    }
-    if ((rc = upload_arena(h, total, at))) return rc;
-    for (size_t i = 0; i < fps.size(); ++i)
-        if ((rc = launch_fused(h, fps[i], at + offs[i]))) return rc;
-    return SV_OK;
+    if (fp.plain) stage_pass(h, fp.code, at);
+    else stage_fused(h, fp, at);
+    if ((rc = upload_arena(h, bytes, at))) return rc;
+    return launch_fused(h, fp, at);
 }
 
 // Fuse and run a gate list.  Each pass is launched as soon as it is compiled
 // (about a millisecond of host time, on any size of state).
 static int run_fused_gates(sv_state *h, const std::vector<Gate> &gs, int k_max, int prec, int *n_blocks) {
     ArenaRoom room;
-    std::vector<FusedPass> ready(1);
-    const int rc = compile_fused_gates(h, gs, k_max, prec, n_blocks, [&](FusedPass fp) -> int {
-        ready[0] = std::move(fp);
-        return run_fused_passes(h, ready, room);
+    // one block of five qubits with all its variants always fits this much,
+    // one gate much less: without it nothing is launched
+    int rc = gs.empty() ? SV_OK : ensure_arena(h, (size_t)1 << 20);
+    if (!rc) rc = compile_fused_gates(h, gs, k_max, prec, n_blocks, [&](FusedPass fp) -> int {
+        return run_fused_pass(h, std::move(fp), room);
     });
     return rc ? rc : room.done(h);
 }
@@ -3024,7 +3093,7 @@ int sv_apply_fused(sv_handle h, int k, const int *qubits, const double *U, int p
     for (int i = 0; i < D * D; ++i) B.M[i] = {U[2 * i], U[2 * i + 1]};
     std::vector<FusedPass> fps = compile_fused(h, std::vector<Block>{B}, prec);
     ArenaRoom room;
-    return run_fused_passes(h, fps, room);
+    return run_fused_pass(h, std::move(fps[0]), room); // one block: one pass
 }
 
 int sv_fuse(int n_qubits, const sv_op *ops, int n_ops, const double *params, int n_params,
