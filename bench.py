@@ -68,7 +68,9 @@ def measured_traffic(kernel_key: str):
 def roofline_of(key: str, cnt: int, ms: float, by: float, fl: float) -> dict:
     """Roofline of one kernel from its launches: the binding roof is the one
     of the kernel's arithmetic intensity (algorithmic flops per algorithmic
-    byte) against the vector-ALU ridge; both views are reported."""
+    byte) against the vector-ALU ridge; both views are reported.  Tile passes
+    of a register that spreads from a basis state leave tiles of zeros as they
+    are: the algorithmic bytes count their stores all the same."""
     sec = ms * 1e-3 / cnt
     gbs = (by / cnt) / sec / 1e9
     tfl = (fl / cnt) / sec / 1e12
@@ -152,17 +154,27 @@ def target_bucket(lo: int) -> str:
     return "q?"
 
 
+def fill_dense(amps, torch):
+    """Normally distributed amplitudes, of norm 1 on average."""
+    for c0 in range(0, amps.numel(), 1 << 28):
+        torch.view_as_real(amps[c0:c0 + (1 << 28)]).normal_().mul_((2.0 * amps.numel()) ** -0.5)
+
+
 def per_gate_breakdown(regs, lib, sv, _lib):
     """Alg. 1 as the paper runs it, one launch per gate (sv_run in per-gate
-    mode, one gate per call) over the headline circuits of every register,
-    untimed: each launch's kernel time from the library's HIP events,
+    mode, one gate per call) over the headline circuits' gates on every
+    register, untimed: each launch's kernel time from the library's HIP events,
     grouped by kernel and by the gate's lowest stride qubit.  GB/s counts the
     launch's algorithmic bytes (2 s N / 2^controls; phase gates touch only
-    their subspace)."""
+    their subspace); the register starts dense, since the kernels do not store
+    the zeros that a basis state is full of, and bytes that are not moved are
+    no rate.  The register is left in the circuits' final state."""
+    import torch
     out = {}
     for r in regs:
         h = r["state"].handle
         _lib.check(lib.sv_set_basis(h, r["qft"].basis))
+        fill_dense(r["state"].amps, torch)
         _lib.check(lib.sv_timing(h, 1))
         agg = {}
         for key, c in (("ops_qft", r["qft"]), ("ops_rnd", r["rnd"])):
@@ -178,6 +190,9 @@ def per_gate_breakdown(regs, lib, sv, _lib):
                     a[1] += ms
                     a[2] += by
         _lib.check(lib.sv_timing(h, 0))
+        _lib.check(lib.sv_set_basis(h, r["qft"].basis))
+        for key, c in (("ops_qft", r["qft"]), ("ops_rnd", r["rnd"])):
+            _lib.check(lib.sv_run(h, sv._opptr(r[key]), len(c.gates), None, 0, sv.SV_RUN_TILED))
         reg = {}
         for kname, buckets in agg.items():
             tot = [sum(v[i] for v in buckets.values()) for i in range(3)]
