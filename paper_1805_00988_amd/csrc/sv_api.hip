@@ -1387,10 +1387,14 @@ static std::vector<Pass> all_passes(PassScheduler ps) {
 // phase gates diag(1, e^{i phi}) with any controls (symmetric in their
 // qubits: the target can be any of them, and with none in the tile the
 // factor is uniform per tile) and uncontrolled one-qubit diagonal gates
-// (uniform per tile for each value of the target), which need none.
+// (uniform per tile for each value of the target), which need none.  The
+// latter are applied as d0 and, where the target is 1, d1 / d0: not for a d0
+// of zero or far below d1, whose quotient is none or leaves the precision.
 static uint64_t tile_need(const Gate &g) {
-    if (is_diag1(g) && (is_one(g.U) || g.ctrl == 0)) return 0;
-    return g.tmask();
+    if (!is_diag1(g)) return g.tmask();
+    if (is_one(g.U)) return 0;
+    const double a0 = std::hypot(g.U[0], g.U[1]), a1 = std::hypot(g.U[6], g.U[7]);
+    return g.ctrl == 0 && a0 > 1e-6 * a1 && a0 > 1e-30 ? 0 : g.tmask();
 }
 
 // outside_diag: let the gates tile_need exempts leave their targets out of
