@@ -159,8 +159,8 @@ hipError_t launch_adjoint_init(const void *psi, void *lam, int n, int dtype, int
 // exchanged through LDS between sweeps one component of one vector at a time,
 // and undoes each sweep's gates on both.  A parametrised gate
 // is preceded by a probe record that adds the group's share of
-// Im <lam| M |psi> to the gate's slot (wave reduction, then lane 0 adds it
-// to its wave's row of slots).  The slot sums of a workgroup cover all its
+// Im <lam| M |psi> to the gate's slot (wave reduction, then the wave adds the
+// sum to its own row of slots).  The slot sums of a workgroup cover all its
 // tiles and are written once at the end.
 static_assert(1 << (adjoint_tile_qubits(SV_C64) - 4) == kAdjThreads &&
                   1 << (adjoint_tile_qubits(SV_C128) - 3) == kAdjThreads,
@@ -259,8 +259,9 @@ __global__ __launch_bounds__(kAdjThreads) void k_adjoint_tile(typename AV<T>::ty
     // LDS of a tile per vector: more workgroups per CU)
     extern __shared__ char lds[];
     const uint32_t tsize = 1u << m;
-    // one row of slot sums per wave, written only by that wave's lane 0 (no
-    // atomics): the workgroup's sums are then formed in a fixed order and the
+    // one row of slot sums per wave, which no other wave touches (no
+    // atomics; the lanes of a wave read, add and write a word in step, all
+    // with the same value): the workgroup's sums are then formed in a fixed order and the
     // gradient is the same bit for bit on every run
     constexpr int kWaves = kAdjThreads / 64;
     __shared__ double slot_acc[kWaves][kMaxAdjSlots];

@@ -456,13 +456,14 @@ static_assert(1 << (tile_max_qubits(SV_C64) - kSweepW) == kTileThreads<float> &&
 // Register qubits per sweep of the batch and adjoint kernels, which hold 8
 // complex128 amplitudes per group.  The tile pass holds 16 (kSweepW) in both
 // precisions.  For complex128 that doubled what a CU has in flight at its
-// four waves per SIMD: a group of 8 in a 512-thread workgroup took the LDS of
-// a whole complex128 tile, 64 KiB, of which two fit; now the two components
-// cross LDS one after the other, in 32 KiB and with two more barriers, and
-// four workgroups of 256 threads fit.  Half the records per amplitude and
-// fewer sweeps come with it: depth 20 at 28 qubits 49.6 -> 40.1 ms.  The same
-// exchange takes complex64 from five to seven waves per SIMD (29 qubits 48.3
-// -> 44.7 ms).
+// four waves per SIMD: with whole amplitudes crossing LDS, 512 threads with a
+// group of 8 each took 64 KiB, of which two workgroups fit; now the two
+// components cross one after the other, with two more barriers, and the same
+// 64 KiB serve a tile of 512 groups of 16.  Half the records per amplitude and
+// fewer sweeps come with it: depth 20 at 28 qubits 49.6 -> 40.1 ms, on tiles of
+// 2^12, of which four workgroups of 256 threads fit (present tiles: see
+// kTileThreads).  The same exchange took complex64 tiles of 2^12 from five to
+// seven waves per SIMD (29 qubits 48.3 -> 44.7 ms); those of 2^14 run eight.
 int sweep_width(int dtype) { return dtype == SV_C64 ? 4 : 3; }
 
 // Waves per SIMD the register allocation aims at.

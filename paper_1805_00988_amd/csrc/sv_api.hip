@@ -2026,12 +2026,13 @@ static std::vector<FusedPass> compile_fused(const sv_state *h, const std::vector
 // loads, stores and exchanges, at least the time of its trip of the state.
 // It only ranks the alternatives of one pass.
 //
-// Split-BF16 calls rank theirs by the model fitted to the first kernels, on
-// the records without permuted stores.  A block's operands there are rounded
-// to 2^-17, a plain pass's to 2^-24, so the ranking decides the result from
-// its fifth digit on: it has to follow from the gates, not from how fast the
-// plain sweeps have become.  The present figures would gain them nothing on
-// the 28-qubit fusion workload (31.4 and 31.5 ms; 3.08 and 2.84 at 24 qubits).
+// Split-BF16 calls on complex64 rank theirs by the model fitted to the first
+// kernels, on the records without permuted stores.  A block's operands there
+// are rounded to 2^-17, a plain pass's to 2^-24, so the ranking decides the
+// result from its fifth digit on: another model gives such calls other results.
+// The present figures would gain them nothing on the 28-qubit fusion workload
+// (31.4 and 31.5 ms; 3.08 and 2.84 at 24 qubits).  A pass with an X gate is
+// compiled twice for this.
 static double fused_pass_cost(const sv_state *h, const FusedPass &fp) {
     const bool c64 = h->dtype == SV_C64;
     double t = c64 ? (fp.engine == SV_PREC_FP32 ? 3.0 : 3.4) : 6.5;
